@@ -76,6 +76,7 @@ __device__ __forceinline__ void batch_phase_body(
     uint64_t roff[R];
     io_reg_offsets<C, RB>(pass, roff);  // bytes of C
     const uint64_t end = run_end < hi ? run_end : hi;
+    warm_program<T>(pass, ops, tid);
     for (; g < end; ++g) {
       const uint64_t t = g - work[e].tile_begin;
       uint64_t base = t;

@@ -156,6 +156,7 @@ __device__ __forceinline__ void tile_body(typename CxT<T>::type* __restrict__ am
       a[j] = *reinterpret_cast<const C*>(wp + ro + lane_off);
     }
   }
+  if (blockIdx.x < kWarmTiles) warm_program<T>(pass, ops, tid);
   // complex64 with 16 registers and complex128 re-lay out in halves (half
   // the LDS)
   tile_apply<T, RB, kHalves<T, RB>>(a, lds, pass, segs, ops, base, tid, true);

@@ -1346,6 +1346,8 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
                               (o.kind == kOpPhaseBlock ? 1.0 : frac);
     }
   }
+  tp.op_begin = op_base;
+  tp.n_ops = int32_t(tops->size()) - op_base;
   // Phase-block records follow the pass's ops, in whole TileOp slots.
   for (const Blob& bl : blobs) {
     const size_t at = tops->size();
@@ -1354,6 +1356,7 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
     std::memcpy(static_cast<void*>(&(*tops)[at]), bl.bytes.data(), bl.bytes.size());
     (*tops)[bl.op].blob = int32_t((at - size_t(bl.op)) * sizeof(TileOp));
   }
+  tp.n_blob = int32_t(tops->size()) - op_base - tp.n_ops;
   tpasses->push_back(tp);
   return "";
 }

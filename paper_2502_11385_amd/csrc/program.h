@@ -191,7 +191,9 @@ struct alignas(16) TilePass {
   int32_t flags;  // kPassLane32 | kPassSpread | kPassOutputs
   int32_t q[16];
   int32_t out_spec;  // kPassOutputs: byte offset from this record
-  int32_t pad_[3];
+  int32_t op_begin;  // the pass's TileOp slots: n_ops ops, then n_blob slots
+  int32_t n_ops;     // that hold its phase-block records
+  int32_t n_blob;
 };
 
 // One gate of a fused block, in the block's local qubit numbering
