@@ -596,6 +596,9 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
       fblocks.push_back(fb);
     }
   }
+  for (TilePass& tp : tpasses)
+    set_lds_offsets(tile_lds_map(s->prec, po.reg_log2), po.reg_log2, &tp,
+                    tsegs.data());
   // Outputs: which ones the last tile pass folds (the last pass of the plan
   // must be a tile pass; a key may span at most L - reg_log2 tile bits, so
   // that each thread's registers fall in one group), and the scratch
@@ -702,6 +705,8 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
     hp->out_spec = int32_t(o_os - o_lp);
     tpasses[size_t(op.last_tile)].flags |= kPassOutputs;
   }
+  // the tile kernels read one op past the one they apply
+  buf.resize(buf.size() + sizeof(TileOp));
   const auto t1 = std::chrono::steady_clock::now();
 
   if ((st = select_device(s)) != QSV_OK) return st;
@@ -1225,19 +1230,19 @@ qsv_status qsv_debug_emulate_tiled(const qsv_circuit* circ, int32_t n,
               (op.mux_reg >= 0 && sg.reg_bits[op.mux_reg] != op.mux))
             return fail(QSV_ERR_DEVICE, "tile op has an inconsistent mux_reg");
           // the ops run by their dispatch codes, as the kernels run them
-          const int cls = op.code >> 3, creg = op.code & 7;
+          const int cls = op.code >> 6, creg = op.code & 7;
           const bool dense = cls <= kCodeCtrlMux;
           if (dense != (op.kind == kOpDense1) ||
               (dense && (creg != op.reg || creg >= po.reg_log2)) ||
               (cls == kCodePhase && op.kind != kOpPhase) ||
               (cls == kCodeDiag && op.kind != kOpDiag) ||
               (cls == kCodePhaseBlock && op.kind != kOpPhaseBlock) ||
-              ((cls == kCodeUniform || cls == kCodeRegMux ||
-                cls == kCodeThreadMux) && op.lctrl != 0) ||
+              (cls <= kCodeThreadMux && (op.lctrl != 0 || op.gctrl != 0)) ||
               ((cls == kCodeUniform || cls == kCodeCtrl) &&
                (op.arg < 0 || op.arg > 63)) ||
               (cls == kCodeRegMux &&
-               (op.arg < 0 || op.arg >= po.reg_log2 || op.arg == creg)) ||
+               (op.arg < 0 || op.arg >= po.reg_log2 || op.arg == creg ||
+                op.arg != (op.code >> 3 & 7))) ||
               (cls == kCodeThreadMux &&
                [&] {  // a thread bit: no register bit of the segment
                  for (int i = 0; i < po.reg_log2; ++i)

@@ -148,6 +148,9 @@ std::string append_variant(int w, const std::vector<HostGate>& G, int b,
       hp->tiles += uint64_t(1) << (w - p.L);
       bc.n_passes = 1;
     }
+    for (int p = 0; p < bc.n_passes; ++p)
+      set_lds_offsets(batch_lds_map(b, RB), RB,
+                      &hp->passes[size_t(bc.pass_begin + p)], hp->segs.data());
     if (hp->out_offsets.empty()) hp->out_offsets.push_back(0);
     bc.out_offset = hp->out_offsets[i];
     hp->out_offsets.push_back(hp->out_offsets[i] + (uint64_t(1) << w));
@@ -281,6 +284,7 @@ qsv_status upload_program(qsv_batch b, const qsv_variant* vars, int L, int RB) {
   b->o_pass = put(buf, b->hp.passes);
   b->o_seg = put(buf, b->hp.segs);
   b->o_op = put(buf, b->hp.ops);
+  buf.resize(buf.size() + sizeof(TileOp));  // kernels read one op ahead
   if (hipMalloc(&b->prog, std::max<size_t>(buf.size(), 256)) != hipSuccess) {
     b->prog = nullptr;
     (void)hipGetLastError();

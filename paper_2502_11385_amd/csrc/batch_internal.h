@@ -41,6 +41,12 @@ void finalize_program(HostProgram* hp);
 std::string append_variant(int w, const std::vector<HostGate>& G, int b,
                            int L, int RB, HostProgram* hp, double* cost);
 
+// The LDS map of the batch kernel's re-layouts (amplitude bytes, register
+// bits).
+inline LdsMap batch_lds_map(int b, int rb) {
+  return b == 16 ? kLds16 : (rb == 4 ? kLds4 : kLds8);
+}
+
 // True when every gate can run inside batched tiles.
 inline bool batchable(const std::vector<HostGate>& G) {
   for (const HostGate& g : G)

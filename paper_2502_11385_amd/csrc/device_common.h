@@ -104,6 +104,10 @@ hipError_t launch_dense(int prec, void* amp, int n, const HostGate& g,
 // Plain diagonal gate (any k, controls).
 hipError_t launch_diag(int prec, void* amp, int n, const HostGate& g,
                        hipStream_t stream);
+// The LDS map of the tile kernel's re-layouts (prec, register bits).
+inline LdsMap tile_lds_map(int prec, int rb) {
+  return prec == 1 && rb == 4 ? kLds4 : kLds8;
+}
 // One tile pass: pass/segs/ops point into the device program buffer,
 // host_pass is the host copy of *pass; rb is the register bits.
 hipError_t launch_tile(int prec, int rb, void* amp, int n,

@@ -28,8 +28,6 @@ __device__ __forceinline__ void batch_phase_body(
     typename CxT<T>::type* __restrict__ states) {
   using C = typename CxT<T>::type;
   constexpr int R = 1 << RB;
-  extern __shared__ double lds_raw[];
-  C* lds = reinterpret_cast<C*>(lds_raw);
   const uint32_t tid = threadIdx.x;
   // this work-group's share of the phase: the tiles whose cumulative cost
   // start lies in [clo, chi)
@@ -76,7 +74,7 @@ __device__ __forceinline__ void batch_phase_body(
     uint64_t roff[R];
     io_reg_offsets<C, RB>(pass, roff);  // bytes of C
     const uint64_t end = run_end < hi ? run_end : hi;
-    warm_program<T>(pass, ops, tid);
+    warm_program<T>(pass, segs, ops, tid);
     for (; g < end; ++g) {
       const uint64_t t = g - work[e].tile_begin;
       uint64_t base = t;
@@ -98,8 +96,8 @@ __device__ __forceinline__ void batch_phase_body(
         }
       }
       // complex64 with 16 registers re-lays out in halves (half the LDS)
-      tile_apply<T, RB, sizeof(T) == 4 && RB == 4>(a, lds, pass, segs, ops,
-                                                  base, tid, active);
+      tile_apply<T, RB, sizeof(T) == 4 && RB == 4>(a, pass, segs, ops, base,
+                                                  tid, active);
       if (active) {
         if (last) {
           const char* ob =

@@ -29,13 +29,18 @@ template <typename T, int RB>
 constexpr bool kHalves = (sizeof(T) == 4 && RB == 4) || sizeof(T) == 8;
 
 // Tile index -> global index of the tile's first amplitude: the index's
-// bits spread over the non-tile qubits.
+// bits spread over the non-tile qubits, run by run (four cover every tile
+// of up to four groups of consecutive qubits, so that the usual tile needs
+// one batch of loads).
 __device__ __forceinline__ uint64_t tile_base(const TilePass* pass,
                                               uint32_t tile) {
   const cptr<TilePass> cp = as_const(pass);
-  uint64_t base = tile;
-  const int L = cp->L;
-  for (int b = 0; b < L; ++b) base = insert_zero64(base, cp->q[b]);
+  uint64_t base = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)  // unused runs have mask 0
+    base |= uint64_t(tile & cp->out_mask[i]) << cp->out_shift[i];
+  for (int i = 4; i < cp->n_out; ++i)
+    base |= uint64_t(tile & cp->out_mask[i]) << cp->out_shift[i];
   return base;
 }
 
@@ -121,29 +126,42 @@ __device__ __forceinline__ void tile_body(typename CxT<T>::type* __restrict__ am
   using Off = std::conditional_t<LANE32, uint32_t, uint64_t>;
   constexpr int R = 1 << RB;
   extern __shared__ double lds_raw[];
-  C* lds = reinterpret_cast<C*>(lds_raw);
+  C* lds = reinterpret_cast<C*>(lds_raw);  // the folded outputs' staging
   const uint32_t tid = threadIdx.x;
   uint32_t tix = blockIdx.x;
-  if (pass->flags & kPassSpread) {
+  if (as_const(pass)->flags & kPassSpread) {
     const uint32_t tb = 31u - __builtin_clz(gridDim.x);  // log2(#tiles)
     tix = tb ? (__builtin_bitreverse32(tix) >> (32u - tb)) : 0u;
   }
+  const cptr<TilePass> cp = as_const(pass);
   const uint64_t base = tile_base(pass, tix);
-  const int W = pass->L - RB;
+  const int W = cp->L - RB;
+  // the tile's qubits, read together
+  int32_t q[16];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const u32x4 v = as_const(reinterpret_cast<const u32x4*>(pass->q))[i];
+    q[4 * i] = int32_t(v.x);
+    q[4 * i + 1] = int32_t(v.y);
+    q[4 * i + 2] = int32_t(v.z);
+    q[4 * i + 3] = int32_t(v.w);
+  }
   const int lane_bits = W < 6 ? W : 6;
   const uint32_t lane = tid & 63u;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   Off lane_el = 0;
-  for (int b = 0; b < lane_bits; ++b)
-    if (lane >> b & 1) lane_el |= Off(1) << pass->q[b];
+#pragma unroll
+  for (int b = 0; b < 6; ++b)
+    if (b < lane_bits) lane_el |= Off(lane >> b & 1u) << q[b];
   const Off lane_off = lane_el * Off(sizeof(C));
   uint64_t wave_el = base;
-  for (int b = 6; b < W; ++b)
-    if (wave >> (b - 6) & 1) wave_el |= uint64_t(1) << pass->q[b];
+#pragma unroll
+  for (int b = 6; b < 9; ++b)
+    if (b < W) wave_el |= uint64_t(wave >> (b - 6) & 1u) << q[b];
   // byte step of each register bit (uniform)
   uint64_t rstep[RB];
 #pragma unroll
-  for (int i = 0; i < RB; ++i) rstep[i] = uint64_t(sizeof(C)) << pass->q[W + i];
+  for (int i = 0; i < RB; ++i) rstep[i] = uint64_t(sizeof(C)) << cp->q[W + i];
   C a[R];
   {
     const char* wp = reinterpret_cast<const char*>(amp) + wave_el * sizeof(C);
@@ -156,10 +174,10 @@ __device__ __forceinline__ void tile_body(typename CxT<T>::type* __restrict__ am
       a[j] = *reinterpret_cast<const C*>(wp + ro + lane_off);
     }
   }
-  if (blockIdx.x < kWarmTiles) warm_program<T>(pass, ops, tid);
+  if (blockIdx.x < kWarmTiles) warm_program<T>(pass, segs, ops, tid);
   // complex64 with 16 registers and complex128 re-lay out in halves (half
   // the LDS)
-  tile_apply<T, RB, kHalves<T, RB>>(a, lds, pass, segs, ops, base, tid, true);
+  tile_apply<T, RB, kHalves<T, RB>>(a, pass, segs, ops, base, tid, true);
   // The store addresses are formed again from the few values they derive
   // from (opaque to the compiler), so that the sixteen register addresses
   // are not held in scalar registers across the op loop.
@@ -213,20 +231,16 @@ __global__ void __launch_bounds__(512)
   tile_body<T, RB, LANE32>(amp, pass, segs, ops);
 }
 
-// Kernel variants: 0 = 64-bit lane offsets, 1 = 32-bit lane offsets.
-template <typename T, int RB, int V>
-static const void* tile_fn() {
-  if constexpr (sizeof(T) == 4 && RB == 4)
-    return reinterpret_cast<const void*>(&tile_kernel_c64_rb4<V == 1>);
-  else
-    return reinterpret_cast<const void*>(&tile_kernel<T, RB, V == 1>);
-}
-
-template <typename T, int RB, int V>
+template <typename T, int RB, bool LANE32>
 static hipError_t tile_launch(void* amp, int n, int L, bool outputs,
                               const TilePass* pass, const TileSeg* segs,
                               const TileOp* ops, hipStream_t stream) {
   using C = typename CxT<T>::type;
+  void (*fn)(C*, const TilePass*, const TileSeg*, const TileOp*);
+  if constexpr (sizeof(T) == 4 && RB == 4)
+    fn = tile_kernel_c64_rb4<LANE32>;
+  else
+    fn = tile_kernel<T, RB, LANE32>;
   // re-layouts in halves need one component per amplitude; the folded
   // outputs stage FP64 values (8 bytes)
   const size_t lds = !kHalves<T, RB> ? size_t(sizeof(C)) << L
@@ -236,22 +250,29 @@ static hipError_t tile_launch(void* amp, int n, int L, bool outputs,
   // scheduler and its clients) reach this together, hence call_once
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
-  std::call_once(once, [] {
-    attr_err = hipFuncSetAttribute(tile_fn<T, RB, V>(),
+  std::call_once(once, [&] {
+    attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                    hipFuncAttributeMaxDynamicSharedMemorySize,
                                    160 * 1024);
   });
   if (attr_err != hipSuccess) return attr_err;
   const unsigned threads = 1u << (L - RB);
   const uint64_t tiles = uint64_t(1) << (n - L);
-  if constexpr (sizeof(T) == 4 && RB == 4) {
-    tile_kernel_c64_rb4<V == 1><<<unsigned(tiles), threads, lds, stream>>>(
-        static_cast<C*>(amp), pass, segs, ops);
-  } else {
-    tile_kernel<T, RB, V == 1><<<unsigned(tiles), threads, lds, stream>>>(
-        static_cast<C*>(amp), pass, segs, ops);
-  }
+  fn<<<unsigned(tiles), threads, lds, stream>>>(static_cast<C*>(amp), pass,
+                                                segs, ops);
   return hipGetLastError();
+}
+
+template <typename T, int RB>
+static hipError_t tile_launch_t(void* amp, int n, const TilePass& hp,
+                                const TilePass* pass, const TileSeg* segs,
+                                const TileOp* ops, hipStream_t stream) {
+  const bool outputs = (hp.flags & kPassOutputs) != 0;
+  if (hp.flags & kPassLane32)
+    return tile_launch<T, RB, true>(amp, n, hp.L, outputs, pass, segs, ops,
+                                    stream);
+  return tile_launch<T, RB, false>(amp, n, hp.L, outputs, pass, segs, ops,
+                                   stream);
 }
 
 hipError_t launch_tile(int prec, int rb, void* amp, int n,
@@ -259,34 +280,21 @@ hipError_t launch_tile(int prec, int rb, void* amp, int n,
                        const TileSeg* segs, const TileOp* ops,
                        hipStream_t stream) {
   const int L = host_pass.L;
-  const bool boff32 = (host_pass.flags & kPassLane32) != 0;
   if (L - rb < 0 || L - rb > 9 || L > kMaxTileBits || n - L > 31)
     return hipErrorInvalidValue;
-  const bool outputs = (host_pass.flags & kPassOutputs) != 0;
-#define QSV_T(T, RBV, V) \
-  return tile_launch<T, RBV, V>(amp, n, L, outputs, pass, segs, ops, stream)
+#define QSV_T(T, RB) \
+  return tile_launch_t<T, RB>(amp, n, host_pass, pass, segs, ops, stream)
   if (prec == 1) {
-    if (rb == 3) {
-      if (boff32) QSV_T(float, 3, 1);
-      QSV_T(float, 3, 0);
-    }
-    if (rb == 4) {
-      if (boff32) QSV_T(float, 4, 1);
-      QSV_T(float, 4, 0);
-    }
-    if (rb != 5) return hipErrorInvalidValue;
-    if (boff32) QSV_T(float, 5, 1);
-    QSV_T(float, 5, 0);
+    if (rb == 3) QSV_T(float, 3);
+    if (rb == 4) QSV_T(float, 4);
+    if (rb == 5) QSV_T(float, 5);
+    return hipErrorInvalidValue;
   }
   // complex128 tiles use 8 or 16 registers per thread (the planner rejects
   // reg_log2 = 5 for them: 32 double2 registers would spill)
-  if (rb == 3) {
-    if (boff32) QSV_T(double, 3, 1);
-    QSV_T(double, 3, 0);
-  }
-  if (rb != 4) return hipErrorInvalidValue;
-  if (boff32) QSV_T(double, 4, 1);
-  QSV_T(double, 4, 0);
+  if (rb == 3) QSV_T(double, 3);
+  if (rb == 4) QSV_T(double, 4);
+  return hipErrorInvalidValue;
 #undef QSV_T
 }
 

@@ -770,12 +770,12 @@ static uint64_t angle_turns(double ang) {
 // by one bit of the tile's base index: the outer mux qubit, or bit 63,
 // which no index has (its second matrix is then a copy of the first).
 std::string set_op_code(TileOp* op) {
-  int32_t cls = 0;
+  int32_t cls = 0, mux_reg = 0;
   op->arg = 0;
   switch (op->kind) {
     case kOpDense1:
       if (op->mux == kMuxNone || op->mux < 0) {
-        cls = op->lctrl ? kCodeCtrl : kCodeUniform;
+        cls = op->lctrl || op->gctrl ? kCodeCtrl : kCodeUniform;
         if (op->mux == kMuxNone) {
           op->arg = 63;
           std::memcpy(op->m2, op->m, sizeof op->m);
@@ -783,26 +783,29 @@ std::string set_op_code(TileOp* op) {
         } else {
           op->arg = -1 - op->mux;
         }
-      } else if (op->lctrl == 0 && op->mux_reg >= 0) {
+      } else if (op->lctrl || op->gctrl) {
+        cls = kCodeCtrlMux;
+        op->arg = op->mux;
+      } else if (op->mux_reg >= 0) {
         cls = kCodeRegMux;
-        op->arg = op->mux_reg;
+        op->arg = mux_reg = op->mux_reg;
       } else {
-        cls = op->lctrl == 0 ? kCodeThreadMux : kCodeCtrlMux;
+        cls = kCodeThreadMux;
         op->arg = op->mux;
       }
       if (op->reg < 0 || op->reg >= kMaxRegBits)
         return "internal planner error: bad register index";
-      op->code = (cls << 3) | op->reg;
+      op->code = (cls << 6) | (mux_reg << 3) | op->reg;
       return "";
     case kOpPhase:
-      op->code = kCodePhase << 3;
+      op->code = kCodePhase << 6;
       return "";
     case kOpDiag:
-      op->code = kCodeDiag << 3;
+      op->code = kCodeDiag << 6;
       op->arg = op->dk;
       return "";
     case kOpPhaseBlock:
-      op->code = kCodePhaseBlock << 3;
+      op->code = kCodePhaseBlock << 6;
       return "";
     default:
       return "internal planner error: unknown op kind";
@@ -845,6 +848,20 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
   for (int j = 0; j < p.L; ++j) {
     tp.q[j] = p.q[j];
     local_of[p.q[j]] = j;
+  }
+  // runs of outer qubits: tile-index bit b (the b-th outer qubit) is qubit
+  // b + (tile qubits below it); n_out covers the qubits up to the highest
+  // any state has (bits above the state's width are 0 in every tile index)
+  for (int j = 0; j <= p.L; ++j) {
+    const int first = j ? p.q[j - 1] + 1 : 0;
+    const int last = j < p.L ? p.q[j] : std::max(first, 32 + j);
+    if (first >= last) continue;
+    // outer qubits [first, last): tile-index bits from first - j
+    const int lo = first - j, hi = std::min(last - j, 32);
+    if (lo >= hi) continue;
+    tp.out_mask[tp.n_out] = uint32_t(((uint64_t(1) << hi) - 1) ^
+                                     ((uint64_t(1) << lo) - 1));
+    tp.out_shift[tp.n_out++] = j;
   }
   auto place_ctrl = [&](TileOp* op, uint64_t mask) {
     for (int q = 0; q < 64; ++q)
@@ -1359,6 +1376,28 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
   tp.n_blob = int32_t(tops->size()) - op_base - tp.n_ops;
   tpasses->push_back(tp);
   return "";
+}
+
+void set_lds_offsets(LdsMap map, int RB, TilePass* pass, TileSeg* segs) {
+  auto fill = [&](const int32_t* bits, uint32_t* lds) {
+    for (int j = 0; j < (1 << RB); ++j) {
+      uint32_t r = 0;
+      for (int i = 0; i < RB; ++i)
+        if (j >> i & 1) r |= 1u << bits[i];
+      lds[j] = lds_place(map, r);
+    }
+  };
+  int32_t io[kMaxRegBits];
+  for (int i = 0; i < RB; ++i) io[i] = pass->L - RB + i;
+  fill(io, pass->lds);
+  const int32_t* cur = io;
+  for (int s = 0; s < pass->nseg; ++s) {
+    TileSeg& sg = segs[pass->seg_begin + s];
+    fill(sg.reg_bits, sg.lds);
+    sg.moved = !std::equal(cur, cur + RB, sg.reg_bits);
+    cur = sg.reg_bits;
+  }
+  pass->moved = !std::equal(cur, cur + RB, io);
 }
 
 void make_plan(const std::vector<HostGate>& G, int n, int b,

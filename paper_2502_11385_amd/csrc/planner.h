@@ -100,6 +100,10 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
                            std::vector<TileOp>* ops,
                            TileEmitStats* stats = nullptr);
 
+// Fill the re-layout fields (lds, moved) of an emitted pass and its segments
+// for the kernel's LDS map (`segs` is the program's whole segment array).
+void set_lds_offsets(LdsMap map, int reg_log2, TilePass* pass, TileSeg* segs);
+
 // Fill a finished tile op's dispatch code and argument (kernel header)
 // from its kind, mux and controls; returns an error text or "".
 std::string set_op_code(TileOp* op);

@@ -10,6 +10,7 @@ namespace qsv {
 constexpr int kMaxQubits = 34;
 constexpr int kMaxK = 5;
 constexpr int kMaxTileBits = 14;
+constexpr int kMaxOutRuns = kMaxTileBits + 1;
 
 // Tile op kinds.
 enum : int32_t {
@@ -20,18 +21,21 @@ enum : int32_t {
 };
 
 // Dispatch classes of a tile op, precomputed by the planner (TileOp::code
-// = class << 3 | register index of the target).  The kernel reads an op's
-// header and both matrices in one batch of scalar loads and branches once.
+// = class << 6 | mux register << 3 | register index of the target).  The
+// kernel reads an op's header and both matrices in one batch of scalar
+// loads and branches on the code once.  The first three classes, the bulk
+// of every circuit, have no controls.
 //  kCodeUniform:   2x2 matrix mf (m) on register bit `reg`, or mf2 (m2)
 //                  where bit `arg` of the tile's base index is 1 (an outer
 //                  mux qubit; arg = 63, a bit no index has, when there is
 //                  no mux).  The matrix is the same for the whole tile.
 //  kCodeRegMux:    mf where register bit `arg` of the pair's index is 0,
-//                  mf2 where it is 1 (fixed per register pair).
+//                  mf2 where it is 1 (fixed per register pair); the code
+//                  holds that bit too.
 //  kCodeThreadMux: mf or mf2 by tile-local bit `arg`, which a thread bit
 //                  holds (fixed per thread).
 //  kCodeCtrl:      as kCodeUniform, applied only where every tile-local
-//                  bit of lctrl is 1.
+//                  bit of lctrl and every outer qubit of gctrl is 1.
 //  kCodeCtrlMux:   mf or mf2 by tile-local bit `arg`, applied only where
 //                  every bit of lctrl is 1.
 //  kCodePhase:     multiply by mf[0..1] (m[0..1]) where every tile-local
@@ -134,12 +138,34 @@ struct alignas(16) PhaseBlock {
 
 // A run of ops executed with one register layout: the tile-local bits in
 // reg_bits[0..RB-1] (ascending) index each thread's registers; the other
-// tile-local bits, in ascending order, index the threads.
-struct alignas(16) TileSeg {
-  int32_t reg_bits[6];
+// tile-local bits, in ascending order, index the threads.  lds[j] is the
+// byte offset that register j's index bits contribute to an amplitude's
+// place in LDS (see LdsMap), which a re-layout XORs with the thread's part
+// (both filled by set_lds_offsets).
+struct alignas(32) TileSeg {
+  int32_t reg_bits[kMaxRegBits];
+  int32_t moved;  // 1: the layout differs from the one before (the first
+                  // segment's from the I/O layout)
   int32_t op_begin;
   int32_t op_end;
+  uint32_t lds[1 << kMaxRegBits];
 };
+static_assert(sizeof(TileSeg) == 160, "kernels read its lines by this size");
+
+// How a tile-local index r is placed in LDS for a re-layout: at element
+// r ^ f(r), an XOR swizzle that spreads the banks.  Linear over XOR, so a
+// thread's part and a register's part combine by XOR.
+//  kLds4:  4-byte elements, one component per amplitude (complex64, 16
+//          registers, moved in halves).
+//  kLds8:  8-byte elements (complex64 whole; complex128 in halves).
+//  kLds16: 16-byte elements (complex128 whole).
+enum LdsMap : int32_t { kLds4 = 0, kLds8 = 1, kLds16 = 2 };
+
+constexpr uint32_t lds_place(int32_t map, uint32_t r) {
+  return map == kLds4   ? (r ^ (((r >> 5) ^ (r >> 10)) & 31u)) * 4u
+         : map == kLds8 ? (r ^ (((r >> 4) ^ (r >> 8)) & 15u)) * 8u
+                        : (r ^ (((r >> 3) ^ (r >> 6) ^ (r >> 9)) & 7u)) * 16u;
+}
 
 // TilePass flags.
 //  kPassLane32: the lane part of the I/O layout's byte offsets (the lowest
@@ -194,6 +220,13 @@ struct alignas(16) TilePass {
   int32_t op_begin;  // the pass's TileOp slots: n_ops ops, then n_blob slots
   int32_t n_ops;     // that hold its phase-block records
   int32_t n_blob;
+  // The qubits outside the tile as runs of consecutive qubits: bits
+  // out_mask[i] of the tile index, moved up by out_shift[i], are run i.
+  int32_t n_out;
+  uint32_t out_mask[kMaxOutRuns];
+  int32_t out_shift[kMaxOutRuns];
+  int32_t moved;  // 1: the last segment's layout differs from the I/O one
+  uint32_t lds[1 << kMaxRegBits];  // as TileSeg::lds, for the I/O layout
 };
 
 // One gate of a fused block, in the block's local qubit numbering

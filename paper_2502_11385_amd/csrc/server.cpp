@@ -271,6 +271,7 @@ void launch_batched(qsv_server s, Group* g, int prec) {
   const size_t o_c = put_vec(img, hp.circs), o_w = put_vec(img, hp.work),
                o_p = put_vec(img, hp.passes), o_s = put_vec(img, hp.segs),
                o_op = put_vec(img, hp.ops);
+  img.resize(img.size() + sizeof(TileOp));  // kernels read one op ahead
   const int grid = batch_grid(prec, RB, L);
   const size_t outb = size_t(hp.out_offsets.back()) * (b == 8 ? 4 : 8);
   const size_t scrb = size_t(hp.state_amps) * size_t(b);

@@ -10,15 +10,6 @@
 
 namespace qsv {
 
-// Bijective XOR swizzle of tile-local indices to spread LDS banks.
-template <typename T>
-__device__ __forceinline__ uint32_t lds_swz(uint32_t r) {
-  if constexpr (sizeof(T) == 4)
-    return r ^ (((r >> 4) ^ (r >> 8)) & 15u);
-  else
-    return r ^ (((r >> 3) ^ (r >> 6) ^ (r >> 9)) & 7u);
-}
-
 // Pair update (x0, x1) <- M (x0, x1) for a 2x2 complex M = m[0..7]
 // (row-major, interleaved), in place: x0 = (a, b), x1 = (c, d).  Each
 // output first sums the three terms that do not read its own input (in
@@ -358,33 +349,6 @@ __device__ __forceinline__ void dense1_muxreg_regs(C* a, const T* m0,
   }
 }
 
-template <int R, typename C, typename T>
-__device__ __forceinline__ void dense1_muxreg_dispatch(int reg, int k, C* a,
-                                                       const T* m0,
-                                                       const T* m1) {
-#define QSV_D1K(I, K)                                                     \
-  case I * 8 + K:                                                         \
-    if constexpr ((1 << I) < R && (1 << K) < R && I != K) {               \
-      dense1_muxreg_regs<I, K, R>(a, m0, m1);                             \
-      break;                                                              \
-    } else {                                                              \
-      __builtin_unreachable();                                            \
-    }
-#define QSV_D1K_ROW(I) \
-  QSV_D1K(I, 0) QSV_D1K(I, 1) QSV_D1K(I, 2) QSV_D1K(I, 3) QSV_D1K(I, 4)
-  switch (reg * 8 + k) {
-    QSV_D1K_ROW(0)
-    QSV_D1K_ROW(1)
-    QSV_D1K_ROW(2)
-    QSV_D1K_ROW(3)
-    QSV_D1K_ROW(4)
-    default:
-      __builtin_unreachable();  // reg, k < RB <= 5 and reg != k
-  }
-#undef QSV_D1K_ROW
-#undef QSV_D1K
-}
-
 // Register layout: reg_bits[i] (ascending) is the tile-local bit selecting
 // register i; the remaining bits, ascending, come from the thread index.
 template <int RB>
@@ -393,20 +357,12 @@ struct Layout {
 };
 
 template <int RB>
-__device__ __forceinline__ bool same_layout(const Layout<RB>& a,
-                                            const Layout<RB>& b) {
-  bool same = true;
-#pragma unroll
-  for (int i = 0; i < RB; ++i) same = same && a.rb[i] == b.rb[i];
-  return same;
-}
-
-template <int RB>
 __device__ __forceinline__ uint32_t thread_local_base(const Layout<RB>& lay,
                                                       uint32_t tid) {
+  // inserting a zero bit at p doubles the bits from p up
   uint32_t rt = tid;
 #pragma unroll
-  for (int i = 0; i < RB; ++i) rt = insert_zero32(rt, lay.rb[i]);
+  for (int i = 0; i < RB; ++i) rt += rt & (0xFFFFFFFFu << lay.rb[i]);
   return rt;
 }
 
@@ -419,24 +375,6 @@ __device__ __forceinline__ uint32_t reg_offset(const Layout<RB>& lay, int j) {
   return o;
 }
 
-// LDS byte offsets of a layout's registers, swz(reg_offset(j)) * sizeof(C),
-// as uniform values.  The swizzle is linear over XOR, so the offsets are
-// XOR combinations of one value per register bit.
-template <typename T, int RB>
-__device__ __forceinline__ void lds_reg_offsets(const Layout<RB>& lay,
-                                                uint32_t* so) {
-  using C = typename CxT<T>::type;
-  uint32_t basis[RB];
-#pragma unroll
-  for (int i = 0; i < RB; ++i)
-    basis[i] = __builtin_amdgcn_readfirstlane(
-        lds_swz<T>(1u << lay.rb[i]) * uint32_t(sizeof(C)));
-  so[0] = 0;
-#pragma unroll
-  for (int j = 1; j < (1 << RB); ++j)
-    so[j] = so[j & (j - 1)] ^ basis[__builtin_ctz(j)];
-}
-
 // Work-group barrier for an exchange through LDS.  It waits for this wave's
 // LDS (and scalar) accesses only, not for its outstanding global memory
 // operations: a streaming tile pass keeps the next tile's prefetch and this
@@ -444,12 +382,6 @@ __device__ __forceinline__ void lds_reg_offsets(const Layout<RB>& lay,
 // barrier, so no LDS access moves across it.
 __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-// Byte address of a shared-memory pointer in the LDS address space.
-template <typename C>
-__device__ __forceinline__ uint32_t lds_address(const C* p) {
-  return uint32_t(size_t((const __attribute__((address_space(3))) C*)p));
 }
 
 // Store and load one complex amplitude at LDS byte address `at` (as a
@@ -472,110 +404,57 @@ __device__ __forceinline__ void lds_load(uint32_t at, C& v) {
   v.y = w.y;
 }
 
-// Move the tile from layout `from` to layout `to` through LDS.
-// Threads with active == false (beyond the tile) only join the barriers.
-template <typename T, int RB, typename C>
-__device__ __forceinline__ void relayout(C* a, C* lds, const Layout<RB>& from,
-                                         const Layout<RB>& to, uint32_t tid,
-                                         bool active) {
-  constexpr int R = 1 << RB;
-  // The thread and register parts of a tile index have disjoint bits and
-  // the swizzle is linear over XOR: swz(rt | o_j) = swz(rt) ^ swz(o_j), one
-  // per-thread term and one uniform term per register.  The kernels place
-  // no other shared variable before the tile, so it starts at LDS address
-  // 0 and each access is one XOR of the two terms; otherwise the base is
-  // added (a uniform branch).
-  const uint32_t lb = lds_address(lds);
-  uint32_t so[R];
-  if (active) {
-    lds_reg_offsets<T, RB>(from, so);
-    const uint32_t rf =
-        lds_swz<T>(thread_local_base(from, tid)) * uint32_t(sizeof(C));
-    if (lb == 0) {
-#pragma unroll
-      for (int j = 0; j < R; ++j) lds_store(rf ^ so[j], a[j]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < R; ++j) lds_store(lb + (rf ^ so[j]), a[j]);
-    }
-  }
-  lds_barrier();
-  if (active) {
-    lds_reg_offsets<T, RB>(to, so);
-    const uint32_t rt =
-        lds_swz<T>(thread_local_base(to, tid)) * uint32_t(sizeof(C));
-    if (lb == 0) {
-#pragma unroll
-      for (int j = 0; j < R; ++j) lds_load(rt ^ so[j], a[j]);
-    } else {
-#pragma unroll
-      for (int j = 0; j < R; ++j) lds_load(lb + (rt ^ so[j]), a[j]);
-    }
-  }
-  lds_barrier();
+// LDS map of a tile's re-layouts (the host filled the register offsets of
+// the same one: tile_lds_map, batch_lds_map).
+template <typename T, bool HALVES>
+constexpr LdsMap lds_map() {
+  return sizeof(T) == 4 ? (HALVES ? kLds4 : kLds8) : (HALVES ? kLds8 : kLds16);
 }
 
-// Re-layout in two halves (the real parts, then the imaginary parts), each
+// Move the tile to another layout through LDS: register j of a thread goes
+// to byte rf ^ sf[j], then comes from byte rt ^ st[j] (rf, rt: the thread's
+// part in either layout; sf, st: the registers' parts, uniform).  The
+// kernels place no other shared variable before the tile, so it starts at
+// LDS address 0.  HALVES: the real parts, then the imaginary parts, each
 // through a copy of the tile with one component per amplitude: half the
-// LDS of relayout(), so that more work-groups fit on a CU, for two more
-// barriers and twice the LDS instructions.  4-byte components (complex64)
-// take a swizzle over the 32 banks like lds_swz's; 8-byte components
-// (complex128) take lds_swz's own 8-byte swizzle.
-__device__ __forceinline__ uint32_t lds_swz4(uint32_t r) {
-  return r ^ (((r >> 5) ^ (r >> 10)) & 31u);
-}
-
-template <typename T>
-__device__ __forceinline__ uint32_t half_swz(uint32_t r) {
-  if constexpr (sizeof(T) == 4)
-    return lds_swz4(r);
-  else
-    return lds_swz<float>(r);
-}
-
-template <typename T, int RB, typename C>
-__device__ __forceinline__ void relayout_halves(C* a, C* lds,
-                                                const Layout<RB>& from,
-                                                const Layout<RB>& to,
-                                                uint32_t tid, bool active) {
-  constexpr int R = 1 << RB;
-  constexpr uint32_t E = sizeof(T);
-  uint32_t sf[R], st[R];
-  {
-    uint32_t bf[RB], bt[RB];
-#pragma unroll
-    for (int i = 0; i < RB; ++i) {
-      bf[i] = __builtin_amdgcn_readfirstlane(half_swz<T>(1u << from.rb[i]) * E);
-      bt[i] = __builtin_amdgcn_readfirstlane(half_swz<T>(1u << to.rb[i]) * E);
-    }
-    sf[0] = st[0] = 0;
-#pragma unroll
-    for (int j = 1; j < R; ++j) {
-      sf[j] = sf[j & (j - 1)] ^ bf[__builtin_ctz(j)];
-      st[j] = st[j & (j - 1)] ^ bt[__builtin_ctz(j)];
-    }
-  }
-  const uint32_t lb = lds_address(lds);
-  const uint32_t rf = lb + half_swz<T>(thread_local_base(from, tid)) * E;
-  const uint32_t rt = lb + half_swz<T>(thread_local_base(to, tid)) * E;
-  typedef __attribute__((address_space(3))) T lds_t;
-  // threads beyond the tile (active == false) only join the barriers
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
+// LDS, so that more work-groups fit on a CU, for two more barriers and
+// twice the LDS instructions.  Threads with active == false (beyond the
+// tile) only join the barriers.
+template <bool HALVES, int R, typename C>
+__device__ __forceinline__ void relayout(C* a, const uint32_t* sf,
+                                         const uint32_t* st, uint32_t rf,
+                                         uint32_t rt, bool active) {
+  if constexpr (!HALVES) {
     if (active) {
 #pragma unroll
-      for (int j = 0; j < R; ++j)
-        *(lds_t*)(size_t(rf ^ sf[j])) = h ? a[j].y : a[j].x;
+      for (int j = 0; j < R; ++j) lds_store(rf ^ sf[j], a[j]);
     }
     lds_barrier();
     if (active) {
 #pragma unroll
-      for (int j = 0; j < R; ++j) {
-        const T v = *(const lds_t*)(size_t(rt ^ st[j]));
-        if (h) a[j].y = v; else a[j].x = v;
+      for (int j = 0; j < R; ++j) lds_load(rt ^ st[j], a[j]);
+    }
+    lds_barrier();
+  } else {
+    using E = decltype(a[0].x);
+    typedef __attribute__((address_space(3))) E lds_t;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (active) {
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+          *(lds_t*)(size_t(rf ^ sf[j])) = h ? a[j].y : a[j].x;
       }
+      lds_barrier();
+      if (active) {
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          const E v = *(const lds_t*)(size_t(rt ^ st[j]));
+          if (h) a[j].y = v; else a[j].x = v;
+        }
+      }
+      lds_barrier();
     }
-    lds_barrier();
   }
 }
 
@@ -786,18 +665,32 @@ __device__ __forceinline__ void pin_op_fields(OpFields<T>& f) {
 constexpr uint32_t kWarmTiles = 1024;
 template <typename T>
 __device__ __forceinline__ void warm_program(const TilePass* pass,
+                                             const TileSeg* segs,
                                              const TileOp* ops, uint32_t tid) {
   static_assert(sizeof(TileOp) == 256, "four lines per slot");
+  static_assert(sizeof(TileSeg) == 160, "five half lines per segment");
   // lines of an op that load_op reads: its header and mf, mf2, or its
   // header and m, m2
   constexpr int LN = sizeof(T) == 4 ? 2 : 4;
   const cptr<TilePass> cp = as_const(pass);
   const cptr<uint32_t> p =
       as_const(reinterpret_cast<const uint32_t*>(ops + cp->op_begin));
+  // the last wave reads the segments while the others read ops
+  const cptr<uint32_t> ps =
+      as_const(reinterpret_cast<const uint32_t*>(segs + cp->seg_begin));
+  const int n_seg = (cp->nseg * int(sizeof(TileSeg)) + 63) / 64;
   const int n_op_lines = cp->n_ops * LN;
   const int n_lines = n_op_lines + cp->n_blob * 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int waves = (int(blockDim.x) + 63) >> 6;
+  for (int i = (waves - 1 - wave) * 8; i < n_seg; i += waves * 8) {
+    uint32_t v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      v[j] = ps[(i + j < n_seg ? i + j : n_seg - 1) * 16];
+    asm volatile("" ::"s"(v[0]), "s"(v[1]), "s"(v[2]), "s"(v[3]), "s"(v[4]),
+                 "s"(v[5]), "s"(v[6]), "s"(v[7]));
+  }
   for (int i = wave * 16; i < n_lines; i += waves * 16) {
     uint32_t v[16];
 #pragma unroll
@@ -815,101 +708,181 @@ __device__ __forceinline__ void warm_program(const TilePass* pass,
   }
 }
 
+// The registers' LDS offsets of a layout, scalar loads issued together.
+template <int RB>
+__device__ __forceinline__ void load_lds_offsets(const uint32_t* p,
+                                                 uint32_t* so) {
+  if constexpr (RB <= 4) {
+    const cptr<u32x4> v = as_const(reinterpret_cast<const u32x4*>(p));
+#pragma unroll
+    for (int i = 0; i < (1 << RB) / 4; ++i) {
+      const u32x4 u = v[i];
+      so[4 * i] = u.x;
+      so[4 * i + 1] = u.y;
+      so[4 * i + 2] = u.z;
+      so[4 * i + 3] = u.w;
+    }
+  } else {
+    // 32 offsets per layout do not fit the scalar registers beside an op's
+    // fields: those of the register bits, and their combinations
+    const cptr<uint32_t> v = as_const(p);
+    so[0] = 0;
+#pragma unroll
+    for (int i = 0; i < RB; ++i) so[1 << i] = v[1 << i];
+#pragma unroll
+    for (int j = 1; j < (1 << RB); ++j)
+      so[j] = so[j & (j - 1)] ^ so[j & -j];
+  }
+}
+
+// One hot op: kCodeUniform, kCodeRegMux or kCodeThreadMux on target register
+// bit I (mux register bit K).  f holds its fields and leaves with the next
+// op's.  These are read while the op computes, once its own matrix has left
+// f; a register mux, whose two matrices stay live, reads them afterwards.
+// Tried instead, both no faster where few work-groups run and slower where
+// many do: a second set of fields for every class, copied over afterwards
+// (24 moves an op), or with the loop unrolled over the two sets (twice the
+// code: 24 qubits 2.10 against 1.95 ms).
+template <int CLS, int I, int K, int RB, typename T, typename C>
+__device__ __forceinline__ void hot_op(C* a, OpFields<T>& f, uint64_t base,
+                                       uint32_t rt, const TileOp* next) {
+  using Bits = typename OpFields<T>::B;
+  constexpr int R = 1 << RB;
+  T m0[8], m1[8];
+  if constexpr (CLS == kCodeUniform) {
+    // one matrix for the whole tile, chosen by one bit of its base index (an
+    // outer mux qubit, or bit 63, which no index has); the choice is made on
+    // the bit patterns, so it stays scalar and the FMAs read the matrix from
+    // scalar registers
+    const bool second = ((base >> (f.arg & 63)) & 1) != 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      Bits b = second ? f.m1[e] : f.m0[e];
+      asm volatile("" : "+s"(b));
+      m0[e] = __builtin_bit_cast(T, b);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      m0[e] = __builtin_bit_cast(T, f.m0[e]);
+      m1[e] = __builtin_bit_cast(T, f.m1[e]);
+    }
+    if constexpr (CLS == kCodeThreadMux) {
+      // mux bit in the thread index: one matrix per thread
+      const bool sel = ((rt >> f.arg) & 1u) != 0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) m0[e] = sel ? m1[e] : m0[e];
+    }
+  }
+  // the barriers keep the compiler from moving the loads below the update,
+  // and their first use above its end
+  if constexpr (CLS != kCodeRegMux) f = load_op<T>(next);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (CLS == kCodeUniform)
+    dense1_regs<I, R, false, true>(a, m0, rt, nullptr, 0u);
+  else if constexpr (CLS == kCodeRegMux)
+    dense1_muxreg_regs<I, K, R>(a, m0, m1);
+  else
+    dense1_regs<I, R, false, false>(a, m0, rt, nullptr, 0u);
+  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (CLS == kCodeRegMux) f = load_op<T>(next);
+  pin_op_fields(f);
+}
+
+// The hot op whose code f holds (op.code < kCodeCtrl << 6).
+template <int RB, typename T, typename C>
+__device__ __forceinline__ void hot_dispatch(C* a, OpFields<T>& f,
+                                             uint64_t base, uint32_t rt,
+                                             const TileOp* next) {
+#define QSV_HOT(CLS, I, K)                                                \
+  case (CLS << 6) | (K << 3) | I:                                         \
+    if constexpr (I < RB && K < RB && (CLS != kCodeRegMux || I != K)) {   \
+      hot_op<CLS, I, K, RB, T>(a, f, base, rt, next);                     \
+      break;                                                              \
+    } else {                                                              \
+      __builtin_unreachable(); /* the planner emits reg bits below RB */  \
+    }
+#define QSV_HOT_K(I)                                                      \
+  QSV_HOT(kCodeRegMux, I, 0) QSV_HOT(kCodeRegMux, I, 1)                   \
+  QSV_HOT(kCodeRegMux, I, 2) QSV_HOT(kCodeRegMux, I, 3)                   \
+  QSV_HOT(kCodeRegMux, I, 4)
+#define QSV_HOT_I(CLS)                                                    \
+  QSV_HOT(CLS, 0, 0) QSV_HOT(CLS, 1, 0) QSV_HOT(CLS, 2, 0)                \
+  QSV_HOT(CLS, 3, 0) QSV_HOT(CLS, 4, 0)
+  switch (f.code) {
+    QSV_HOT_I(kCodeUniform)
+    QSV_HOT_I(kCodeThreadMux)
+    QSV_HOT_K(0)
+    QSV_HOT_K(1)
+    QSV_HOT_K(2)
+    QSV_HOT_K(3)
+    QSV_HOT_K(4)
+    default:
+      __builtin_unreachable();
+  }
+#undef QSV_HOT
+#undef QSV_HOT_K
+#undef QSV_HOT_I
+}
+
 // Apply every segment of one tile pass to the register tile `a`, which is
 // in the I/O layout on entry and is left in the I/O layout on exit.  `base`
 // is the tile's global index with all tile bits zero (outer controls and
 // diagonal bits outside the tile are read from it).
-template <typename T, int RB, bool HALVES = false>
+//
+// Where few work-groups run (small states), each wave's own chain of
+// latencies bounds the pass: the scalar loads of an op, the branches to its
+// code, the address arithmetic of a re-layout.  So an op's fields are read
+// while the op before it computes, the hot ops are reached through one
+// switch on the planner's code, and a re-layout takes its LDS offsets from
+// the segment record. 
+template <typename T, int RB, bool HALVES>
 __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
-                                           typename CxT<T>::type* lds,
                                            const TilePass* pass,
                                            const TileSeg* segs,
                                            const TileOp* ops, uint64_t base,
                                            uint32_t tid, bool active) {
   using C = typename CxT<T>::type;
-  using Bits = typename OpFields<T>::B;
   constexpr int R = 1 << RB;
+  constexpr LdsMap kMap = lds_map<T, HALVES>();
   const cptr<TilePass> cp = as_const(pass);
-  const int W = cp->L - RB;
-  Layout<RB> io;
-#pragma unroll
-  for (int i = 0; i < RB; ++i) io.rb[i] = W + i;
-  Layout<RB> cur = io;
   const int nseg = cp->nseg;
-  const cptr<TileSeg> sp = as_const(segs) + cp->seg_begin;
-  for (int s = 0; s < nseg; ++s) {
+  const TileSeg* sg = segs + cp->seg_begin;
+  const uint32_t* lds_from = pass->lds;
+  // thread tid's part of a tile index in the current layout (the I/O layout
+  // takes the low bits)
+  uint32_t rt = tid;
+  int o = cp->op_begin;
+  OpFields<T> f = load_op<T>(ops + o);
+  pin_op_fields(f);
+  for (int s = 0; s < nseg; ++s, ++sg) {
+    const cptr<u32x4> head = as_const(reinterpret_cast<const u32x4*>(sg));
+    const u32x4 h0 = head[0], h1 = head[1];
+    uint32_t sf[R], st[R];
+    load_lds_offsets<RB>(lds_from, sf);
+    load_lds_offsets<RB>(sg->lds, st);
+    const int32_t bits[5] = {int32_t(h0.x), int32_t(h0.y), int32_t(h0.z),
+                             int32_t(h0.w), int32_t(h1.x)};
+    const int o_end = int32_t(h1.w);
     Layout<RB> lay;
 #pragma unroll
-    for (int i = 0; i < RB; ++i) lay.rb[i] = sp[s].reg_bits[i];
-    if (!same_layout(cur, lay)) {
-      if constexpr (HALVES)
-        relayout_halves<T, RB>(a, lds, cur, lay, tid, active);
-      else
-        relayout<T, RB>(a, lds, cur, lay, tid, active);
-    }
-    cur = lay;
-    const uint32_t rt = thread_local_base(lay, tid);
-    const int o_end = sp[s].op_end;
-    int o = sp[s].op_begin;
+    for (int i = 0; i < RB; ++i) lay.rb[i] = bits[i];
+    const uint32_t to = thread_local_base(lay, tid);
+    if (h1.y)
+      relayout<HALVES, R>(a, sf, st, lds_place(kMap, rt), lds_place(kMap, to),
+                          active);
+    rt = to;
+    lds_from = sg->lds;
     while (o < o_end) {
-      // Runs of control-free dense ops (the bulk of every circuit) go
-      // through a tight loop that branches only on the class and the
-      // target register, and whose every arm updates the amplitudes in
-      // place; controlled, phase and diagonal ops take the general path.
       const TileOp* op = ops + o;
-      // the header and both matrices, in one batch of scalar loads; the
-      // planner resolved every choice it could into the dispatch code
-      OpFields<T> f = load_op<T>(op);
-      pin_op_fields(f);
-      int cls = f.code >> 3;
-      if (cls <= kCodeThreadMux) {
-        for (;;) {
-          if ((base & f.gctrl) == f.gctrl) {  // else an outer control is 0
-            const int reg = f.code & 7;
-            if (cls == kCodeUniform) {
-              // one matrix for the whole tile, chosen by one bit of its
-              // base index (an outer mux qubit, or bit 63, which no index
-              // has); the choice is made on the bit patterns, so it stays
-              // scalar and the FMAs read the matrix from scalar registers
-              const bool second = ((base >> (f.arg & 63)) & 1) != 0;
-              T m[8];
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                Bits b = second ? f.m1[e] : f.m0[e];
-                asm volatile("" : "+s"(b));
-                m[e] = __builtin_bit_cast(T, b);
-              }
-              dense1_dispatch<R, false, true>(reg, a, m, rt, nullptr, 0u);
-            } else {
-              T m0[8], m1[8];
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                m0[e] = __builtin_bit_cast(T, f.m0[e]);
-                m1[e] = __builtin_bit_cast(T, f.m1[e]);
-              }
-              if (cls == kCodeRegMux) {
-                // mux bit in a register: the pairs' matrices are fixed
-                dense1_muxreg_dispatch<R>(reg, f.arg, a, m0, m1);
-              } else {
-                // mux bit in the thread index: one matrix per thread
-                const bool sel = ((rt >> f.arg) & 1u) != 0;
-                T m[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) m[e] = sel ? m1[e] : m0[e];
-                dense1_dispatch<R, false, false>(reg, a, m, rt, nullptr, 0u);
-              }
-            }
-          }
-          if (++o >= o_end) break;
-          f = load_op<T>(ops + o);
-          pin_op_fields(f);
-          cls = f.code >> 3;
-          if (cls > kCodeThreadMux) break;
-        }
-        continue;  // o is the next op of another class, or the end
+      if (f.code < (kCodeCtrl << 6)) {
+        hot_dispatch<RB, T>(a, f, base, rt, op + 1);
+        ++o;
+        continue;
       }
-      ++o;
-      if ((base & f.gctrl) != f.gctrl) continue;  // an outer control is 0
+      // controlled, phase and diagonal ops
+      const int cls = f.code >> 6;
+      if ((base & f.gctrl) == f.gctrl) {  // else an outer control is 0
       const int reg = f.code & 7;
       T m0[8], m1[8];
 #pragma unroll
@@ -977,13 +950,18 @@ __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
           a[j] = csel(on, y, a[j]);
         }
       }
+      }
+      ++o;
+      f = load_op<T>(ops + o);
+      pin_op_fields(f);
     }
   }
-  if (!same_layout(cur, io)) {
-    if constexpr (HALVES)
-      relayout_halves<T, RB>(a, lds, cur, io, tid, active);
-    else
-      relayout<T, RB>(a, lds, cur, io, tid, active);
+  if (cp->moved) {
+    uint32_t sf[R], st[R];
+    load_lds_offsets<RB>(lds_from, sf);
+    load_lds_offsets<RB>(pass->lds, st);
+    relayout<HALVES, R>(a, sf, st, lds_place(kMap, rt), lds_place(kMap, tid),
+                        active);
   }
 }
 
