@@ -1672,14 +1672,13 @@ qsv_status qsv_expectation_pauli(qsv_state s, int32_t n_terms,
     if ((x_masks[t] | z_masks[t]) & ~full)
       return fail(QSV_ERR_INVALID_ARG, "Pauli mask names a qubit >= n");
   if ((st = select_device(s)) != QSV_OK) return st;
-  const size_t part = (pauli_scratch_bytes(s->n) + 255) & ~size_t(255);
+  const size_t part = (pauli_scratch_bytes(n_terms) + 255) & ~size_t(255);
   const size_t outb = 16 * size_t(n_terms);
   if ((st = ensure_scratch(s, part + outb)) != QSV_OK) return st;
   double* od = reinterpret_cast<double*>(s->scratch + part);
-  for (int t = 0; t < n_terms; ++t)
-    QSV_HIP(s, launch_pauli(s->prec, s->amp, s->n, x_masks[t], z_masks[t],
-                            reinterpret_cast<double*>(s->scratch), od + 2 * t,
-                            s->stream));
+  QSV_HIP(s, launch_pauli(s->prec, s->amp, s->n, n_terms, x_masks, z_masks,
+                          reinterpret_cast<double*>(s->scratch), od,
+                          s->stream));
   std::vector<double> sri(2 * size_t(n_terms));
   QSV_HIP(s, hipMemcpyAsync(sri.data(), od, outb, hipMemcpyDeviceToHost,
                             s->stream));

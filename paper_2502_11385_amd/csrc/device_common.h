@@ -180,10 +180,16 @@ struct PermArgs {
 };
 hipError_t launch_permute(int prec, const void* src, void* dst, int n,
                           const PermArgs& p, hipStream_t stream);
-size_t pauli_scratch_bytes(int n);
-hipError_t launch_pauli(int prec, const void* amp, int n, uint64_t xm,
-                        uint64_t zm, double* scratch, double* out_dev,
-                        hipStream_t stream);
+// Pauli terms of one launch (kernel argument); scratch for n_terms of them.
+constexpr int kPauliBatch = 64;
+struct PauliTerms {
+  uint64_t x[kPauliBatch];
+  uint64_t z[kPauliBatch];
+};
+size_t pauli_scratch_bytes(int n_terms);
+hipError_t launch_pauli(int prec, const void* amp, int n, int n_terms,
+                        const uint64_t* x_masks, const uint64_t* z_masks,
+                        double* scratch, double* out_dev, hipStream_t stream);
 hipError_t launch_sample(int prec, const void* amp, int n, uint64_t shots,
                          uint64_t seed, void* scratch, uint64_t* out_dev,
                          hipStream_t stream);

@@ -8,6 +8,8 @@
 // 12-bit digits (one histogram pass over the state per digit, integer
 // counts) fixes the threshold key; the elements above it are gathered, and
 // the remaining places go to the elements equal to it in index order.
+#include <algorithm>
+
 #include "reduce_core.h"
 
 namespace qsv {
@@ -193,85 +195,143 @@ hipError_t launch_topk_ties(int prec, const void* amp, uint64_t count,
 // For P = i^{|x & z|} X^x Z^z (x: qubits with X or Y, z: qubits with Z or
 // Y), P|i> = i^{|x & z|} (-1)^{|i & z|} |i ^ x>, so
 // <psi|P|psi> = Re(i^{|x & z|} S), S = sum_i conj(a_{i^x}) a_i (-1)^{|i & z|}.
-// Each block sums 4096 terms of S (real and imaginary parts, FP64 with
-// Neumaier compensation, fixed order); one block then sums the blocks.
+// With x != 0 the terms of i and i ^ x are t and (-1)^{|x & z|} conj(t): S is
+// twice the real part (|x & z| even) or i times twice the imaginary part
+// (odd) of the sum over the i with the highest bit of x clear.  So a term
+// reads every amplitude once and sums one real number per pair; with x = 0
+// it sums one per amplitude.  Each block sums consecutive pairs in FP64 with
+// Neumaier compensation, in a fixed order; one block per term then sums the
+// blocks.
+//
+// Bound by HBM, one read of the state per term.  All terms of a call go in
+// one launch, neighbouring blocks taking the same part of the state for
+// different terms, so that terms share what the caches still hold.  Four
+// terms on 27 qubits: 1.32 -> 0.62 ms complex64, 2.02 -> 1.24 ms complex128
+// (one term 0.33 -> 0.21 and 0.46 -> 0.37 ms), against summing both parts of
+// every amplitude's term, a launch and a final sum of 32768 blocks per term.
 
-constexpr int kPauliChunkLog = 12;
+// At most 2^11 blocks per term: eight per CU with a single term.
+constexpr int kPauliBlocksLog = 11;
+constexpr int kPauliMinChunkLog = 8;
+
+static int pauli_chunk_log(int pairs_log) {
+  return pairs_log - kPauliBlocksLog > kPauliMinChunkLog
+             ? pairs_log - kPauliBlocksLog
+             : kPauliMinChunkLog;
+}
+
+template <typename C>
+__device__ __forceinline__ double pauli_value(C y, C x, bool imag) {
+  // conj(x) y: real part xr yr + xi yi, imaginary part xr yi - xi yr
+  const double xr = double(x.x), xi = double(x.y);
+  const double u = double(imag ? y.y : y.x);
+  const double v = double(imag ? -y.x : y.y);
+  return __builtin_fma(xr, u, xi * v);
+}
+
+template <typename C, bool DIAG>
+__device__ __forceinline__ void pauli_block(const C* __restrict__ a,
+                                            uint64_t count, int chunk_log,
+                                            uint64_t chunk, uint64_t xm,
+                                            uint64_t zm, double* s,
+                                            double* c) {
+  const int hb = DIAG ? 0 : 63 - __clzll((long long)xm);
+  const bool imag = !DIAG && (__popcll(xm & zm) & 1);
+  const uint64_t start = chunk << chunk_log;
+  const uint64_t full = start + (uint64_t(1) << chunk_log);
+  const uint64_t end = full < count ? full : count;
+#pragma unroll 4
+  for (uint64_t k = start + threadIdx.x; k < end; k += 256) {
+    const uint64_t i = DIAG ? k : insert_zero64(k, hb);
+    double v = DIAG ? prob_of(a[i]) : pauli_value(a[i], a[i ^ xm], imag);
+    if (__popcll(i & zm) & 1) v = -v;
+    nadd(*s, *c, v);
+  }
+}
 
 template <typename C>
 __global__ void __launch_bounds__(256)
-    pauli_partial_kernel(const C* __restrict__ a, uint64_t count, uint64_t xm,
-                         uint64_t zm, double* __restrict__ partial) {
+    pauli_partial_kernel(const C* __restrict__ a, int n, PauliTerms terms,
+                         uint32_t n_terms, double* __restrict__ partial) {
   __shared__ double sh[512];
-  const uint64_t start = uint64_t(blockIdx.x) << kPauliChunkLog;
-  double sr = 0, cr = 0, si = 0, ci = 0;
-  for (int it = 0; it < (1 << kPauliChunkLog) / 256; ++it) {
-    const uint64_t i = start + uint64_t(it) * 256 + threadIdx.x;
-    if (i < count) {
-      const C ai = a[i], aj = a[i ^ xm];
-      const double xr = double(aj.x), xi = double(aj.y);
-      const double yr = double(ai.x), yi = double(ai.y);
-      double re = xr * yr + xi * yi;
-      double im = xr * yi - xi * yr;
-      if (__popcll(i & zm) & 1) {
-        re = -re;
-        im = -im;
-      }
-      nadd(sr, cr, re);
-      nadd(si, ci, im);
-    }
-  }
-  block_reduce_pair(sr, cr, sh);
-  __syncthreads();
-  block_reduce_pair(si, ci, sh);
+  const uint32_t t = blockIdx.x % n_terms;
+  const uint64_t chunk = blockIdx.x / n_terms;
+  const uint64_t xm = terms.x[t], zm = terms.z[t];
+  const int pairs_log = xm ? n - 1 : n;
+  const uint64_t count = uint64_t(1) << pairs_log;
+  int cl = pairs_log - kPauliBlocksLog;
+  if (cl < kPauliMinChunkLog) cl = kPauliMinChunkLog;
+  double s = 0, c = 0;
+  if (chunk << cl >= count) return;  // a term with x needs half the blocks
+  if (xm) pauli_block<C, false>(a, count, cl, chunk, xm, zm, &s, &c);
+  else pauli_block<C, true>(a, count, cl, chunk, xm, zm, &s, &c);
+  block_reduce_pair(s, c, sh);
   if (threadIdx.x == 0) {
-    double* p = partial + 4 * uint64_t(blockIdx.x);
-    p[0] = sr;
-    p[1] = cr;
-    p[2] = si;
-    p[3] = ci;
+    double* p = partial + (uint64_t(t) * (1u << kPauliBlocksLog) + chunk) * 2;
+    p[0] = s;
+    p[1] = c;
   }
 }
 
+// out[2 t], out[2 t + 1]: real and imaginary part of term t's S.
 __global__ void __launch_bounds__(256)
-    pauli_final_kernel(const double* __restrict__ partial, uint64_t blocks,
-                       double* __restrict__ out) {
+    pauli_final_kernel(const double* __restrict__ partial, int n,
+                       PauliTerms terms, double* __restrict__ out) {
   __shared__ double sh[512];
-  double sr = 0, cr = 0, si = 0, ci = 0;
-  for (uint64_t b = threadIdx.x; b < blocks; b += 256) {
-    nadd(sr, cr, partial[4 * b]);
-    cr += partial[4 * b + 1];
-    nadd(si, ci, partial[4 * b + 2]);
-    ci += partial[4 * b + 3];
+  const uint32_t t = blockIdx.x;
+  const uint64_t xm = terms.x[t], zm = terms.z[t];
+  const int pairs_log = xm ? n - 1 : n;
+  int cl = pairs_log - kPauliBlocksLog;
+  if (cl < kPauliMinChunkLog) cl = kPauliMinChunkLog;
+  const uint32_t blocks =
+      pairs_log > cl ? 1u << (pairs_log - cl) : 1u;
+  const double* p = partial + uint64_t(t) * (2u << kPauliBlocksLog);
+  double s = 0, c = 0;
+#pragma unroll 8
+  for (uint32_t b = threadIdx.x; b < blocks; b += 256) {
+    nadd(s, c, p[2 * b]);
+    c += p[2 * b + 1];
   }
-  block_reduce_pair(sr, cr, sh);
-  __syncthreads();
-  block_reduce_pair(si, ci, sh);
+  block_reduce_pair(s, c, sh);
   if (threadIdx.x == 0) {
-    out[0] = sr + cr;
-    out[1] = si + ci;
+    const double v = (s + c) * (xm ? 2.0 : 1.0);
+    const bool imag = __popcll(xm & zm) & 1;
+    out[2 * t] = imag ? 0.0 : v;
+    out[2 * t + 1] = imag ? v : 0.0;
   }
 }
 
-size_t pauli_scratch_bytes(int n) {
-  const uint64_t blocks =
-      ((uint64_t(1) << n) + (1u << kPauliChunkLog) - 1) >> kPauliChunkLog;
-  return size_t(blocks) * 4 * sizeof(double);
+size_t pauli_scratch_bytes(int n_terms) {
+  return size_t(std::min(n_terms, kPauliBatch)) * (2u << kPauliBlocksLog) *
+         sizeof(double);
 }
 
-hipError_t launch_pauli(int prec, const void* amp, int n, uint64_t xm,
-                        uint64_t zm, double* scratch, double* out_dev,
+hipError_t launch_pauli(int prec, const void* amp, int n, int n_terms,
+                        const uint64_t* x_masks, const uint64_t* z_masks,
+                        double* scratch, double* out_dev,
                         hipStream_t stream) {
-  const uint64_t count = uint64_t(1) << n;
-  const uint64_t blocks =
-      (count + (1u << kPauliChunkLog) - 1) >> kPauliChunkLog;
-  if (prec == 1)
-    pauli_partial_kernel<float2><<<unsigned(blocks), 256, 0, stream>>>(
-        as<float2>(amp), count, xm, zm, scratch);
-  else
-    pauli_partial_kernel<double2><<<unsigned(blocks), 256, 0, stream>>>(
-        as<double2>(amp), count, xm, zm, scratch);
-  pauli_final_kernel<<<1, 256, 0, stream>>>(scratch, blocks, out_dev);
+  for (int t0 = 0; t0 < n_terms; t0 += kPauliBatch) {
+    const int nt = std::min(kPauliBatch, n_terms - t0);
+    PauliTerms terms = {};
+    bool diag = false;
+    for (int t = 0; t < nt; ++t) {
+      terms.x[t] = x_masks[t0 + t];
+      terms.z[t] = z_masks[t0 + t];
+      diag = diag || !terms.x[t];
+    }
+    // blocks of the term with the most pairs
+    const int pl = diag || n == 0 ? n : n - 1;
+    const int cl = pauli_chunk_log(pl);
+    const unsigned blocks = (pl > cl ? 1u << (pl - cl) : 1u) * unsigned(nt);
+    if (prec == 1)
+      pauli_partial_kernel<float2><<<blocks, 256, 0, stream>>>(
+          as<float2>(amp), n, terms, uint32_t(nt), scratch);
+    else
+      pauli_partial_kernel<double2><<<blocks, 256, 0, stream>>>(
+          as<double2>(amp), n, terms, uint32_t(nt), scratch);
+    pauli_final_kernel<<<nt, 256, 0, stream>>>(scratch, n, terms,
+                                               out_dev + 2 * t0);
+  }
   return hipGetLastError();
 }
 
