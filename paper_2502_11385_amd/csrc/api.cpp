@@ -1540,6 +1540,26 @@ qsv_status qsv_permute_qubits(qsv_state s, const int32_t* perm) {
 
 // ------------------------------------------------------------- top-k
 
+// The first k of the gathered (key, index) pairs, largest key first, equal
+// keys by index.
+static qsv_status write_top_k(uint32_t k, const std::vector<uint64_t>& keys,
+                              const std::vector<uint64_t>& idx,
+                              uint64_t* idx_out, double* p_out) {
+  std::vector<uint32_t> ord(keys.size());
+  for (size_t i = 0; i < ord.size(); ++i) ord[i] = uint32_t(i);
+  std::partial_sort(ord.begin(), ord.begin() + k, ord.end(),
+                    [&](uint32_t x, uint32_t y) {
+                      if (keys[x] != keys[y]) return keys[x] > keys[y];
+                      return idx[x] < idx[y];
+                    });
+  for (uint32_t i = 0; i < k; ++i) {
+    idx_out[i] = idx[ord[i]];
+    const uint64_t kb = keys[ord[i]];
+    std::memcpy(&p_out[i], &kb, 8);
+  }
+  return QSV_OK;
+}
+
 qsv_status qsv_top_k(qsv_state s, uint32_t k, uint64_t* idx_out,
                      double* p_out) {
   qsv_status st = check_state(s);
@@ -1549,11 +1569,16 @@ qsv_status qsv_top_k(qsv_state s, uint32_t k, uint64_t* idx_out,
   if (k < 1 || k > 65536 || uint64_t(k) > count)
     return fail(QSV_ERR_INVALID_ARG, "k must be 1..min(65536, 2^n)");
   if ((st = select_device(s)) != QSV_OK) return st;
-  // scratch: histogram, counter, k keys, k indices, tie counts/offsets
+  // scratch: histogram (of either kind), counters, gathered keys and
+  // indices, tie counts/offsets.  The gather has room for the k keys and for
+  // as many again as usually share the k-th one's bin.
   const unsigned tie_blocks = 1024;
   const uint64_t chunk = (count + tie_blocks - 1) / tie_blocks;
-  const size_t o_cnt = 4096 * 8, o_key = o_cnt + 256, o_idx = o_key + 8 * size_t(k);
-  const size_t o_tc = (o_idx + 8 * size_t(k) + 255) & ~size_t(255);
+  const uint64_t cap = std::min<uint64_t>(count, 2 * uint64_t(k) + 16384);
+  const size_t o_cnt = (std::max<size_t>(4096 * 8, topk_hist_bytes()) + 255) &
+                       ~size_t(255);
+  const size_t o_key = o_cnt + 256, o_idx = o_key + 8 * size_t(cap);
+  const size_t o_tc = (o_idx + 8 * size_t(cap) + 255) & ~size_t(255);
   const size_t o_to = o_tc + 8 * tie_blocks;
   if ((st = ensure_scratch(s, o_to + 8 * tie_blocks)) != QSV_OK) return st;
   char* sc = s->scratch;
@@ -1563,6 +1588,25 @@ qsv_status qsv_top_k(qsv_state s, uint32_t k, uint64_t* idx_out,
   auto* didx = reinterpret_cast<uint64_t*>(sc + o_idx);
   auto* tcount = reinterpret_cast<unsigned long long*>(sc + o_tc);
   auto* toff = reinterpret_cast<unsigned long long*>(sc + o_to);
+  std::vector<uint64_t> keys, idx;
+  unsigned long long found[4];
+  QSV_HIP(s, launch_topk_select(s->prec, s->amp, count, k,
+                                reinterpret_cast<unsigned int*>(sc), counter,
+                                cap, dkey, didx, s->stream));
+  QSV_HIP(s, hipMemcpyAsync(found, counter, sizeof found,
+                            hipMemcpyDeviceToHost, s->stream));
+  QSV_HIP(s, hipStreamSynchronize(s->stream));
+  if (found[1] + found[2] <= cap) {
+    const size_t m = size_t(found[1] + found[2]);
+    keys.resize(m);
+    idx.resize(m);
+    QSV_HIP(s, hipMemcpyAsync(keys.data(), dkey, 8 * m, hipMemcpyDeviceToHost,
+                              s->stream));
+    QSV_HIP(s, hipMemcpyAsync(idx.data(), didx, 8 * m, hipMemcpyDeviceToHost,
+                              s->stream));
+    QSV_HIP(s, hipStreamSynchronize(s->stream));
+    return write_top_k(k, keys, idx, idx_out, p_out);
+  }
   // radix select of the k-th largest key, 12 bits per pass from the top
   uint64_t prefix = 0, mask = 0, need = k, above = 0;
   int fixed = 0;
@@ -1594,7 +1638,6 @@ qsv_status qsv_top_k(qsv_state s, uint32_t k, uint64_t* idx_out,
       break;
     }
   }
-  std::vector<uint64_t> keys, idx;
   if (whole_bin) {
     QSV_HIP(s, hipMemsetAsync(counter, 0, 8, s->stream));
     QSV_HIP(s, launch_topk_collect(s->prec, s->amp, count, mask, prefix, 1,
@@ -1643,18 +1686,7 @@ qsv_status qsv_top_k(qsv_state s, uint32_t k, uint64_t* idx_out,
     QSV_HIP(s, hipStreamSynchronize(s->stream));
     for (uint64_t i = above; i < k; ++i) keys[i] = prefix;
   }
-  std::vector<uint32_t> ord(k);
-  for (uint32_t i = 0; i < k; ++i) ord[i] = i;
-  std::sort(ord.begin(), ord.end(), [&](uint32_t x, uint32_t y) {
-    if (keys[x] != keys[y]) return keys[x] > keys[y];
-    return idx[x] < idx[y];
-  });
-  for (uint32_t i = 0; i < k; ++i) {
-    idx_out[i] = idx[ord[i]];
-    const uint64_t kb = keys[ord[i]];
-    std::memcpy(&p_out[i], &kb, 8);
-  }
-  return QSV_OK;
+  return write_top_k(k, keys, idx, idx_out, p_out);
 }
 
 // ------------------------------------------------- Pauli expectations

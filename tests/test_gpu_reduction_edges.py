@@ -63,3 +63,47 @@ def test_more_pauli_terms_than_one_launch():
     s.free()
     want = [oracle.pauli_expectation(psi, n, t) for t in terms]
     assert np.max(np.abs(got - want)) <= 1e-13
+
+
+@pytest.mark.parametrize("prec", [C64, C128])
+@pytest.mark.parametrize("n,k", [(1, 2), (13, 1), (13, 8192), (14, 100),
+                                 (16, 1), (16, 100), (16, 30000)])
+def test_top_k_gather_and_refine(n, k, prec):
+    """A state with few distinct magnitudes, so that from 16 qubits the k-th
+    key's bin holds more keys than the gather has room for and the digits
+    decide; below, and for k near 2^n, the gather does."""
+    rng = np.random.default_rng(n + k)
+    psi = (rng.integers(1, 4, 1 << n) *
+           np.exp(1j * rng.integers(0, 4, 1 << n) * np.pi / 2)).astype(DT[prec])
+    s = _state(psi, prec)
+    idx, p = s.top_k(k)
+    s.free()
+    widx, wp = oracle.top_k(oracle.probs_of_amplitudes(psi), k)
+    assert idx.tolist() == widx.tolist()
+    assert p.tolist() == wp.tolist()
+
+
+@pytest.mark.parametrize("n", [1, 10, 11, 16, 17, 20])
+def test_sample_block_search_edges(n):
+    """1, 2, 64, 128 and 1024 blocks; all weight on one amplitude of the first
+    or the last block, then spread out: the least index with C(i) > t, where
+    no step of the cumulative sum lies within 1e-9 of t."""
+    shots = 2000
+    for where in (0, (1 << n) - 1):
+        psi = np.zeros(1 << n, np.complex128)
+        psi[where] = 1
+        s = _state(psi, C128)
+        assert np.all(s.sample(shots, 11) == where)
+        s.free()
+    psi = random_state(n, n)
+    s = _state(psi, C128)
+    got = s.sample(shots, 12)
+    s.free()
+    p = oracle.probabilities(psi)
+    c = np.cumsum(p)
+    t = oracle.uniforms(12, shots) * c[-1]
+    want = np.searchsorted(c, t, side="right")
+    off = np.nonzero(got != want)[0]
+    for j in off:
+        lo, hi = sorted((int(got[j]), int(want[j])))
+        assert np.min(np.abs(c[lo:hi] - t[j])) <= 1e-9
