@@ -1,6 +1,7 @@
 // Cut reconstruction: host validation, tables and launch (Section III.A).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <string>
 #include <vector>
@@ -11,6 +12,9 @@
 namespace qsv {
 qsv_status set_error(qsv_status st, const std::string& msg);
 hipError_t launch_cut(const CutArgs& a, double* out, hipStream_t stream);
+// Copy the first `bytes` of a call's tables to dst in stream order.
+hipError_t launch_cut_tables(char* dst, const char* host, size_t bytes,
+                             hipStream_t stream);
 }  // namespace qsv
 
 using namespace qsv;
@@ -25,7 +29,9 @@ struct CutPlan {
   std::vector<uint64_t> n_variants;   // per subcircuit
   std::vector<uint64_t> tt;           // [4^K][n_sub]
   std::vector<std::vector<int>> end_cut;  // per subcircuit, cut of each end
-  std::vector<int> vary, uni;         // wave-kernel split of subcircuits
+  std::vector<int> vary, uni;         // split of the subcircuits
+  std::vector<int> vary_pos, free_pos;  // tile kernel (n_low > 0), CutArgs
+  int32_t n_low = 0;
   std::vector<uint64_t> ttv, ttu;     // its term-vector start tables
   uint64_t n_c = 1, n_u = 1, o_ttv = 0, o_ttu = 0;
   uint64_t total_variants = 0, total_entries = 0, n_terms = 1;
@@ -140,18 +146,37 @@ std::string plan_cut(const qsv_cut_spec* sp, CutPlan* P) {
   };
   for (uint64_t t = 0; t < P->n_terms; ++t)
     for (int s = 0; s < S; ++s) P->tt[t * S + s] = term_start(s, t);
-  // wave kernel split: subcircuits with an output among uncut qubits 0..5
-  // vary across a wave's lanes; cuts touching them index c, the rest u
-  P->vary.clear();
-  P->uni.clear();
-  std::vector<int> cut_vary(K, 0);
-  for (int s = 0; s < S; ++s) {
-    const CutSubDev& d = P->subs[s];
-    bool vary = false;
-    for (int i = 0; i < d.eff; ++i) vary = vary || d.out_uncut[i] < 6;
-    (vary ? P->vary : P->uni).push_back(s);
-    if (vary)
-      for (int k : P->end_cut[s]) cut_vary[k] = 1;
+  // Split: subcircuits with an output among the lowest uncut qubits vary
+  // across a wave's lanes (qubits 0..5) or a work-group's row (kCutLow);
+  // cuts touching them index c, the rest u.
+  std::vector<int> cut_vary;
+  auto split = [&](int low) {
+    P->vary.clear();
+    P->uni.clear();
+    cut_vary.assign(size_t(K), 0);
+    for (int s = 0; s < S; ++s) {
+      const CutSubDev& d = P->subs[s];
+      bool vary = false;
+      for (int i = 0; i < d.eff; ++i) vary = vary || d.out_uncut[i] < low;
+      (vary ? P->vary : P->uni).push_back(s);
+      if (vary)
+        for (int k : P->end_cut[s]) cut_vary[k] = 1;
+    }
+    return uint64_t(1) << (2 * std::count(cut_vary.begin(), cut_vary.end(), 1));
+  };
+  // The tile kernel needs 4^(cuts of its varying subcircuits) <= kCutTileC
+  // and some qubits outside a row.
+  P->n_low = 0;
+  if (n > kCutLow && split(kCutLow) <= uint64_t(kCutTileC)) {
+    P->n_low = kCutLow;
+    uint64_t vm = 0;
+    for (int s : P->vary)
+      for (int i = 0; i < P->subs[s].eff; ++i)
+        vm |= uint64_t(1) << P->subs[s].out_uncut[i];
+    for (int q = kCutLow; q < n; ++q)
+      (vm >> q & 1 ? P->vary_pos : P->free_pos).push_back(q);
+  } else {
+    split(6);
   }
   std::vector<int> cv, cu;
   for (int k = 0; k < K; ++k) (cut_vary[k] ? cv : cu).push_back(k);
@@ -229,9 +254,16 @@ qsv_status qsv_cut_reconstruct(const qsv_cut_spec* spec, const void* probs_dev,
   std::memcpy(host.data() + P.o_ttv, P.ttv.data(), 8 * P.ttv.size());
   std::memcpy(host.data() + P.o_ttu, P.ttu.data(), 8 * P.ttu.size());
   char* ws = static_cast<char*>(workspace);
-  hipError_t he = hipMemcpyAsync(ws, host.data(), host.size(),
-                                 hipMemcpyHostToDevice, stream);
-  if (he == hipSuccess) he = hipStreamSynchronize(stream);
+  hipError_t he;
+  if (host.size() <= 4 * sizeof(CutTables)) {
+    // the usual few kilobytes travel as kernel arguments: no wait for the
+    // stream before the host copy may go
+    he = launch_cut_tables(ws, host.data(), host.size(), stream);
+  } else {
+    he = hipMemcpyAsync(ws, host.data(), host.size(), hipMemcpyHostToDevice,
+                        stream);
+    if (he == hipSuccess) he = hipStreamSynchronize(stream);
+  }
   if (he != hipSuccess)
     return set_error(QSV_ERR_DEVICE, hipGetErrorString(he));
   CutArgs a = {};
@@ -254,6 +286,11 @@ qsv_status qsv_cut_reconstruct(const qsv_cut_spec* spec, const void* probs_dev,
   for (int k = 0; k < a.n_uni; ++k) a.uni_sub[k] = P.uni[k];
   a.n_c = P.n_c;
   a.n_u = P.n_u;
+  a.n_low = P.n_low;
+  a.n_vary_hi = int32_t(P.vary_pos.size());
+  a.n_free = int32_t(P.free_pos.size());
+  std::copy(P.vary_pos.begin(), P.vary_pos.end(), a.vary_pos);
+  std::copy(P.free_pos.begin(), P.free_pos.end(), a.free_pos);
   he = launch_cut(a, out_dev, stream);
   if (he != hipSuccess) return set_error(QSV_ERR_DEVICE, hipGetErrorString(he));
   return set_error(QSV_OK, "");

@@ -10,6 +10,9 @@ constexpr int kCutMaxWidth = 24;
 constexpr int kCutMaxEnds = 6;
 constexpr int kCutMaxQubits = 30;
 constexpr int kCutMaxVary = 4;  // wave kernel: subcircuits varying in a wave
+constexpr int kCutLow = 8;      // tile kernel: outcomes per work-group row, log2
+constexpr int kCutRowsLog = 6;  // rows per work-group at most, log2
+constexpr int kCutTileC = 16;   // and the most term choices it sums there
 
 // One subcircuit, as the kernels see it.
 //  out_pos[i]  : local qubit of the subcircuit's i-th output (ascending);
@@ -71,6 +74,20 @@ struct CutArgs {
   uint64_t n_u;
   double* T;
   const void* probs;
+  // Tile kernel (n_low > 0: usable; the split above then is by uncut qubits
+  // 0..n_low-1).  vary_pos: the other qubits that the varying subcircuits
+  // output, free_pos: the remaining ones (uniform subcircuits only).
+  int32_t n_low;
+  int32_t n_vary_hi;
+  int32_t n_free;
+  int32_t pad;
+  int32_t vary_pos[kCutMaxQubits];
+  int32_t free_pos[kCutMaxQubits];
+};
+
+// Tables of a call, passed by value to a kernel that stores them.
+struct CutTables {
+  uint64_t w[440];
 };
 
 }  // namespace qsv
