@@ -1480,12 +1480,21 @@ qsv_status qsv_permute_qubits(qsv_state s, const int32_t* perm) {
   for (int q = 0; q < n; ++q) identity = identity && perm[q] == q;
   if (identity) return QSV_OK;
   if ((st = select_device(s)) != QSV_OK) return st;
-  // tile source bits: the m lowest, and those that land on the m lowest
-  const int m = std::min(n, s->b == 8 ? 5 : 4);
-  uint64_t smask = 0;
-  for (int q = 0; q < m; ++q) smask |= (uint64_t(1) << q) | (uint64_t(1) << inv[q]);
+  // Tile source bits: the m lowest and those that land on the m lowest, m as
+  // large as a tile of 32 KiB allows, then the lowest others.
+  const int cap = std::min(n, s->b == 8 ? 12 : 11);
+  auto span = [&](int m) {
+    uint64_t v = 0;
+    for (int q = 0; q < m; ++q)
+      v |= (uint64_t(1) << q) | (uint64_t(1) << inv[q]);
+    return v;
+  };
+  int m = 0;
+  while (m < n && __builtin_popcountll(span(m + 1)) <= cap) ++m;
+  uint64_t smask = span(m);
+  for (int q = 0; __builtin_popcountll(smask) < cap; ++q)
+    smask |= uint64_t(1) << q;
   PermArgs pa = {};
-  pa.m = m;
   for (int q = 0; q < n; ++q)
     if (smask >> q & 1) pa.s_bits[pa.s++] = q;
     else {
@@ -1495,28 +1504,41 @@ qsv_status qsv_permute_qubits(qsv_state s, const int32_t* perm) {
   std::vector<int> d(pa.s_bits, pa.s_bits + pa.s);
   for (int& x : d) x = perm[x];
   std::sort(d.begin(), d.end());
+  int src_of[kPermMaxTileBits];  // source tile bit of destination tile bit j
   for (int j = 0; j < pa.s; ++j) {
     pa.d_bits[j] = d[j];
     const int q = inv[d[j]];
     for (int k = 0; k < pa.s; ++k)
-      if (pa.s_bits[k] == q) pa.src_of[j] = k;
+      if (pa.s_bits[k] == q) src_of[j] = k;
   }
+  // LDS slots: a load or store of 128 bytes goes to the banks at once, lb
+  // bits' worth of amplitudes, whose slots must differ in the lowest lb bits.
+  // Stores run over r's lowest bits; loads over the source bits of the lowest
+  // destination bits, and those of them above the lowest lb are XORed into
+  // slot bits that no other of them takes.
+  const int lb = std::min(pa.s, s->b == 8 ? 4 : 3);
+  for (int j = 0; j < pa.s; ++j) pa.w_slot[j] = 1u << j;
+  uint32_t taken = 0;
+  for (int j = 0; j < lb; ++j)
+    if (src_of[j] < lb) taken |= 1u << src_of[j];
+  for (int j = 0, f = 0; j < lb; ++j)
+    if (src_of[j] >= lb) {
+      while (taken >> f & 1) ++f;
+      pa.w_slot[src_of[j]] |= 1u << f++;
+    }
+  for (int j = 0; j < pa.s; ++j) pa.g_slot[j] = pa.w_slot[src_of[j]];
   // uniform per-step parts of the tile index maps (see the kernel)
   const uint32_t step = std::min(256u, 1u << pa.s);
   pa.ne = int32_t((1u << pa.s) / step);
   for (int e = 0; e < pa.ne; ++e) {
     const uint32_t r = uint32_t(e) * step;
-    uint64_t sv = 0, dv = 0;
-    uint32_t gv = 0;
     for (int j = 0; j < pa.s; ++j) {
-      const uint32_t bit = (r >> j) & 1u;
-      sv |= uint64_t(bit) << pa.s_bits[j];
-      dv |= uint64_t(bit) << pa.d_bits[j];
-      gv |= bit << pa.src_of[j];
+      if (!(r >> j & 1u)) continue;
+      pa.se[e] |= uint64_t(1) << pa.s_bits[j];
+      pa.de[e] |= uint64_t(1) << pa.d_bits[j];
+      pa.we[e] ^= pa.w_slot[j];
+      pa.ge[e] ^= pa.g_slot[j];
     }
-    pa.se[e] = sv;
-    pa.de[e] = dv;
-    pa.ge[e] = gv;
   }
   const size_t bytes = size_t(s->b) << n;
   if (!s->spare) {
@@ -1532,8 +1554,7 @@ qsv_status qsv_permute_qubits(qsv_state s, const int32_t* perm) {
   if (s->owned) {
     std::swap(s->amp, s->spare);
   } else {
-    QSV_HIP(s, hipMemcpyAsync(s->amp, s->spare, bytes, hipMemcpyDeviceToDevice,
-                              s->stream));
+    QSV_HIP(s, launch_copy(s->spare, s->amp, bytes, s->stream));
   }
   return QSV_OK;
 }

@@ -168,27 +168,33 @@ hipError_t launch_topk_ties(int prec, const void* amp, uint64_t count,
                             const unsigned long long* offsets, uint64_t need,
                             uint64_t* out_idx, hipStream_t stream);
 // qubit relabelling (k_permute.hip): tile source bits s_bits (ascending,
-// s of them), their destinations d_bits (ascending), destination tile bit j
-// taken from source tile bit src_of[j], and the outer source bits with their
-// destinations
+// s of them), their destinations d_bits (ascending), and the outer source
+// bits with their destinations
+constexpr int kPermMaxTileBits = 12;
 struct PermArgs {
   int32_t s;
   int32_t n_outer;
-  int32_t m;  // lowest qubits kept contiguous (the LDS slot fold width)
   int32_t ne; // steps of blockDim.x amplitudes per tile
+  // LDS slot of source tile bit j, and of the source tile bit that lands on
+  // destination tile bit j
+  uint32_t w_slot[kPermMaxTileBits];
+  uint32_t g_slot[kPermMaxTileBits];
   // per step e (r = e * blockDim.x + tid): the uniform parts of the source
-  // spread, the destination spread and the destination-to-source map
+  // spread, the destination spread and the two LDS slots
   uint64_t se[16];
   uint64_t de[16];
+  uint32_t we[16];
   uint32_t ge[16];
-  int32_t s_bits[10];
-  int32_t d_bits[10];
-  int32_t src_of[10];
+  int32_t s_bits[kPermMaxTileBits];
+  int32_t d_bits[kPermMaxTileBits];
   int32_t outer_src[34];
   int32_t outer_dst[34];
 };
 hipError_t launch_permute(int prec, const void* src, void* dst, int n,
                           const PermArgs& p, hipStream_t stream);
+// Device copy of a multiple of 16 bytes, both ends 16-byte aligned.
+hipError_t launch_copy(const void* src, void* dst, uint64_t bytes,
+                       hipStream_t stream);
 // Pauli terms of one launch (kernel argument); scratch for n_terms of them.
 constexpr int kPauliBatch = 64;
 struct PauliTerms {
