@@ -18,8 +18,6 @@
 #include <functional>
 #include <map>
 #include <tuple>
-#include <unordered_map>
-#include <unordered_set>
 
 namespace qsv {
 
@@ -79,7 +77,7 @@ std::string make_gate(int n, int k, int c, const int32_t* qubits,
     h.tmask |= 1ull << qubits[i];
   }
   for (int i = 0; i < c; ++i) {
-    h.ctl[i] = qubits[k + i];
+    h.ctl[i] = int8_t(qubits[k + i]);
     h.cmask |= 1ull << qubits[k + i];
   }
   const int d = 1 << k;
@@ -108,26 +106,43 @@ uint64_t plain_gate_bytes(const HostGate& g, int n, int b) {
   return 2ull * (uint64_t(1) << free_bits) * uint64_t(b);
 }
 
+// What the scans below read of a gate, in one place (the gates themselves
+// spread over several cache lines each).
+struct GateLite {
+  uint64_t touch, dense;
+  bool tileable, diagonal;
+};
+
+static bool tileable(const HostGate& g) {
+  return g.diagonal ? (g.masked_phase || g.k <= 2) : g.k == 1;
+}
+
+static GateLite lite(const HostGate& g) {
+  return {g.touch(), g.dense(), tileable(g), g.diagonal};
+}
+
 // One greedy scan over `pending` in list order.  A gate is taken when it
 // commutes with every gate skipped before it in this scan, `ok` accepts its
 // index and the bits it requires fit into `set` (at most `capacity` bits).
 // Taken gates keep their relative order; skipped gates stay pending in
-// their order.  `took` hears of each gate taken, as it is taken.
+// their order.  `took` hears of each gate taken, as it is taken.  Once every
+// qubit of `all` is the target of a skipped gate, no later gate commutes
+// with the skipped ones and the scan ends.
 template <class Need, class Ok, class Took>
-static void greedy(const std::vector<HostGate>& G, std::vector<int>* pending,
-                   uint64_t* set, int capacity, Need need, Ok ok,
-                   std::vector<int>* taken, Took took) {
-  std::vector<int> rest;
-  rest.reserve(pending->size());
+static void greedy(const std::vector<GateLite>& G, uint64_t all,
+                   std::vector<int>* pending, uint64_t* set, int capacity,
+                   Need need, Ok ok, std::vector<int>* taken, Took took) {
   uint64_t blk_touch = 0, blk_dense = 0;
-  for (int gi : *pending) {
-    const HostGate& g = G[gi];
+  size_t keep = 0, i = 0;
+  std::vector<int>& p = *pending;
+  for (; i < p.size() && (all & ~blk_dense); ++i) {
+    const int gi = p[i];
+    const GateLite& g = G[size_t(gi)];
     bool take = false;
-    bool conflict = (g.dense() & blk_touch) || (g.touch() & blk_dense);
-    if (!conflict && ok(gi)) {
-      uint64_t want = need(g) & ~*set;
-      if (popc(*set | want) <= capacity) {
-        *set |= want;
+    if (!(g.dense & blk_touch) && !(g.touch & blk_dense) && ok(gi)) {
+      const uint64_t with = *set | need(gi);
+      if (popc(with) <= capacity) {
+        *set = with;
         take = true;
       }
     }
@@ -135,16 +150,12 @@ static void greedy(const std::vector<HostGate>& G, std::vector<int>* pending,
       taken->push_back(gi);
       took(gi);
     } else {
-      rest.push_back(gi);
-      blk_touch |= g.touch();
-      blk_dense |= g.dense();
+      p[keep++] = gi;
+      blk_touch |= g.touch;
+      blk_dense |= g.dense;
     }
   }
-  pending->swap(rest);
-}
-
-static bool tileable(const HostGate& g) {
-  return g.diagonal ? (g.masked_phase || g.k <= 2) : g.k == 1;
+  p.erase(p.begin() + std::ptrdiff_t(keep), p.begin() + std::ptrdiff_t(i));
 }
 
 // Which op absorbs a two-qubit diagonal gate (a CZ, say) decides how many
@@ -175,53 +186,211 @@ static bool tileable(const HostGate& g) {
 // the pass would have with no segment boundaries, so that an owner's next
 // gate does not land in a later segment than the other side's (see
 // plan_tiled).
-// A pass's gates in processing order, with per-qubit rows (compressed) of
-// the positions touching each qubit and of the dense gates on it.
+// A pass's gates in processing order, as the model sees them: per qubit, its
+// dense gates in order, and for each what lies between it and the one before.
+// Everything but the owners is fixed by the order, so it is worked out once
+// and the search below runs over short rows.
 struct PassOrder {
-  const std::vector<HostGate>& G;
-  std::vector<int> order, target, ev, tp;
-  std::array<int, 65> eo, to;
-  PassOrder(const std::vector<HostGate>& g, std::vector<int> ord)
-      : G(g), order(std::move(ord)) {
-    const int N = int(order.size());
-    target.resize(N);
-    eo.fill(0);
-    to.fill(0);
-    for (int i = 0; i < N; ++i) {
-      const HostGate& h = G[order[i]];
-      target[i] = (!h.diagonal && h.k == 1) ? h.t[0] : -1;
-      for (uint64_t m = h.touch(); m; m &= m - 1) ++eo[__builtin_ctzll(m) + 1];
-      if (target[i] >= 0) ++to[target[i] + 1];
+  struct Target {
+    int64_t read;      // the gate's single control with its version (-1: none)
+    int32_t shared;    // two-qubit diagonal gates in between: the first of
+    int32_t n_shared;  // them in `between`, and their number
+    int8_t plain;      // more than one control
+    int8_t apart;      // something else reads the qubit in between
+  };
+  struct Shared {
+    int64_t other;  // the other qubit with its version
+    int32_t pos;    // position in the order
+  };
+  // a qubit and its version: the dense gates on it before
+  static int64_t versioned(int q, int v) { return int64_t(q) << 32 | int64_t(v); }
+  int n = 0;
+  std::vector<int8_t> qa, qb;  // two-qubit diagonal gates: qa < qb (else -1)
+  std::vector<int> na, nb;     // and the next dense gates on these (-1: none)
+  std::vector<int> ka, kb;     // the same as indices into `targets` (the end
+                               // of the qubit's row: none)
+  std::vector<int> owner0;     // a one-qubit diagonal gate's qubit, else -1
+  std::vector<Target> targets;
+  std::vector<Shared> between;
+  std::array<int, 65> row;  // targets of qubit q: row[q] .. row[q + 1] - 1
+  uint64_t used = 0;        // qubits with targets
+
+  PassOrder(const std::vector<HostGate>& G, const std::vector<int>& order)
+      : n(int(order.size())) {
+    const size_t N = order.size();
+    qa.assign(N, -1);
+    qb.assign(N, -1);
+    na.assign(N, -1);
+    nb.assign(N, -1);
+    ka.assign(N, 0);
+    kb.assign(N, 0);
+    owner0.assign(N, -1);
+    std::vector<int8_t> target(N, -1);
+    row.fill(0);
+    std::array<int, 65> shared_row;
+    shared_row.fill(0);
+    for (size_t i = 0; i < N; ++i) {
+      const HostGate& g = G[size_t(order[i])];
+      const uint64_t tm = g.touch();
+      if (!g.diagonal) {
+        if (g.k == 1) {
+          target[i] = int8_t(g.t[0]);
+          ++row[g.t[0] + 1];
+          used |= uint64_t(1) << g.t[0];
+        }
+      } else if (popc(tm) == 1) {
+        owner0[i] = __builtin_ctzll(tm);
+      } else if (popc(tm) == 2) {
+        qa[i] = int8_t(__builtin_ctzll(tm));
+        qb[i] = int8_t(63 - __builtin_clzll(tm));
+        ++shared_row[qa[i] + 1];
+        ++shared_row[qb[i] + 1];
+      }
     }
     for (int q = 0; q < 64; ++q) {
-      eo[q + 1] += eo[q];
-      to[q + 1] += to[q];
+      row[q + 1] += row[q];
+      shared_row[q + 1] += shared_row[q];
     }
-    ev.resize(eo[64]);
-    tp.resize(to[64]);
-    std::array<int, 64> fe, ft;
-    std::copy(eo.begin(), eo.begin() + 64, fe.begin());
-    std::copy(to.begin(), to.begin() + 64, ft.begin());
-    for (int i = 0; i < N; ++i) {
-      for (uint64_t m = G[order[i]].touch(); m; m &= m - 1)
-        ev[fe[__builtin_ctzll(m)]++] = i;
-      if (target[i] >= 0) tp[ft[target[i]]++] = i;
+    targets.resize(size_t(row[64]));
+    between.resize(size_t(shared_row[64]));
+    std::array<int, 64> tf, sf, s0, dense;
+    std::copy(row.begin(), row.begin() + 64, tf.begin());
+    std::copy(shared_row.begin(), shared_row.begin() + 64, sf.begin());
+    s0 = sf;
+    dense.fill(0);
+    uint64_t apart = 0;
+    for (size_t i = 0; i < N; ++i) {
+      if (owner0[i] >= 0) continue;  // its qubit's next gate takes it
+      const HostGate& g = G[size_t(order[i])];
+      if (qa[i] >= 0) {
+        const int a = qa[i], b = qb[i];
+        ka[i] = tf[a];
+        kb[i] = tf[b];
+        between[size_t(sf[a]++)] = {versioned(b, dense[b]), int32_t(i)};
+        between[size_t(sf[b]++)] = {versioned(a, dense[a]), int32_t(i)};
+        continue;
+      }
+      const int t = target[i];
+      for (uint64_t m = g.touch(); m; m &= m - 1) {
+        const int q = __builtin_ctzll(m);
+        if (q != t) {
+          apart |= uint64_t(1) << q;
+          continue;
+        }
+        targets[size_t(tf[q]++)] = {
+            g.c == 1 ? versioned(g.ctl[0], dense[g.ctl[0]]) : int64_t(-1),
+            int32_t(s0[q]), int32_t(sf[q] - s0[q]), int8_t(g.c > 1),
+            int8_t(apart >> q & 1)};
+        s0[q] = sf[q];
+        apart &= ~(uint64_t(1) << q);
+      }
+      if (t >= 0) ++dense[t];
+    }
+    std::array<int, 64> next;
+    next.fill(-1);
+    for (size_t i = N; i-- > 0;) {
+      if (qa[i] >= 0) {
+        na[i] = next[qa[i]];
+        nb[i] = next[qb[i]];
+      }
+      if (target[i] >= 0) next[target[i]] = int(i);
     }
   }
-  int size() const { return int(order.size()); }
-  // dense gates on target b before position i
-  int version(int b, int i) const {
-    return int(std::lower_bound(tp.begin() + to[b], tp.begin() + to[b + 1], i) -
-               (tp.begin() + to[b]));
+
+  // The most joins on a qubit is a dynamic program over its dense gates.  Its
+  // state after a gate: the most joins so far with the current op unmuxed
+  // (bn) or muxed by the reads mr (bm); kNo: not possible.
+  static constexpr int kNo = -(1 << 30);
+  struct State {
+    int bn, bm;
+    int64_t mr;
+  };
+
+  // The state after target k (index into targets) of qubit q, from the state
+  // before it, under `owner`.
+  State step(int k, int q, const State& s, const std::vector<int>& owner) const {
+    const Target& x = targets[size_t(k)];
+    const bool first = k == row[q];
+    const bool prev_plain = !first && targets[size_t(k) - 1].plain;
+    bool apart = x.apart, bad = false;
+    int64_t rd = -1;  // the reads attached to the gate
+    const Shared* sh = between.data() + x.shared;
+    for (int j = 0; j < x.n_shared; ++j) {
+      const int64_t v = sh[j].other;
+      if (owner[size_t(sh[j].pos)] != q) {
+        apart = true;
+      } else if (rd < 0) {
+        rd = v;
+      } else if (rd != v) {
+        bad = true;
+      }
+    }
+    const int64_t ctl = x.read;
+    if (ctl >= 0) {
+      if (rd < 0) rd = ctl;
+      else if (rd != ctl) bad = true;
+    }
+    if (bad || x.plain) {  // the reads are emitted apart from the gate
+      apart = true;
+      rd = ctl;
+    }
+    const bool join = !first && !apart && !x.plain && !prev_plain;
+    int best = first ? 0 : std::max(s.bn, s.bm);
+    if (join && s.bn >= 0) best = std::max(best, s.bn + 1);
+    State r;
+    if (rd < 0) {
+      r = {best, join && s.bm >= 0 ? s.bm + 1 : kNo, s.mr};
+    } else {
+      if (join && s.bm >= 0 && s.mr == rd) best = std::max(best, s.bm + 1);
+      r = {kNo, best, rd};
+    }
+    if (x.plain) r = {std::max(r.bn, r.bm), kNo, r.mr};  // stands alone
+    return r;
   }
-  // next position after i with a dense gate on target q (-1: none)
-  int next_on(int q, int i) const {
-    auto it = std::upper_bound(tp.begin() + to[q], tp.begin() + to[q + 1], i);
-    return it == tp.begin() + to[q + 1] ? -1 : *it;
+  static constexpr State kStart = {kNo, kNo, -1};
+};
+
+// The joins of every qubit under an ownership, kept gate by gate so that a
+// flip of one shared gate is priced from the gate after it, and only until
+// the state is again the kept one, up to a constant.  Planning is host work
+// that a call with new gates pays each time: 1180 gates on 20 qubits took
+// 1.23 ms of a 1.64 ms call, half of it in these joins, and 40 served
+// requests of 8 to 22 qubits spent 26 of 36 ms in it.  With this table, the
+// gate records in rows (PassOrder, GateLite), scans that end where nothing
+// more can be taken and owners kept from the plan for the emitter, the call
+// takes 0.83 ms and the requests 10.7 ms, with the same programs.
+struct JoinTable {
+  const PassOrder& po;
+  std::vector<PassOrder::State> after;  // by target
+  explicit JoinTable(const PassOrder& p) : po(p), after(p.targets.size()) {}
+
+  // Fill qubit q's states from target k on; its joins.
+  int fill(int q, int k, const std::vector<int>& owner) {
+    const int end = po.row[q + 1];
+    if (end == po.row[q]) return 0;
+    PassOrder::State s =
+        k == po.row[q] ? PassOrder::kStart : after[size_t(k) - 1];
+    for (; k < end; ++k) s = after[size_t(k)] = po.step(k, q, s, owner);
+    s = after[size_t(end) - 1];
+    return std::max(0, std::max(s.bn, s.bm));
   }
-  // the other qubit of the two-qubit gate at position d
-  int other(int d, int q) const {
-    return __builtin_ctzll(G[order[d]].touch() & ~(uint64_t(1) << q));
+
+  // Qubit q's joins under `owner`, which differs from the filled states' in
+  // a gate before target k only; `joins` is the filled states' value.
+  int price(int q, int k, int joins, const std::vector<int>& owner) const {
+    const int end = po.row[q + 1];
+    if (k >= end) return joins;
+    PassOrder::State s =
+        k == po.row[q] ? PassOrder::kStart : after[size_t(k) - 1];
+    for (; k < end; ++k) {
+      s = po.step(k, q, s, owner);
+      const PassOrder::State& o = after[size_t(k)];
+      const bool n = s.bn >= 0, m = s.bm >= 0;
+      if (n == (o.bn >= 0) && m == (o.bm >= 0) && (!m || s.mr == o.mr) &&
+          (!n || !m || s.bn - o.bn == s.bm - o.bm))
+        return joins + (n ? s.bn - o.bn : s.bm - o.bm);
+    }
+    return std::max(0, std::max(s.bn, s.bm));
   }
 };
 
@@ -233,125 +402,63 @@ static std::vector<int> choose_owners(const PassOrder& po,
                                       const std::vector<int>* seg_of,
                                       std::vector<int>* shared,
                                       int* joined = nullptr) {
-  const std::vector<HostGate>& G = po.G;
-  const int N = po.size();
-  std::vector<int> owner(N, -1);
+  const int N = po.n;
+  std::vector<int> owner = po.owner0;
   shared->clear();
   for (int d = 0; d < N; ++d) {
-    const HostGate& g = G[po.order[d]];
-    if (!g.diagonal) continue;
-    const uint64_t tm = g.touch();
-    if (popc(tm) == 1) {
-      owner[d] = __builtin_ctzll(tm);
-    } else if (popc(tm) == 2) {
-      const int a = __builtin_ctzll(tm), b = 63 - __builtin_clzll(tm);
-      const int na = po.next_on(a, d), nb = po.next_on(b, d);
-      const bool apart = seg_of && na >= 0 && nb >= 0 &&
-                         (*seg_of)[na] != (*seg_of)[nb];
-      if (na >= 0 && nb >= 0 && !apart) shared->push_back(d);
-      else if (na >= 0 && (nb < 0 || (*seg_of)[na] < (*seg_of)[nb])) owner[d] = a;
-      else if (nb >= 0) owner[d] = b;
-    }
+    if (po.qa[d] < 0) continue;
+    const int na = po.na[d], nb = po.nb[d];
+    const bool apart = seg_of && na >= 0 && nb >= 0 &&
+                       (*seg_of)[na] != (*seg_of)[nb];
+    if (na >= 0 && nb >= 0 && !apart) shared->push_back(d);
+    else if (na >= 0 && (nb < 0 || (*seg_of)[na] < (*seg_of)[nb])) owner[d] = po.qa[d];
+    else if (nb >= 0) owner[d] = po.qb[d];
   }
-  // the most joins on qubit q under `owner`
-  auto joins = [&](int q) -> int {
-    int bn = -1, bm = -1, mq = -1, mv = -1;  // best per op state
-    bool first = true, apart = false, prev_plain = false;
-    int rq = -1, rv = -1;
-    bool rbad = false;
-    auto read = [&](int b, int v) {
-      if (rq < 0) {
-        rq = b;
-        rv = v;
-      } else if (rq != b || rv != v) {
-        rbad = true;
-      }
-    };
-    for (int e = po.eo[q]; e < po.eo[q + 1]; ++e) {
-      const int i = po.ev[e];
-      const HostGate& g = G[po.order[i]];
-      if (po.target[i] != q) {
-        if (!g.diagonal || owner[i] != q || popc(g.touch()) > 2) {
-          apart = true;  // q is read by another op, or the gate stands apart
-        } else if (popc(g.touch()) == 2) {
-          const int b = po.other(i, q);
-          read(b, po.version(b, i));
-        }
-        continue;
-      }
-      const bool plain = g.c > 1;
-      if (g.c == 1) read(g.ctl[0], po.version(g.ctl[0], i));
-      if (rbad || plain) {  // the reads are emitted apart from the gate
-        apart = true;
-        rq = rv = -1;
-        if (g.c == 1) {
-          rq = g.ctl[0];
-          rv = po.version(rq, i);
-        }
-      }
-      const bool join = !first && !apart && !plain && !prev_plain;
-      const int top = std::max(bn, bm);
-      if (first) {
-        bn = rq < 0 ? 0 : -1;
-        bm = rq < 0 ? -1 : 0;
-        mq = rq;
-        mv = rv;
-      } else if (rq < 0) {
-        const int nn = std::max(top, join && bn >= 0 ? bn + 1 : -1);
-        bm = join && bm >= 0 ? bm + 1 : -1;
-        bn = nn;
-      } else {
-        int nm = top;
-        if (join && bn >= 0) nm = std::max(nm, bn + 1);
-        if (join && bm >= 0 && mq == rq && mv == rv) nm = std::max(nm, bm + 1);
-        bm = nm;
-        bn = -1;
-        mq = rq;
-        mv = rv;
-      }
-      if (plain) {  // a controlled op stands alone
-        bn = std::max(bn, bm);
-        bm = -1;
-      }
-      first = false;
-      apart = false;
-      prev_plain = plain;
-      rq = rv = -1;
-      rbad = false;
+  JoinTable jt(po);
+  auto joins_all = [&](std::array<int, 64>* jq) {
+    int total = 0;
+    jq->fill(0);
+    for (uint64_t m = po.used; m; m &= m - 1) {
+      const int q = __builtin_ctzll(m);
+      total += (*jq)[q] = jt.fill(q, po.row[q], owner);
     }
-    return std::max(0, std::max(bn, bm));
+    return total;
   };
+  std::array<int, 64> jq;
   if (shared->empty()) {
-    if (joined) {
-      *joined = 0;
-      for (int q = 0; q < 64; ++q)
-        if (po.eo[q + 1] > po.eo[q]) *joined += joins(q);
-    }
+    if (joined) *joined = joins_all(&jq);
     return owner;
   }
   std::vector<int> best_owner;
   int best_total = -1;
+  // A flip that gained nothing gains nothing again until another flip of one
+  // of its two qubits is kept: flips are numbered, each qubit remembers its
+  // last kept one and each gate when it was last tried.
+  std::vector<int> tried(shared->size());
   for (int start = 0; start < 2; ++start) {
-    for (int d : *shared) {
-      const uint64_t tm = G[po.order[d]].touch();
-      owner[d] = start == 0 ? __builtin_ctzll(tm) : 63 - __builtin_clzll(tm);
-    }
-    std::array<int, 64> jq;
-    jq.fill(0);
-    int total = 0;
-    for (int q = 0; q < 64; ++q)
-      if (po.eo[q + 1] > po.eo[q]) total += (jq[q] = joins(q));
+    for (int d : *shared) owner[d] = start == 0 ? po.qa[d] : po.qb[d];
+    int total = joins_all(&jq), now = 1;
+    std::array<int, 64> kept;
+    kept.fill(0);
+    std::fill(tried.begin(), tried.end(), -1);
     for (int round = 0; round < 8; ++round) {
       bool better = false;
-      for (int d : *shared) {
-        const int a = owner[d], b = po.other(d, a);
+      for (size_t i = 0; i < shared->size(); ++i) {
+        const int d = (*shared)[i];
+        const int a = owner[d], b = a == po.qa[d] ? po.qb[d] : po.qa[d];
+        if (tried[i] >= kept[a] && tried[i] >= kept[b]) continue;
         owner[d] = b;
-        const int ja = joins(a), jb = joins(b);
+        const bool low = a == po.qa[d];
+        const int ta = low ? po.ka[d] : po.kb[d], tb = low ? po.kb[d] : po.ka[d];
+        const int ja = jt.price(a, ta, jq[a], owner),
+                  jb = jt.price(b, tb, jq[b], owner);
+        tried[i] = now++;
         if (ja + jb > jq[a] + jq[b]) {
           total += ja + jb - jq[a] - jq[b];
-          jq[a] = ja;
-          jq[b] = jb;
+          jq[a] = jt.fill(a, ta, owner);
+          jq[b] = jt.fill(b, tb, owner);
           better = true;
+          kept[a] = kept[b] = now++;
         } else {
           owner[d] = a;
         }
@@ -367,7 +474,8 @@ static std::vector<int> choose_owners(const PassOrder& po,
   return best_owner;
 }
 
-// The processing order of each segment of a tile pass (see above).
+// The processing order of each segment of a tile pass (see above), from the
+// owners the plan chose for its gates.
 static std::vector<std::vector<int>> merge_order(
     const Pass& p, const std::vector<HostGate>& G) {
   std::vector<int> order, seg_of;
@@ -379,20 +487,19 @@ static std::vector<std::vector<int>> merge_order(
       seg_of.push_back(int(si));
     }
   }
-  const PassOrder po(G, std::move(order));
-  std::vector<int> shared;
-  const std::vector<int> owner = choose_owners(po, &seg_of, &shared);
+  const std::vector<int>&shared = p.shared, &owner = p.owner;
   if (shared.empty()) return out;
+  const PassOrder po(G, order);
   // per segment: dependency edges (gates that do not commute keep their
   // order: per qubit, a dense gate after everything since the previous
   // dense gate, anything else after the previous dense gate) plus "owner's
   // next gate first" edges; Kahn's algorithm taking the earliest ready
   // gate; a cycle keeps the segment's order
-  const int N = po.size();
-  std::vector<std::vector<int>> first_of(N);
+  const int N = po.n;
+  std::vector<std::vector<int>> first_of(static_cast<size_t>(N));
   for (int d : shared) {
-    const int ua = po.next_on(owner[d], d),
-              ub = po.next_on(po.other(d, owner[d]), d);
+    const bool low = owner[d] == po.qa[d];
+    const int ua = low ? po.na[d] : po.nb[d], ub = low ? po.nb[d] : po.na[d];
     if (ua > ub && seg_of[ua] == seg_of[ub]) first_of[ua].push_back(ub);
   }
   int lo = 0;
@@ -411,7 +518,7 @@ static std::vector<std::vector<int>> merge_order(
       last_dense.fill(-1);
       std::array<std::vector<int>, 64> since;
       for (int j = 0; j < m; ++j) {
-        const HostGate& g = G[po.order[lo + j]];
+        const HostGate& g = G[order[lo + j]];
         for (uint64_t t = g.touch(); t; t &= t - 1) {
           const int q = __builtin_ctzll(t);
           if (last_dense[q] >= 0) edge(last_dense[q], j);
@@ -435,7 +542,7 @@ static std::vector<std::vector<int>> merge_order(
         std::pop_heap(heap.begin(), heap.end(), std::greater<int>());
         const int i = heap.back();
         heap.pop_back();
-        res.push_back(po.order[lo + i]);
+        res.push_back(order[lo + i]);
         for (int j : succ[i])
           if (--indeg[j] == 0) {
             heap.push_back(j);
@@ -466,11 +573,18 @@ static void plan_tiled(const std::vector<HostGate>& G, int n, int b,
   const int L = std::min(o.tile_log2, n);
   const int RB = o.reg_log2;
   const int m = std::min(o.low_qubits, L);
+  const uint64_t all = n >= 64 ? ~0ull : (uint64_t(1) << n) - 1;
   std::vector<int> pending(G.size());
-  for (size_t i = 0; i < G.size(); ++i) pending[i] = int(i);
+  std::vector<GateLite> lg(G.size());
+  for (size_t i = 0; i < G.size(); ++i) {
+    pending[i] = int(i);
+    lg[i] = lite(G[i]);
+  }
+  // positions in the current pass of the gates it takes, by gate
+  std::vector<int> at(G.size(), -1);
 
   while (!pending.empty()) {
-    if (!tileable(G[pending[0]])) {
+    if (!lg[size_t(pending[0])].tileable) {
       add_plain(G, pending[0], n, b, plan);
       pending.erase(pending.begin());
       continue;
@@ -483,32 +597,30 @@ static void plan_tiled(const std::vector<HostGate>& G, int n, int b,
     // windows follow the light cone of nearest-neighbour circuits, where the
     // greedy choice takes one or two layers of a window's gates per pass.
     const uint64_t low = (m >= 64) ? ~0ull : ((1ull << m) - 1);
-    auto tile_ok = [&](int gi) { return tileable(G[gi]); };
+    auto need_dense = [&](int gi) { return lg[size_t(gi)].dense; };
+    auto tile_ok = [&](int gi) { return lg[size_t(gi)].tileable; };
     auto no_took = [](int) {};
-    auto dense_count = [&](const std::vector<int>& t) {
-      int c = 0;
-      for (int gi : t) c += !G[gi].diagonal;
-      return c;
-    };
     uint64_t Q = low;
     std::vector<int> taken, rest = pending;
-    greedy(G, &rest, &Q, L, [](const HostGate& g) { return g.dense(); },
-           tile_ok, &taken, no_took);
-    int best = dense_count(taken), best_s0 = -1;
+    greedy(lg, all, &rest, &Q, L, need_dense, tile_ok, &taken, no_took);
+    int best = 0, best_s0 = -1;
+    for (int gi : taken) best += !lg[size_t(gi)].diagonal;
     for (int s0 = m; s0 + (L - m) <= n && L > m; ++s0) {
-      // the dense gates a fixed window takes (the greedy scan, counting)
+      // the dense gates a fixed window takes (the greedy scan, counting, to
+      // where a skipped gate touches each of its qubits)
       uint64_t W = low;
       for (int q = s0; q < s0 + L - m; ++q) W |= uint64_t(1) << q;
       uint64_t blk_touch = 0, blk_dense = 0;
       int c = 0;
       for (int gi : pending) {
-        const HostGate& g = G[gi];
-        if (!(g.dense() & blk_touch) && !(g.touch() & blk_dense) &&
-            tileable(g) && !(g.dense() & ~W)) {
+        const GateLite& g = lg[size_t(gi)];
+        if (!(g.dense & blk_touch) && !(g.touch & blk_dense) && g.tileable &&
+            !(g.dense & ~W)) {
           c += !g.diagonal;
         } else {
-          blk_touch |= g.touch();
-          blk_dense |= g.dense();
+          blk_touch |= g.touch;
+          blk_dense |= g.dense;
+          if (!(W & ~blk_touch)) break;
         }
       }
       if (c > best) {
@@ -521,8 +633,7 @@ static void plan_tiled(const std::vector<HostGate>& G, int n, int b,
       for (int q = best_s0; q < best_s0 + L - m; ++q) Q |= uint64_t(1) << q;
       taken.clear();
       rest = pending;
-      greedy(G, &rest, &Q, L, [](const HostGate& g) { return g.dense(); },
-             tile_ok, &taken, no_took);
+      greedy(lg, all, &rest, &Q, L, need_dense, tile_ok, &taken, no_took);
     }
     pending.swap(rest);
     // Fill the tile's qubit set up to exactly L qubits (lowest free first).
@@ -548,24 +659,34 @@ static void plan_tiled(const std::vector<HostGate>& G, int n, int b,
     // it, chosen as if there were no segments) should keep that gate no
     // later than the other side's: with `keep_owners`, a gate waits for the
     // owners' gates it must follow (`after`).
-    std::unordered_map<int, std::vector<int>> after;  // gate -> owners' gates
     p.steer = o.steer;
+    for (size_t i = 0; i < taken.size(); ++i) at[size_t(taken[i])] = int(i);
+    struct Wait {
+      int gate, owner;  // positions in `taken`
+    };
+    std::vector<Wait> after;  // by waiting gate, then in order of discovery
     if (o.steer) {
       const PassOrder po(G, taken);
       std::vector<int> shared;
       const std::vector<int> owner = choose_owners(po, nullptr, &shared);
       for (int d : shared) {
-        const int ua = po.next_on(owner[d], d),
-                  ub = po.next_on(po.other(d, owner[d]), d);
+        const bool lo = owner[d] == po.qa[d];
+        const int ua = lo ? po.na[d] : po.nb[d], ub = lo ? po.nb[d] : po.na[d];
         if (ua < 0 || ub < 0) continue;
-        after[po.order[ub]].push_back(po.order[ua]);
+        after.push_back({ub, ua});
       }
+      std::stable_sort(after.begin(), after.end(),
+                       [](const Wait& x, const Wait& y) { return x.gate < y.gate; });
     }
+    std::vector<int> wait_of(taken.size() + 1, 0);  // rows of `after`
+    for (const Wait& w : after) ++wait_of[size_t(w.gate) + 1];
+    for (size_t i = 0; i < taken.size(); ++i) wait_of[i + 1] += wait_of[i];
+    std::vector<char> placed;
     auto build_segs = [&](bool seed_io, bool keep_owners) {
       std::vector<Pass::Seg> segs;
       std::vector<int> seg_pending = taken;
       bool waits = keep_owners && !after.empty();
-      std::unordered_set<int> placed;
+      placed.assign(taken.size(), 0);
       bool first = true;
       while (!seg_pending.empty()) {
         // seed_io: the first segment takes the I/O layout's register bits
@@ -573,35 +694,32 @@ static void plan_tiled(const std::vector<HostGate>& G, int n, int b,
         uint64_t S = (first && seed_io) ? ((1ull << RB) - 1) << (L - RB) : 0;
         first = false;
         std::vector<int> seg_gates;
-        auto need = [&](const HostGate& g) -> uint64_t {
-          return g.diagonal ? 0 : (1ull << local_of[g.t[0]]);
+        auto need = [&](int gi) -> uint64_t {
+          return lg[size_t(gi)].diagonal
+                     ? 0
+                     : (1ull << local_of[__builtin_ctzll(lg[size_t(gi)].dense)]);
         };
         if (!waits) {
-          greedy(G, &seg_pending, &S, RB, need, [](int) { return true; },
+          greedy(lg, all, &seg_pending, &S, RB, need, [](int) { return true; },
                  &seg_gates, [](int) {});
         } else {
-          greedy(G, &seg_pending, &S, RB, need,
+          greedy(lg, all, &seg_pending, &S, RB, need,
                  [&](int gi) {
-                   const auto it = after.find(gi);
-                   if (it == after.end()) return true;
-                   for (int ga : it->second)
-                     if (!placed.count(ga)) return false;
+                   const size_t i = size_t(at[size_t(gi)]);
+                   for (int w = wait_of[i]; w < wait_of[i + 1]; ++w)
+                     if (!placed[size_t(after[size_t(w)].owner)]) return false;
                    return true;
                  },
-                 &seg_gates, [&](int gi) { placed.insert(gi); });
+                 &seg_gates, [&](int gi) { placed[size_t(at[size_t(gi)])] = 1; });
           bool any_dense = false;
-          for (int gi : seg_gates) any_dense |= !G[gi].diagonal;
+          for (int gi : seg_gates) any_dense |= !lg[size_t(gi)].diagonal;
           if (!any_dense && !seg_pending.empty()) {
             // waiting gates block every remaining one: drop the waits
             waits = false;
             seg_pending.insert(seg_pending.begin(), seg_gates.begin(),
                                seg_gates.end());
-            std::vector<int> keep_order;
-            for (int gi : taken)
-              if (std::find(seg_pending.begin(), seg_pending.end(), gi) !=
-                  seg_pending.end())
-                keep_order.push_back(gi);
-            seg_pending.swap(keep_order);
+            std::sort(seg_pending.begin(), seg_pending.end(),
+                      [&](int x, int y) { return at[size_t(x)] < at[size_t(y)]; });
             first = segs.empty();
             continue;
           }
@@ -629,20 +747,38 @@ static void plan_tiled(const std::vector<HostGate>& G, int n, int b,
         r += !same(segs[i], segs[i - 1].reg_bits);
       return r;
     };
+    auto same_segs = [&](const std::vector<Pass::Seg>& x,
+                         const std::vector<Pass::Seg>& y) {
+      if (x.size() != y.size()) return false;
+      for (size_t i = 0; i < x.size(); ++i)
+        if (!std::equal(x[i].reg_bits, x[i].reg_bits + RB, y[i].reg_bits) ||
+            x[i].gates != y[i].gates)
+          return false;
+      return true;
+    };
     // ops the emitted program would hold, as the ownership model counts
-    // them: one-target gates less the joins it finds
-    auto op_count = [&](const std::vector<Pass::Seg>& segs) -> double {
-      std::vector<int> order, seg_of;
+    // them: one-target gates less the joins it finds; and the owners behind
+    // that count
+    struct Owners {
+      std::vector<int> owner, shared;
+    };
+    int ones = 0;
+    for (int gi : taken) {
+      const GateLite& g = lg[size_t(gi)];
+      ones += !g.diagonal;  // a tile pass takes dense gates of one target
+    }
+    std::vector<int> order, seg_of;
+    auto op_count = [&](const std::vector<Pass::Seg>& segs, Owners* w) -> double {
+      order.clear();
+      seg_of.clear();
       for (size_t si = 0; si < segs.size(); ++si)
         for (int gi : segs[si].gates) {
           order.push_back(gi);
           seg_of.push_back(int(si));
         }
-      const PassOrder po(G, std::move(order));
-      int ones = 0, joined = 0;
-      for (int t : po.target) ones += t >= 0;
-      std::vector<int> shared;
-      choose_owners(po, &seg_of, &shared, &joined);
+      const PassOrder po(G, order);
+      int joined = 0;
+      w->owner = choose_owners(po, &seg_of, &w->shared, &joined);
       return double(ones - joined);
     };
     // Of the plain and the I/O-seeded scans, with and without the owners'
@@ -657,16 +793,22 @@ static void plan_tiled(const std::vector<HostGate>& G, int n, int b,
       std::vector<Pass::Seg> seeded = build_segs(true, false);
       if (relayouts(seeded) < relayouts(p.segs)) p.segs.swap(seeded);
     } else if (!p.segs.empty()) {
-      double best = op_count(p.segs) + relayout_ops * relayouts(p.segs);
+      Owners chosen;
+      double best = op_count(p.segs, &chosen) + relayout_ops * relayouts(p.segs);
       for (int v = 1; v < 4; ++v) {
         if ((v & 2) && after.empty()) continue;
         std::vector<Pass::Seg> alt = build_segs(v & 1, (v & 2) != 0);
-        const double c = op_count(alt) + relayout_ops * relayouts(alt);
+        if (same_segs(alt, p.segs)) continue;
+        Owners w;
+        const double c = op_count(alt, &w) + relayout_ops * relayouts(alt);
         if (c < best) {
           best = c;
           p.segs.swap(alt);
+          std::swap(chosen, w);
         }
       }
+      p.owner = std::move(chosen.owner);
+      p.shared = std::move(chosen.shared);
     }
     for (const auto& sg : p.segs)
       p.gates.insert(p.gates.end(), sg.gates.begin(), sg.gates.end());
@@ -681,8 +823,13 @@ static void plan_tiled(const std::vector<HostGate>& G, int n, int b,
 static void plan_fused(const std::vector<HostGate>& G, int n, int b,
                        const PlanOptions& o, Plan* plan) {
   const int K = std::min(o.k_max, n);
+  const uint64_t all = n >= 64 ? ~0ull : (uint64_t(1) << n) - 1;
   std::vector<int> pending(G.size());
-  for (size_t i = 0; i < G.size(); ++i) pending[i] = int(i);
+  std::vector<GateLite> lg(G.size());
+  for (size_t i = 0; i < G.size(); ++i) {
+    pending[i] = int(i);
+    lg[i] = lite(G[i]);
+  }
   auto fits = [K](const HostGate& g) { return popc(g.touch()) <= K; };
   while (!pending.empty()) {
     if (!fits(G[pending[0]])) {
@@ -692,8 +839,8 @@ static void plan_fused(const std::vector<HostGate>& G, int n, int b,
     }
     uint64_t S = 0;
     std::vector<int> taken;
-    greedy(G, &pending, &S, K,
-           [](const HostGate& g) { return g.touch(); },
+    greedy(lg, all, &pending, &S, K,
+           [&](int gi) { return lg[size_t(gi)].touch; },
            [&](int gi) { return fits(G[gi]); }, &taken, [](int) {});
     Pass p;
     p.kind = kPassFused;
@@ -864,13 +1011,13 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
     tp.out_shift[tp.n_out++] = j;
   }
   auto place_ctrl = [&](TileOp* op, uint64_t mask) {
-    for (int q = 0; q < 64; ++q)
-      if (mask >> q & 1) {
-        if (p.qubits >> q & 1)
-          op->lctrl |= 1u << local_of[q];
-        else
-          op->gctrl |= uint64_t(1) << q;
-      }
+    for (; mask; mask &= mask - 1) {
+      const int q = __builtin_ctzll(mask);
+      if (p.qubits >> q & 1)
+        op->lctrl |= 1u << local_of[q];
+      else
+        op->gctrl |= uint64_t(1) << q;
+    }
   };
   auto emit_diag = [&](const HostGate& g) {
     TileOp op = {};
@@ -909,12 +1056,15 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
   // qubit's value cannot have changed in between (no dense op on it since):
   // M(v) <- M_new(v) M_prev(v).  The state after the pass is unchanged up
   // to rounding.
-  const int n_q = 64;
-  std::vector<int> last_touch(n_q, -1), last_dense(n_q, -1);
+  std::array<int, 64> last_touch, last_dense;
+  last_touch.fill(-1);
+  last_dense.fill(-1);
   const int op_base = int(tops->size());
   auto touch_op = [&](uint64_t mask, int idx) {
-    for (int q = 0; q < n_q; ++q)
-      if (mask >> q & 1) last_touch[q] = std::max(last_touch[q], idx);
+    for (; mask; mask &= mask - 1) {
+      const int q = __builtin_ctzll(mask);
+      last_touch[q] = std::max(last_touch[q], idx);
+    }
   };
   auto mux_code = [&](int q) -> int32_t {
     return q < 0 ? kMuxNone
@@ -924,9 +1074,9 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
   std::vector<int> op_mux_q, op_target_q;
   // pending (deferred) one-target products per qubit, and the segment
   // (pass-local index) where each would be emitted
-  std::vector<std::array<double, 8>> pp(n_q);
-  std::vector<char> has_pp(n_q, 0);
-  std::vector<int> pp_seg(n_q, -1);
+  std::array<std::array<double, 8>, 64> pp;
+  uint64_t has_pp = 0;  // the qubits that have one
+  std::array<int, 64> pp_seg;
   int cur_si = 0;          // the segment being emitted
   TileSeg* cur_ts = nullptr;
   auto emit_diag_tracked = [&](const HostGate& g) {
@@ -1104,7 +1254,7 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
     }
     if (defer && mux_q < 0) {
       std::memcpy(pp[t].data(), M[0], sizeof M[0]);
-      has_pp[t] = 1;
+      has_pp |= uint64_t(1) << t;
       pp_seg[t] = seg_idx;
       return "";
     }
@@ -1162,19 +1312,18 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
   // goes into the latest segment so far that holds its qubit in a register
   // bit (at that segment's end when the segment is already closed).
   auto flush = [&](int q) -> std::string {
-    if (!has_pp[q]) return "";
-    has_pp[q] = 0;
+    if (!(has_pp >> q & 1)) return "";
+    has_pp &= ~(uint64_t(1) << q);
     double M[2][8];
     std::memcpy(M[0], pp[q].data(), sizeof M[0]);
     std::memcpy(M[1], pp[q].data(), sizeof M[1]);
     return put_dense(q, -1, M, pp_seg[q], false);
   };
   auto flush_mask = [&](uint64_t mask) -> std::string {
-    for (int q = 0; q < n_q; ++q)
-      if (mask >> q & 1) {
-        std::string e = flush(q);
-        if (!e.empty()) return e;
-      }
+    for (mask &= has_pp; mask; mask &= mask - 1) {
+      std::string e = flush(__builtin_ctzll(mask));
+      if (!e.empty()) return e;
+    }
     return "";
   };
   auto touched_by = [&](const std::vector<int>& ds) {
@@ -1182,7 +1331,7 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
     for (int d : ds) m |= G[d].touch();
     return m;
   };
-  std::vector<int> pend;
+  std::vector<int> pend, hit;
   std::vector<std::vector<int>> seg_order;
   if (p.steer) {
     seg_order = merge_order(p, G);
@@ -1200,7 +1349,7 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
     // segment so far that holds its qubit in a register bit
     for (int i = 0; i < RB; ++i) {
       const int q = p.q[sg.reg_bits[i]];
-      if (has_pp[q]) pp_seg[q] = int(si);
+      if (has_pp >> q & 1) pp_seg[q] = int(si);
     }
     for (int gi : seg_order[si]) {
       const HostGate& g = G[gi];
@@ -1209,10 +1358,13 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
         continue;
       }
       const int t = g.t[0];
-      std::vector<int> hit, keep;
-      for (int d : pend)
-        (G[d].touch() >> t & 1 ? hit : keep).push_back(d);
-      pend.swap(keep);
+      hit.clear();
+      size_t left = 0;
+      for (int d : pend) {
+        if (G[d].touch() >> t & 1) hit.push_back(d);
+        else pend[left++] = d;
+      }
+      pend.resize(left);
       // the gate as mux matrices
       int mux_q = -1;
       const bool plain = g.c > 1;  // more than one control: a controlled op
@@ -1290,8 +1442,8 @@ std::string emit_tile_pass(const Pass& p, const std::vector<HostGate>& G,
         continue;
       }
       // absorb the target's pending product (applied before this gate)
-      if (has_pp[t]) {
-        has_pp[t] = 0;
+      if (has_pp >> t & 1) {
+        has_pp &= ~(uint64_t(1) << t);
         for (int v = 0; v < 2; ++v) {
           double out[8];
           const double* A = M[v];

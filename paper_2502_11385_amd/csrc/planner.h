@@ -2,6 +2,7 @@
 #pragma once
 #include <stdint.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -9,15 +10,62 @@
 
 namespace qsv {
 
+// A gate's matrix entries: a fixed array that holds a 2x2 matrix without an
+// allocation of its own.
+class GateMatrix {
+ public:
+  GateMatrix() = default;
+  GateMatrix(const GateMatrix& o) { assign(o.begin(), o.end()); }
+  GateMatrix(GateMatrix&& o) noexcept { take(o); }
+  GateMatrix& operator=(const GateMatrix& o) {
+    if (this != &o) assign(o.begin(), o.end());
+    return *this;
+  }
+  GateMatrix& operator=(GateMatrix&& o) noexcept {
+    if (this != &o) {
+      delete[] heap_;
+      take(o);
+    }
+    return *this;
+  }
+  ~GateMatrix() { delete[] heap_; }
+  void assign(const double* b, const double* e) {
+    const size_t n = size_t(e - b);
+    double* h = n > kInline ? new double[n] : nullptr;
+    std::copy(b, e, h ? h : inline_);
+    delete[] heap_;
+    heap_ = h;
+    size_ = n;
+  }
+  size_t size() const { return size_; }
+  const double* data() const { return heap_ ? heap_ : inline_; }
+  const double* begin() const { return data(); }
+  const double* end() const { return data() + size_; }
+  double operator[](size_t i) const { return data()[i]; }
+
+ private:
+  static constexpr size_t kInline = 8;
+  void take(GateMatrix& o) {
+    heap_ = o.heap_;
+    size_ = o.size_;
+    if (!heap_) std::copy(o.inline_, o.inline_ + size_, inline_);
+    o.heap_ = nullptr;
+    o.size_ = 0;
+  }
+  double* heap_ = nullptr;
+  size_t size_ = 0;
+  double inline_[kInline];
+};
+
 // A validated gate in normalised form.
 struct HostGate {
   int k = 0, c = 0;
   int t[kMaxK] = {0};
-  int ctl[kMaxQubits] = {0};
-  std::vector<double> m;   // 2^k x 2^k complex, interleaved, row-major
+  GateMatrix m;            // 2^k x 2^k complex, interleaved, row-major
   bool diagonal = false;   // off-diagonal entries are all exactly zero
   bool masked_phase = false;  // diagonal with every entry 1 except the last
   uint64_t tmask = 0, cmask = 0;
+  int8_t ctl[kMaxQubits] = {0};  // the c controls
   // Commutation footprint: "dense" qubits are targets of a non-diagonal
   // gate; "touch" is every qubit the gate involves.  Two gates commute when
   // neither's dense set meets the other's touch set.
@@ -41,6 +89,9 @@ struct Pass {
   };
   std::vector<Seg> segs;
   bool steer = false;           // order segments for ownership (see above)
+  // steer: the owner of each gate (by position in `gates`, -1: none) and the
+  // positions of the gates either side could own, as the plan chose them
+  std::vector<int> owner, shared;
   // fused
   int32_t fk = 0;
   int32_t fq[8] = {0};
