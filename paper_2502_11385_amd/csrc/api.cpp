@@ -30,13 +30,20 @@ struct qsv_state_s {
   hipStream_t stream = nullptr;
   int device = 0;
   bool failed = false;
-  // program buffer (device) and its pinned host staging copy
+  // program buffer (device) and its pinned host staging copies
   char* prog_dev = nullptr;
   size_t prog_cap = 0;
-  char* prog_host = nullptr;
-  size_t host_cap = 0;
-  hipEvent_t upload_done = nullptr;
-  bool upload_pending = false;
+  // two of them, taken in turn: a call fills one while the device may still
+  // read the other; `done` follows the call's last kernel
+  struct Staging {
+    char* host = nullptr;
+    size_t cap = 0;
+    hipEvent_t done = nullptr;
+    bool pending = false;
+  };
+  Staging stage[2];
+  int stage_i = 0;
+  bool stage_open = false;  // filled by the call under way
   // second state-sized buffer for out-of-place relabelling (on demand)
   void* spare = nullptr;
   // reduction scratch
@@ -123,17 +130,18 @@ qsv_status ensure_scratch(qsv_state s, size_t bytes) {
 }
 
 // Copy `bytes` of host data into the state's device program buffer, in
-// stream order (kernels already enqueued keep reading the previous
+// stream order; the caller holds an UploadEnd (kernels already enqueued keep reading the previous
 // program until the copy runs).
 qsv_status upload(qsv_state s, const void* data, size_t bytes) {
   if (bytes == 0) return QSV_OK;
-  if (bytes > s->prog_cap) {
+  const size_t room = (bytes + 15) & ~size_t(15);  // copied in 16-byte words
+  if (room > s->prog_cap) {
     const size_t old = s->prog_cap;
     QSV_HIP(s, hipStreamSynchronize(s->stream));
     if (s->prog_dev) QSV_HIP(s, hipFree(s->prog_dev));
     s->prog_dev = nullptr;
     s->prog_cap = 0;
-    size_t cap = std::max(bytes, std::max(size_t(1) << 16, 2 * old));
+    size_t cap = std::max(room, std::max(size_t(1) << 16, 2 * old));
     hipError_t e = dev_malloc(reinterpret_cast<void**>(&s->prog_dev), cap);
     if (e != hipSuccess) {
       s->prog_dev = nullptr;
@@ -142,30 +150,53 @@ qsv_status upload(qsv_state s, const void* data, size_t bytes) {
     }
     s->prog_cap = cap;
   }
-  if (s->upload_pending) {
-    QSV_HIP(s, hipEventSynchronize(s->upload_done));
-    s->upload_pending = false;
+  qsv_state_s::Staging& g = s->stage[s->stage_i];
+  if (g.pending) {
+    QSV_HIP(s, hipEventSynchronize(g.done));
+    g.pending = false;
   }
-  if (bytes > s->host_cap) {
-    if (s->prog_host) QSV_HIP(s, hipHostFree(s->prog_host));
-    s->prog_host = nullptr;
-    s->host_cap = 0;
-    size_t cap = std::max(bytes, size_t(1) << 16);
-    hipError_t e = hipHostMalloc(&s->prog_host, cap, hipHostMallocDefault);
+  if (room > g.cap) {
+    if (g.host) QSV_HIP(s, hipHostFree(g.host));
+    g.host = nullptr;
+    g.cap = 0;
+    size_t cap = std::max(room, size_t(1) << 16);
+    hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&g.host), cap,
+                                 hipHostMallocDefault);
     if (e != hipSuccess) {
-      s->prog_host = nullptr;
+      g.host = nullptr;
       (void)hipGetLastError();
       return fail(QSV_ERR_OUT_OF_MEMORY, "pinned staging allocation failed");
     }
-    s->host_cap = cap;
+    g.cap = cap;
   }
-  std::memcpy(s->prog_host, data, bytes);
-  QSV_HIP(s, hipMemcpyAsync(s->prog_dev, s->prog_host, bytes,
-                            hipMemcpyHostToDevice, s->stream));
-  QSV_HIP(s, hipEventRecord(s->upload_done, s->stream));
-  s->upload_pending = true;
+  std::memcpy(g.host, data, bytes);
+  s->stage_open = true;
+  QSV_HIP(s, launch_upload(g.host, s->prog_dev, bytes, s->stream));
   return QSV_OK;
 }
+
+// Ends a call that may have uploaded: records the staging buffer's event
+// after the call's kernels (not between the upload and the kernels that read
+// it) and turns to the other buffer.
+class UploadEnd {
+ public:
+  explicit UploadEnd(qsv_state s) : s_(s) {}
+  ~UploadEnd() {
+    if (!s_->stage_open) return;
+    s_->stage_open = false;
+    qsv_state_s::Staging& g = s_->stage[s_->stage_i];
+    if (hipEventRecord(g.done, s_->stream) == hipSuccess) {
+      g.pending = true;
+      s_->stage_i ^= 1;
+    } else {
+      (void)hipGetLastError();
+      s_->failed = true;
+    }
+  }
+
+ private:
+  qsv_state s_;
+};
 
 qsv_status parse_circuit(const qsv_circuit* circ, int n,
                          std::vector<HostGate>* out) {
@@ -271,9 +302,12 @@ qsv_status qsv_alloc(int32_t n, int32_t prec, void* stream, qsv_state* out) {
   s->owned = true;
   s->stream = static_cast<hipStream_t>(stream);
   s->device = dev;
-  e = hipEventCreateWithFlags(&s->upload_done, hipEventDisableTiming);
+  for (auto& g : s->stage)
+    if (e == hipSuccess)
+      e = hipEventCreateWithFlags(&g.done, hipEventDisableTiming);
   if (e != hipSuccess) {
     (void)hipFree(p);
+    if (s->stage[0].done) (void)hipEventDestroy(s->stage[0].done);
     delete s;
     return device_fail(nullptr, e, "hipEventCreate");
   }
@@ -305,8 +339,11 @@ qsv_status qsv_wrap(int32_t n, int32_t prec, void* ptr, size_t bytes,
   s->owned = false;
   s->stream = static_cast<hipStream_t>(stream);
   s->device = dev;
-  e = hipEventCreateWithFlags(&s->upload_done, hipEventDisableTiming);
+  for (auto& g : s->stage)
+    if (e == hipSuccess)
+      e = hipEventCreateWithFlags(&g.done, hipEventDisableTiming);
   if (e != hipSuccess) {
+    if (s->stage[0].done) (void)hipEventDestroy(s->stage[0].done);
     delete s;
     return device_fail(nullptr, e, "hipEventCreate");
   }
@@ -322,8 +359,10 @@ qsv_status qsv_free(qsv_state s) {
   if (s->prog_dev) (void)hipFree(s->prog_dev);
   if (s->scratch) (void)hipFree(s->scratch);
   if (s->spare) (void)hipFree(s->spare);
-  if (s->prog_host) (void)hipHostFree(s->prog_host);
-  if (s->upload_done) (void)hipEventDestroy(s->upload_done);
+  for (auto& g : s->stage) {
+    if (g.host) (void)hipHostFree(g.host);
+    if (g.done) (void)hipEventDestroy(g.done);
+  }
   for (hipEvent_t e2 : s->evs) (void)hipEventDestroy(e2);
   delete s;
   if (e != hipSuccess) return device_fail(nullptr, e, "hipStreamSynchronize");
@@ -407,6 +446,7 @@ qsv_status qsv_apply_gate(qsv_state s, const int32_t* targets, int32_t k,
   std::string err = make_gate(s->n, k, c, qs.data(), matrix, &g);
   if (!err.empty()) return fail(QSV_ERR_INVALID_ARG, err);
   if ((st = select_device(s)) != QSV_OK) return st;
+  UploadEnd end(s);
   if (g.diagonal) {
     QSV_HIP(s, launch_diag(s->prec, s->amp, s->n, g, s->stream));
   } else if (block_gate(g)) {
@@ -710,6 +750,7 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
   const auto t1 = std::chrono::steady_clock::now();
 
   if ((st = select_device(s)) != QSV_OK) return st;
+  UploadEnd end(s);
   if ((st = upload(s, buf.data(), buf.size())) != QSV_OK) return st;
   char* dev = s->prog_dev;
   const TilePass* d_tp = reinterpret_cast<const TilePass*>(dev + o_tp);

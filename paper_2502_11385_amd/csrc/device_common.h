@@ -192,6 +192,10 @@ struct PermArgs {
 };
 hipError_t launch_permute(int prec, const void* src, void* dst, int n,
                           const PermArgs& p, hipStream_t stream);
+// Copy pinned host memory to the device in stream order, both ends 16-byte
+// aligned and padded to 16 bytes.
+hipError_t launch_upload(const void* host, void* dev, uint64_t bytes,
+                         hipStream_t stream);
 // Device copy of a multiple of 16 bytes, both ends 16-byte aligned.
 hipError_t launch_copy(const void* src, void* dst, uint64_t bytes,
                        hipStream_t stream);

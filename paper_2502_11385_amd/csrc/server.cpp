@@ -288,8 +288,7 @@ void launch_batched(qsv_server s, Group* g, int prec) {
     return;
   }
   std::memcpy(hstage, img.data(), img.size());
-  hipError_t e = hipMemcpyAsync(prog, hstage, img.size(),
-                                hipMemcpyHostToDevice, st);
+  hipError_t e = launch_upload(hstage, prog, img.size(), st);
   if (e == hipSuccess)
     e = launch_batch(prec, b == 16, RB,
                      reinterpret_cast<const BatchCircuit*>(prog + o_c),
