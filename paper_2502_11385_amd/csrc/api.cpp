@@ -132,16 +132,19 @@ qsv_status ensure_scratch(qsv_state s, size_t bytes) {
 // Copy `bytes` of host data into the state's device program buffer, in
 // stream order; the caller holds an UploadEnd (kernels already enqueued keep reading the previous
 // program until the copy runs).
-qsv_status upload(qsv_state s, const void* data, size_t bytes) {
+qsv_status upload(qsv_state s, const void* data, size_t bytes,
+                  size_t at_least = 0) {
   if (bytes == 0) return QSV_OK;
-  const size_t room = (bytes + 15) & ~size_t(15);  // copied in 16-byte words
+  // copied in 16-byte words; a buffer that has to grow, or is new, grows to
+  // at_least
+  const size_t room = (bytes + 15) & ~size_t(15);
   if (room > s->prog_cap) {
     const size_t old = s->prog_cap;
     QSV_HIP(s, hipStreamSynchronize(s->stream));
     if (s->prog_dev) QSV_HIP(s, hipFree(s->prog_dev));
     s->prog_dev = nullptr;
     s->prog_cap = 0;
-    size_t cap = std::max(room, std::max(size_t(1) << 16, 2 * old));
+    size_t cap = std::max({room, at_least, size_t(1) << 16, 2 * old});
     hipError_t e = dev_malloc(reinterpret_cast<void**>(&s->prog_dev), cap);
     if (e != hipSuccess) {
       s->prog_dev = nullptr;
@@ -159,7 +162,7 @@ qsv_status upload(qsv_state s, const void* data, size_t bytes) {
     if (g.host) QSV_HIP(s, hipHostFree(g.host));
     g.host = nullptr;
     g.cap = 0;
-    size_t cap = std::max(room, size_t(1) << 16);
+    size_t cap = std::max({room, at_least, size_t(1) << 16});
     hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&g.host), cap,
                                  hipHostMallocDefault);
     if (e != hipSuccess) {
@@ -477,10 +480,10 @@ qsv_status qsv_apply_gate(qsv_state s, const int32_t* targets, int32_t k,
   return QSV_OK;
 }
 
-static qsv_status plan_for(const qsv_circuit* circ, int n, int prec,
-                           const qsv_fuse_opts* opts,
-                           std::vector<HostGate>* G, PlanOptions* po,
-                           Plan* plan) {
+// Parse and validate a circuit and its options.
+static qsv_status parse_for(const qsv_circuit* circ, int n, int prec,
+                            const qsv_fuse_opts* opts,
+                            std::vector<HostGate>* G, PlanOptions* po) {
   qsv_status st = parse_circuit(circ, n, G);
   if (st != QSV_OK) return st;
   int v[5] = {0, 0, 0, 0, 0};
@@ -495,6 +498,15 @@ static qsv_status plan_for(const qsv_circuit* circ, int n, int prec,
   if (!err.empty())
     return fail(v[0] < 0 || v[0] > 3 ? QSV_ERR_UNSUPPORTED : QSV_ERR_INVALID_ARG,
                 err);
+  return QSV_OK;
+}
+
+static qsv_status plan_for(const qsv_circuit* circ, int n, int prec,
+                           const qsv_fuse_opts* opts,
+                           std::vector<HostGate>* G, PlanOptions* po,
+                           Plan* plan) {
+  const qsv_status st = parse_for(circ, n, prec, opts, G, po);
+  if (st != QSV_OK) return st;
   make_plan(*G, n, bytes_of(prec), *po, plan);
   return QSV_OK;
 }
@@ -539,6 +551,95 @@ static qsv_status check_outputs(qsv_state s, const qsv_outputs* o) {
   return QSV_OK;
 }
 
+// ---- launching passes while later ones are being planned
+//
+// Planning a circuit takes the host longer than running its passes takes the
+// device up to about 20 qubits, so the device would wait for the whole plan
+// and the caller for both in turn.  Each time the stream has run dry, the
+// passes planned so far, all but the newest (it may turn out to be the last,
+// which folds the outputs), are uploaded and launched.  While the stream
+// still has work, from this circuit or an earlier call, nothing is split off,
+// so that a caller who queues circuits pays for one upload each.
+// 1180 gates on 20 qubits: 0.81 -> 0.67 ms a call.
+
+// Bytes that hold the program of any plan of these gates, all tileable: an
+// op slot per gate, a phase block's record and terms, a segment and a pass
+// each at most, and the parts' alignment.
+static size_t program_bound(const std::vector<HostGate>& G) {
+  return G.size() * 1024 + 8192;
+}
+constexpr size_t kEarlyProgram = size_t(2) << 20;
+// A part of its own costs about 8 us on the device (an upload and its
+// latency), as much as planning this many more gates takes the host.
+constexpr size_t kEarlyGates = 64;
+constexpr size_t kEarlyScratch = size_t(16) << 20;
+
+// Scratch that any plan of the options needs for these outputs.
+static size_t outputs_bound(qsv_state s, const PlanOptions& po,
+                            const qsv_outputs* o) {
+  const int n = s->n, L = std::min(po.tile_log2, n);
+  const int kb = std::max(0, L - po.reg_log2);
+  const size_t tiles = size_t(1) << (n - L);
+  size_t b = 8 * 256;
+  if (o->marg_m)
+    b += (tiles << std::min(o->marg_m, kb)) * sizeof(double) +
+         (sizeof(double) << o->marg_m) + marginal_scratch_bytes(n, o->marg_m);
+  if (o->n_shots)
+    b += sample_scratch_bytes(n, 0) + o->n_shots * sizeof(uint64_t) +
+         (tiles << kb) * sizeof(double);
+  if (o->probs_dev) b += norm_scratch_bytes(n);
+  return b;
+}
+
+// Only where no buffer can need to grow once a pass has been launched, so
+// that a failed allocation still leaves the state as it was.
+static bool may_launch_early(qsv_state s, const std::vector<HostGate>& G,
+                             const PlanOptions& po, const qsv_outputs* o) {
+  // (below the width where the planner searches, planning is quick)
+  const bool tiled = (po.strategy == 0 || po.strategy == 2) && po.steer &&
+                     s->n >= po.reg_log2 + 2;
+  const size_t need = program_bound(G);
+  if (!tiled || s->profiling || G.empty() || need > kEarlyProgram ||
+      s->prog_cap < need || s->stage[0].cap < need || s->stage[1].cap < need)
+    return false;
+  if (o && s->scratch_cap < outputs_bound(s, po, o)) return false;
+  if (!all_tileable(G)) return false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s->stream, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return cs == hipStreamCaptureStatusNone;
+}
+
+static bool stream_idle(qsv_state s) {
+  if (hipStreamQuery(s->stream) == hipSuccess) return true;
+  (void)hipGetLastError();  // not ready
+  return false;
+}
+
+// Upload emitted tile passes and launch them.
+static qsv_status launch_tiles(qsv_state s, const PlanOptions& po,
+                               const std::vector<TilePass>& tpasses,
+                               const std::vector<TileSeg>& tsegs,
+                               const std::vector<TileOp>& tops) {
+  std::vector<char> buf;
+  const size_t o_tp = put(buf, tpasses.data(), tpasses.size());
+  const size_t o_ts = put(buf, tsegs.data(), tsegs.size());
+  const size_t o_to = put(buf, tops.data(), tops.size());
+  buf.resize(buf.size() + sizeof(TileOp));  // read one op ahead
+  UploadEnd end(s);
+  const qsv_status st = upload(s, buf.data(), buf.size());
+  if (st != QSV_OK) return st;
+  for (size_t i = 0; i < tpasses.size(); ++i)
+    QSV_HIP(s, launch_tile(s->prec, po.reg_log2, s->amp, s->n, tpasses[i],
+                           reinterpret_cast<const TilePass*>(s->prog_dev + o_tp) + i,
+                           reinterpret_cast<const TileSeg*>(s->prog_dev + o_ts),
+                           reinterpret_cast<const TileOp*>(s->prog_dev + o_to),
+                           s->stream));
+  return QSV_OK;
+}
+
 static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
                                    const qsv_fuse_opts* opts,
                                    const qsv_outputs* outs);
@@ -565,15 +666,56 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
   std::vector<HostGate> G;
   PlanOptions po;
   Plan plan;
-  if ((st = plan_for(circ, s->n, s->prec, opts, &G, &po, &plan)) != QSV_OK)
+  if ((st = parse_for(circ, s->n, s->prec, opts, &G, &po)) != QSV_OK)
     return st;
   const int n = s->n;
-
-  // ---- serialise the program
   std::vector<TilePass> tpasses;
   std::vector<TileSeg> tsegs;
   std::vector<TileOp> tops;
   TileEmitStats est;
+  auto emit = [&](const Pass& p) -> qsv_status {
+    std::string err = emit_tile_pass(p, G, po.reg_log2, &tpasses, &tsegs,
+                                     &tops, &est);
+    if (!err.empty()) return fail(QSV_ERR_DEVICE, err);
+    set_lds_offsets(tile_lds_map(s->prec, po.reg_log2), po.reg_log2,
+                    &tpasses.back(), tsegs.data());
+    return QSV_OK;
+  };
+  // Passes already launched; a call that ends with only those has applied
+  // part of the circuit, and leaves the state failed.
+  struct Early {
+    qsv_state s;
+    size_t passes = 0;
+    bool whole = false;
+    ~Early() {
+      if (passes && !whole) s->failed = true;
+    }
+  } early{s};
+  size_t& done = early.passes;
+  if (may_launch_early(s, G, po, outs)) {
+    // launch every pass but the newest whenever the stream has run dry
+    if ((st = select_device(s)) != QSV_OK) return st;
+    size_t left = G.size();
+    make_plan(G, n, s->b, po, &plan, [&] {
+      left -= plan.passes.back().gates.size();
+      if (st != QSV_OK || left < kEarlyGates ||
+          plan.passes.size() < done + 2 || !stream_idle(s))
+        return;
+      const size_t upto = plan.passes.size() - 1;
+      for (size_t pi = done; pi < upto && st == QSV_OK; ++pi)
+        st = emit(plan.passes[pi]);
+      if (st == QSV_OK) st = launch_tiles(s, po, tpasses, tsegs, tops);
+      tpasses.clear();
+      tsegs.clear();
+      tops.clear();
+      done = upto;
+    });
+    if (st != QSV_OK) return st;
+  } else {
+    make_plan(G, n, s->b, po, &plan);
+  }
+
+  // ---- serialise the program (of the passes not yet launched)
   std::vector<FusedBlock> fblocks;
   std::vector<FusedGate> fgates;
   std::vector<double> mats;             // gate matrices (FP64)
@@ -583,12 +725,10 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
   std::vector<float> plain32;  // their FP32 matrices, after the fused ones
   size_t u64_total = 0, u32_total = 0;  // fused outputs (in doubles/floats)
 
-  for (size_t pi = 0; pi < plan.passes.size(); ++pi) {
+  for (size_t pi = done; pi < plan.passes.size(); ++pi) {
     const Pass& p = plan.passes[pi];
     if (p.kind == kPassTile) {
-      std::string err = emit_tile_pass(p, G, po.reg_log2, &tpasses, &tsegs,
-                                       &tops, &est);
-      if (!err.empty()) return fail(QSV_ERR_DEVICE, err);
+      if ((st = emit(p)) != QSV_OK) return st;
     } else if (p.kind == kPassPlain) {
       const HostGate& g = G[p.gates[0]];
       if (block_gate(g)) {
@@ -636,9 +776,6 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
       fblocks.push_back(fb);
     }
   }
-  for (TilePass& tp : tpasses)
-    set_lds_offsets(tile_lds_map(s->prec, po.reg_log2), po.reg_log2, &tp,
-                    tsegs.data());
   // Outputs: which ones the last tile pass folds (the last pass of the plan
   // must be a tile pass; a key may span at most L - reg_log2 tile bits, so
   // that each thread's registers fall in one group), and the scratch
@@ -690,7 +827,11 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
       other = std::max(other, marginal_scratch_bytes(n, outs->marg_m));
     op.total = off + al(other);
     if ((st = select_device(s)) != QSV_OK) return st;
-    if ((st = ensure_scratch(s, op.total)) != QSV_OK) return st;
+    // (room for any plan's outputs where that is little: may_launch_early)
+    const size_t any = outputs_bound(s, po, outs);
+    if ((st = ensure_scratch(s, any <= kEarlyScratch ? std::max(any, op.total)
+                                                     : op.total)) != QSV_OK)
+      return st;
   }
 
   // Fused outputs follow the gate matrices in the FP64 region.
@@ -751,7 +892,10 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
 
   if ((st = select_device(s)) != QSV_OK) return st;
   UploadEnd end(s);
-  if ((st = upload(s, buf.data(), buf.size())) != QSV_OK) return st;
+  const size_t bound = program_bound(G);
+  if ((st = upload(s, buf.data(), buf.size(),
+                   bound <= kEarlyProgram ? bound : 0)) != QSV_OK)
+    return st;
   char* dev = s->prog_dev;
   const TilePass* d_tp = reinterpret_cast<const TilePass*>(dev + o_tp);
   const TileSeg* d_ts = reinterpret_cast<const TileSeg*>(dev + o_ts);
@@ -779,7 +923,7 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
     s->ev_used = 0;
   }
   size_t ti = 0, fi = 0;
-  for (size_t pi = 0; pi < plan.passes.size(); ++pi) {
+  for (size_t pi = done; pi < plan.passes.size(); ++pi) {
     const Pass& p = plan.passes[pi];
     if (s->profiling) {
       s->ev_kinds[pi] = p.kind;
@@ -816,6 +960,7 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
     if (s->profiling)
       QSV_HIP(s, hipEventRecord(s->evs[2 * pi + 1], s->stream));
   }
+  early.whole = true;
   s->stats[0] = plan.passes.size();
   s->stats[1] = G.size();
   s->stats[2] = plan.alg_bytes;

@@ -568,8 +568,15 @@ static void add_plain(const std::vector<HostGate>& G, int gi, int n, int b,
   plan->passes.push_back(std::move(p));
 }
 
+bool all_tileable(const std::vector<HostGate>& G) {
+  for (const HostGate& g : G)
+    if (!tileable(g)) return false;
+  return true;
+}
+
 static void plan_tiled(const std::vector<HostGate>& G, int n, int b,
-                       const PlanOptions& o, Plan* plan) {
+                       const PlanOptions& o, Plan* plan,
+                       const std::function<void()>& on_pass) {
   const int L = std::min(o.tile_log2, n);
   const int RB = o.reg_log2;
   const int m = std::min(o.low_qubits, L);
@@ -817,6 +824,7 @@ static void plan_tiled(const std::vector<HostGate>& G, int n, int b,
     plan->tile_passes++;
     plan->segments += int(p.segs.size());
     plan->passes.push_back(std::move(p));
+    if (on_pass) on_pass();
   }
 }
 
@@ -1553,7 +1561,8 @@ void set_lds_offsets(LdsMap map, int RB, TilePass* pass, TileSeg* segs) {
 }
 
 void make_plan(const std::vector<HostGate>& G, int n, int b,
-               const PlanOptions& o, Plan* plan) {
+               const PlanOptions& o, Plan* plan,
+               const std::function<void()>& on_pass) {
   *plan = Plan();
   int strategy = o.strategy;
   if (strategy == 0) strategy = (n >= o.reg_log2 + 2) ? 2 : 1;
@@ -1561,7 +1570,7 @@ void make_plan(const std::vector<HostGate>& G, int n, int b,
   if (strategy == 1) {
     for (size_t i = 0; i < G.size(); ++i) add_plain(G, int(i), n, b, plan);
   } else if (strategy == 2) {
-    plan_tiled(G, n, b, o, plan);
+    plan_tiled(G, n, b, o, plan, on_pass);
   } else {
     plan_fused(G, n, b, o, plan);
   }

@@ -3,6 +3,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -124,9 +125,14 @@ std::string resolve_options(int n, int bytes_per_amp, const int* in5,
 std::string make_gate(int n, int k, int c, const int32_t* qubits,
                       const double* matrix, HostGate* out);
 
-// Build the pass list for gates on n qubits.
+// Build the pass list for gates on n qubits.  `on_pass`, where given, hears
+// of each tile pass added to plan->passes.
 void make_plan(const std::vector<HostGate>& gates, int n, int bytes_per_amp,
-               const PlanOptions& opt, Plan* plan);
+               const PlanOptions& opt, Plan* plan,
+               const std::function<void()>& on_pass = nullptr);
+
+// Whether every gate can run in tile passes (no plain passes in the plan).
+bool all_tileable(const std::vector<HostGate>& gates);
 
 // Counts of what emit_tile_pass produced (accumulated over calls).
 struct TileEmitStats {
