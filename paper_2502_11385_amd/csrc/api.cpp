@@ -33,15 +33,20 @@ struct qsv_state_s {
   // program buffer (device) and its pinned host staging copies
   char* prog_dev = nullptr;
   size_t prog_cap = 0;
-  // two of them, taken in turn: a call fills one while the device may still
-  // read the other; `done` follows the call's last kernel
+  // taken in turn, four for programs of up to kStageSmall bytes (parts of one
+  // allocation) and the first two for larger ones: a call fills one while the
+  // device may still read the others; `done` follows the call's last kernel.
+  // With two, a queue of calls of about 30 us waited for the host's waking up
+  // from each event (9 qubits, 6 layers: 33.5 us a call, and 51.7 alone).
   struct Staging {
     char* host = nullptr;
     size_t cap = 0;
     hipEvent_t done = nullptr;
     bool pending = false;
+    bool own = false;  // an allocation of its own
   };
-  Staging stage[2];
+  char* stage_block = nullptr;
+  Staging stage[4];
   int stage_i = 0;
   bool stage_open = false;  // filled by the call under way
   // second state-sized buffer for out-of-place relabelling (on demand)
@@ -129,6 +134,17 @@ qsv_status ensure_scratch(qsv_state s, size_t bytes) {
   return QSV_OK;
 }
 
+constexpr size_t kStageSmall = size_t(1) << 16;
+
+bool pinned(char** p, size_t bytes) {
+  if (hipHostMalloc(reinterpret_cast<void**>(p), bytes,
+                    hipHostMallocDefault) == hipSuccess)
+    return true;
+  *p = nullptr;
+  (void)hipGetLastError();
+  return false;
+}
+
 // Copy `bytes` of host data into the state's device program buffer, in
 // stream order; the caller holds an UploadEnd (kernels already enqueued keep reading the previous
 // program until the copy runs).
@@ -153,23 +169,29 @@ qsv_status upload(qsv_state s, const void* data, size_t bytes,
     }
     s->prog_cap = cap;
   }
+  if (!s->stage_block) {
+    if (!pinned(&s->stage_block, 4 * kStageSmall))
+      return fail(QSV_ERR_OUT_OF_MEMORY, "pinned staging allocation failed");
+    for (int i = 0; i < 4; ++i) {
+      s->stage[i].host = s->stage_block + i * kStageSmall;
+      s->stage[i].cap = kStageSmall;
+    }
+  }
+  s->stage_i &= room <= kStageSmall ? 3 : 1;
   qsv_state_s::Staging& g = s->stage[s->stage_i];
   if (g.pending) {
     QSV_HIP(s, hipEventSynchronize(g.done));
     g.pending = false;
   }
   if (room > g.cap) {
-    if (g.host) QSV_HIP(s, hipHostFree(g.host));
+    if (g.own) QSV_HIP(s, hipHostFree(g.host));
+    g.own = false;
     g.host = nullptr;
     g.cap = 0;
-    size_t cap = std::max({room, at_least, size_t(1) << 16});
-    hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&g.host), cap,
-                                 hipHostMallocDefault);
-    if (e != hipSuccess) {
-      g.host = nullptr;
-      (void)hipGetLastError();
+    const size_t cap = std::max(room, at_least);
+    if (!pinned(&g.host, cap))
       return fail(QSV_ERR_OUT_OF_MEMORY, "pinned staging allocation failed");
-    }
+    g.own = true;
     g.cap = cap;
   }
   std::memcpy(g.host, data, bytes);
@@ -190,7 +212,7 @@ class UploadEnd {
     qsv_state_s::Staging& g = s_->stage[s_->stage_i];
     if (hipEventRecord(g.done, s_->stream) == hipSuccess) {
       g.pending = true;
-      s_->stage_i ^= 1;
+      s_->stage_i = (s_->stage_i + 1) & 3;
     } else {
       (void)hipGetLastError();
       s_->failed = true;
@@ -310,7 +332,8 @@ qsv_status qsv_alloc(int32_t n, int32_t prec, void* stream, qsv_state* out) {
       e = hipEventCreateWithFlags(&g.done, hipEventDisableTiming);
   if (e != hipSuccess) {
     (void)hipFree(p);
-    if (s->stage[0].done) (void)hipEventDestroy(s->stage[0].done);
+    for (auto& g : s->stage)
+      if (g.done) (void)hipEventDestroy(g.done);
     delete s;
     return device_fail(nullptr, e, "hipEventCreate");
   }
@@ -346,7 +369,8 @@ qsv_status qsv_wrap(int32_t n, int32_t prec, void* ptr, size_t bytes,
     if (e == hipSuccess)
       e = hipEventCreateWithFlags(&g.done, hipEventDisableTiming);
   if (e != hipSuccess) {
-    if (s->stage[0].done) (void)hipEventDestroy(s->stage[0].done);
+    for (auto& g : s->stage)
+      if (g.done) (void)hipEventDestroy(g.done);
     delete s;
     return device_fail(nullptr, e, "hipEventCreate");
   }
@@ -363,9 +387,10 @@ qsv_status qsv_free(qsv_state s) {
   if (s->scratch) (void)hipFree(s->scratch);
   if (s->spare) (void)hipFree(s->spare);
   for (auto& g : s->stage) {
-    if (g.host) (void)hipHostFree(g.host);
+    if (g.own) (void)hipHostFree(g.host);
     if (g.done) (void)hipEventDestroy(g.done);
   }
+  if (s->stage_block) (void)hipHostFree(s->stage_block);
   for (hipEvent_t e2 : s->evs) (void)hipEventDestroy(e2);
   delete s;
   if (e != hipSuccess) return device_fail(nullptr, e, "hipStreamSynchronize");
