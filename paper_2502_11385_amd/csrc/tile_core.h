@@ -18,8 +18,8 @@ namespace qsv {
 // in their registers through every switch arm of an op: compiled code
 // computed the new values into fresh registers and copied all sixteen
 // amplitudes back at the arms' join (32 moves per op, a fifth of its
-// instructions).  SM: the matrix is uniform, in scalar registers (each
-// instruction reads one of them); else it is in vector registers.
+// instructions).  The FP64 form's matrix is in scalar registers where it is
+// uniform (SM; each instruction reads one of them, at the same rate).
 #define QSV_PAIR_F32(MC)                                                      \
   asm volatile(                                                               \
       "v_mul_f32 %[t0], -%[m1], %[b]\n\t"                                     \
@@ -67,242 +67,217 @@ namespace qsv {
 #define QSV_SREG(x) "s"(x)
 #define QSV_VREG(x) "v"(x)
 
-template <bool SM, typename C, typename T>
-__device__ __forceinline__ void pair2x2(C& x0, C& x1, T m0r, T m0i, T m1r,
-                                        T m1i, T m2r, T m2i, T m3r, T m3i) {
-  T t0, t1, t2, t3;
+// A 2x2 matrix in vector registers, and an FP64 one in scalar registers
+// (m as the pair update's m0r..m3i).  Every FP32 multiply and FMA, in the
+// two- and the three-operand encoding, with or without a negation, issues at
+// twice the rate of the same instruction reading a scalar register on this
+// chip (1.0 to 1.2 ns against 1.8 to 1.9 ns a wave with six waves a SIMD),
+// so complex64 ops copy their uniform matrix to vector registers once, four
+// 64-bit moves.  FP64 instructions take 1.8 to 1.9 ns either way.
+template <typename T>
+struct VecMat {
+  T m[8];
+};
+struct ScalarMat64 {
+  double m[8];
+};
+
+#define QSV_PAIR_ARGS(v)                                                      \
+  const auto m0r = v.m[0], m0i = v.m[1], m1r = v.m[2], m1i = v.m[3],          \
+             m2r = v.m[4], m2i = v.m[5], m3r = v.m[6], m3i = v.m[7];          \
+  decltype(x0.x) t0, t1, t2, t3
+template <typename C>
+__device__ __forceinline__ void pair2x2(C& x0, C& x1, const VecMat<float>& v) {
+  QSV_PAIR_ARGS(v);
+  QSV_PAIR_F32(QSV_VREG);
+}
+template <typename C>
+__device__ __forceinline__ void pair2x2(C& x0, C& x1, const VecMat<double>& v) {
+  QSV_PAIR_ARGS(v);
+  QSV_PAIR_F64(QSV_VREG);
+}
+template <typename C>
+__device__ __forceinline__ void pair2x2(C& x0, C& x1, const ScalarMat64& v) {
+  QSV_PAIR_ARGS(v);
+  QSV_PAIR_F64(QSV_SREG);
+}
+
+// A matrix as an op's fields hold it: 64-bit words in scalar registers, two
+// FP32 entries (real part first) or one FP64 entry each.
+template <typename T>
+constexpr int kMatWords = sizeof(T);
+
+template <typename T>
+__device__ __forceinline__ T mat_entry(const uint64_t* q, int e) {
+  if constexpr (sizeof(T) == 4)
+    return __builtin_bit_cast(float, uint32_t(q[e >> 1] >> (32 * (e & 1))));
+  else
+    return __builtin_bit_cast(double, q[e]);
+}
+
+template <typename T>
+__device__ __forceinline__ auto uniform_mat(const uint64_t* q) {
   if constexpr (sizeof(T) == 4) {
-    if constexpr (SM) QSV_PAIR_F32(QSV_SREG);
-    else QSV_PAIR_F32(QSV_VREG);
+    VecMat<float> v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      uint64_t d;
+      asm volatile("v_mov_b64 %0, %1" : "=v"(d) : "s"(q[e]));
+      v.m[2 * e] = __builtin_bit_cast(float, uint32_t(d));
+      v.m[2 * e + 1] = __builtin_bit_cast(float, uint32_t(d >> 32));
+    }
+    return v;
   } else {
-    if constexpr (SM) QSV_PAIR_F64(QSV_SREG);
-    else QSV_PAIR_F64(QSV_VREG);
+    ScalarMat64 v;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v.m[e] = mat_entry<double>(q, e);
+    return v;
   }
 }
 
-// A 2x2 FP32 matrix for the complex64 pair update, with the negated
-// imaginary part of each entry beside it.  Multiplies and two-operand FMAs
-// (VOP2 encoding) whose operands are all vector registers issue at twice
-// the rate of the same instructions reading a scalar register or carrying
-// a negation on this chip, so the cross terms take their factors from
-// vector registers: an op copies its uniform matrix there once (six moves,
-// four of them 64-bit) and each pair's twelve cross terms run at the
-// double rate.  The diagonal
-// entries' real parts (m[0], m[6]) feed only the four three-operand FMAs,
-// which run at the single rate either way; for a uniform matrix (SM) they
-// stay in scalar registers, which keeps the tile kernel at six waves per
-// SIMD.
-struct VMat32 {
-  float m[8];  // as pair2x2's m0r..m3i
-  float n[4];  // -m[1], -m[3], -m[5], -m[7]
-};
-
-// Two uniform FP32 values into a vector-register pair with one 64-bit move
-// (a move from scalar registers costs the same issue time for 64 bits as
-// for 32).
-__device__ __forceinline__ void vmov2(float lo, float hi, float* vlo,
-                                      float* vhi) {
-  const uint64_t s = uint64_t(__builtin_bit_cast(uint32_t, lo)) |
-                     (uint64_t(__builtin_bit_cast(uint32_t, hi)) << 32);
-  uint64_t d;
-  asm volatile("v_mov_b64 %0, %1" : "=v"(d) : "s"(s));
-  *vlo = __builtin_bit_cast(float, uint32_t(d));
-  *vhi = __builtin_bit_cast(float, uint32_t(d >> 32));
-}
-
-template <bool SM>
-__device__ __forceinline__ VMat32 vmat32(const float* m) {
-  VMat32 v;
-  if constexpr (SM) {
-    // uniform: m[2..5] and the four negations in 64-bit pairs, m[1] and
-    // m[7] alone; m[0] and m[6] stay scalar (six moves, not ten)
-    v.m[0] = m[0];
-    v.m[6] = m[6];
-    vmov2(m[2], m[3], &v.m[2], &v.m[3]);
-    vmov2(m[4], m[5], &v.m[4], &v.m[5]);
-    vmov2(-m[1], -m[3], &v.n[0], &v.n[1]);
-    vmov2(-m[5], -m[7], &v.n[2], &v.n[3]);
-    v.m[1] = m[1];
-    v.m[7] = m[7];
-    asm volatile("" : "+v"(v.m[1]), "+v"(v.m[7]));
+// The matrix of each thread: q1 where `sel`, else q0.  Both are uniform: q0
+// is moved to every lane, then q1 to the selected ones, one 64-bit move a
+// word each.  (A select takes at most one scalar operand, its mask, so
+// compiled code moved every entry of both matrices to vector registers and
+// then selected: six issues a word instead of two.)
+template <typename T>
+__device__ __forceinline__ VecMat<T> thread_mat(const uint64_t* q0,
+                                                const uint64_t* q1, bool sel) {
+  const uint64_t mask = __builtin_amdgcn_ballot_w64(sel);
+  VecMat<T> v;
+  uint64_t d[kMatWords<T>], all;
+  if constexpr (sizeof(T) == 4) {
+    asm volatile(
+        "s_mov_b64 %[all], exec\n\t"
+        "v_mov_b64 %[d0], %[a0]\n\t"
+        "v_mov_b64 %[d1], %[a1]\n\t"
+        "v_mov_b64 %[d2], %[a2]\n\t"
+        "v_mov_b64 %[d3], %[a3]\n\t"
+        "s_mov_b64 exec, %[mask]\n\t"
+        "v_mov_b64 %[d0], %[b0]\n\t"
+        "v_mov_b64 %[d1], %[b1]\n\t"
+        "v_mov_b64 %[d2], %[b2]\n\t"
+        "v_mov_b64 %[d3], %[b3]\n\t"
+        "s_mov_b64 exec, %[all]"
+        : [all] "=&s"(all), [d0] "=&v"(d[0]), [d1] "=&v"(d[1]),
+          [d2] "=&v"(d[2]), [d3] "=&v"(d[3])
+        : [mask] "s"(mask), [a0] "s"(q0[0]), [a1] "s"(q0[1]), [a2] "s"(q0[2]),
+          [a3] "s"(q0[3]), [b0] "s"(q1[0]), [b1] "s"(q1[1]), [b2] "s"(q1[2]),
+          [b3] "s"(q1[3]));
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      v.m[e] = __builtin_bit_cast(float, uint32_t(d[e >> 1] >> (32 * (e & 1))));
   } else {
+    asm volatile(
+        "s_mov_b64 %[all], exec\n\t"
+        "v_mov_b64 %[d0], %[a0]\n\t"
+        "v_mov_b64 %[d1], %[a1]\n\t"
+        "v_mov_b64 %[d2], %[a2]\n\t"
+        "v_mov_b64 %[d3], %[a3]\n\t"
+        "v_mov_b64 %[d4], %[a4]\n\t"
+        "v_mov_b64 %[d5], %[a5]\n\t"
+        "v_mov_b64 %[d6], %[a6]\n\t"
+        "v_mov_b64 %[d7], %[a7]\n\t"
+        "s_mov_b64 exec, %[mask]\n\t"
+        "v_mov_b64 %[d0], %[b0]\n\t"
+        "v_mov_b64 %[d1], %[b1]\n\t"
+        "v_mov_b64 %[d2], %[b2]\n\t"
+        "v_mov_b64 %[d3], %[b3]\n\t"
+        "v_mov_b64 %[d4], %[b4]\n\t"
+        "v_mov_b64 %[d5], %[b5]\n\t"
+        "v_mov_b64 %[d6], %[b6]\n\t"
+        "v_mov_b64 %[d7], %[b7]\n\t"
+        "s_mov_b64 exec, %[all]"
+        : [all] "=&s"(all), [d0] "=&v"(d[0]), [d1] "=&v"(d[1]),
+          [d2] "=&v"(d[2]), [d3] "=&v"(d[3]), [d4] "=&v"(d[4]),
+          [d5] "=&v"(d[5]), [d6] "=&v"(d[6]), [d7] "=&v"(d[7])
+        : [mask] "s"(mask), [a0] "s"(q0[0]), [a1] "s"(q0[1]), [a2] "s"(q0[2]),
+          [a3] "s"(q0[3]), [a4] "s"(q0[4]), [a5] "s"(q0[5]), [a6] "s"(q0[6]),
+          [a7] "s"(q0[7]), [b0] "s"(q1[0]), [b1] "s"(q1[1]), [b2] "s"(q1[2]),
+          [b3] "s"(q1[3]), [b4] "s"(q1[4]), [b5] "s"(q1[5]), [b6] "s"(q1[6]),
+          [b7] "s"(q1[7]));
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      v.m[e] = m[e];
-      asm volatile("" : "+v"(v.m[e]));
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      v.n[k] = -m[2 * k + 1];
-      asm volatile("" : "+v"(v.n[k]));
-    }
+    for (int e = 0; e < 8; ++e) v.m[e] = __builtin_bit_cast(double, d[e]);
   }
   return v;
 }
 
-// The pair update of pair2x2 with the cross-term factors in vector
-// registers: the same products and fused sums in the same order (a negated
-// factor gives the exactly negated product), so the results are bitwise
-// those of pair2x2; the twelve cross terms are VOP2 instructions, the four
-// own terms stay three-operand FMAs that write the amplitude registers in
-// place.
-#define QSV_PAIR_F32V(DC)                                                     \
-  asm volatile(                                                               \
-      "v_mul_f32_e32 %[t0], %[n0], %[b]\n\t"                                  \
-      "v_mul_f32_e32 %[t1], %[m1], %[a]\n\t"                                  \
-      "v_mul_f32_e32 %[t2], %[m4], %[a]\n\t"                                  \
-      "v_mul_f32_e32 %[t3], %[m4], %[b]\n\t"                                  \
-      "v_fmac_f32_e32 %[t0], %[m2], %[c]\n\t"                                 \
-      "v_fmac_f32_e32 %[t1], %[m2], %[d]\n\t"                                 \
-      "v_fmac_f32_e32 %[t2], %[n2], %[b]\n\t"                                 \
-      "v_fmac_f32_e32 %[t3], %[m5], %[a]\n\t"                                 \
-      "v_fmac_f32_e32 %[t0], %[n1], %[d]\n\t"                                 \
-      "v_fmac_f32_e32 %[t1], %[m3], %[c]\n\t"                                 \
-      "v_fmac_f32_e32 %[t2], %[n3], %[d]\n\t"                                 \
-      "v_fmac_f32_e32 %[t3], %[m7], %[c]\n\t"                                 \
-      "v_fma_f32 %[a], %[m0], %[a], %[t0]\n\t"                                \
-      "v_fma_f32 %[b], %[m0], %[b], %[t1]\n\t"                                \
-      "v_fma_f32 %[c], %[m6], %[c], %[t2]\n\t"                                \
-      "v_fma_f32 %[d], %[m6], %[d], %[t3]"                                     \
-      : [a] "+v"(x0.x), [b] "+v"(x0.y), [c] "+v"(x1.x), [d] "+v"(x1.y),     \
-        [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2), [t3] "=&v"(t3)        \
-      : [m0] DC(v.m[0]), [m1] "v"(v.m[1]), [m2] "v"(v.m[2]),                  \
-        [m3] "v"(v.m[3]), [m4] "v"(v.m[4]), [m5] "v"(v.m[5]),                 \
-        [m6] DC(v.m[6]), [m7] "v"(v.m[7]), [n0] "v"(v.n[0]),                  \
-        [n1] "v"(v.n[1]), [n2] "v"(v.n[2]), [n3] "v"(v.n[3]))
-
-template <bool SM, typename C>
-__device__ __forceinline__ void pair2x2v(C& x0, C& x1, const VMat32& v) {
-  float t0, t1, t2, t3;
-  if constexpr (SM) QSV_PAIR_F32V(QSV_SREG);
-  else QSV_PAIR_F32V(QSV_VREG);
+// Whether the pair of register index offset lr is under every control.
+__device__ __forceinline__ bool pair_on(uint32_t rt, uint32_t lr,
+                                        uint32_t lctrl) {
+  // rt and lr have disjoint bits: the thread part is tested once
+  return ((rt & lctrl) | (lr & lctrl)) == lctrl;
 }
 
-template <int I, int R, bool CTRL, bool SM, typename C, typename T>
-__device__ __forceinline__ void dense1_regs(C* a, const T* m, uint32_t rt,
-                                            const uint32_t* lr,
-                                            uint32_t lctrl) {
-  if constexpr (sizeof(T) == 4) {
-    const VMat32 v = vmat32<SM>(m);
+template <int I, int R, typename C, typename M>
+__device__ __forceinline__ void dense1_regs(C* a, const M& m) {
+#pragma unroll
+  for (int j = 0; j < R; ++j)
+    if (!(j & (1 << I))) pair2x2(a[j], a[j | (1 << I)], m);
+}
+
+// The same update, applied only where every tile-local bit of lctrl is 1.
+template <int I, int R, typename T, typename C>
+__device__ __forceinline__ void dense1_ctrl_regs(C* a, const uint64_t* q,
+                                                 uint32_t rt,
+                                                 const uint32_t* lr,
+                                                 uint32_t lctrl) {
+  const auto m = uniform_mat<T>(q);
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    if (j & (1 << I)) continue;
+    const int j1 = j | (1 << I);
+    C y0 = a[j], y1 = a[j1];
+    pair2x2(y0, y1, m);
+    const bool on = pair_on(rt, lr[j], lctrl);
+    a[j] = csel(on, y0, a[j]);
+    a[j1] = csel(on, y1, a[j1]);
+  }
+}
+
+// And with the matrix chosen per pair by tile-local bit mbit: q0 where the
+// bit is 0, q1 where it is 1 (mbit differs from the target).  Every pair
+// under q0 (kept where selected), then under q1: twice the FMAs of a plain
+// op, but one uniform matrix at a time (selecting one per pair set the
+// register peak of the whole kernel, for an op class that circuits rarely
+// produce).
+template <int I, int R, typename T, typename C>
+__device__ __forceinline__ void dense1_mux_regs(C* a, const uint64_t* q0,
+                                                const uint64_t* q1,
+                                                uint32_t rt,
+                                                const uint32_t* lr,
+                                                uint32_t lctrl, int mbit) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const auto m = uniform_mat<T>(h ? q1 : q0);
 #pragma unroll
     for (int j = 0; j < R; ++j) {
       if (j & (1 << I)) continue;
       const int j1 = j | (1 << I);
-      if constexpr (CTRL) {
-        C y0 = a[j], y1 = a[j1];
-        pair2x2v<SM>(y0, y1, v);
-        const bool on = ((rt & lctrl) | (lr[j] & lctrl)) == lctrl;
-        a[j] = csel(on, y0, a[j]);
-        a[j1] = csel(on, y1, a[j1]);
-      } else {
-        pair2x2v<SM>(a[j], a[j1], v);
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    if (j & (1 << I)) continue;
-    const int j1 = j | (1 << I);
-    if constexpr (CTRL) {
+      const bool sel = (((rt >> mbit) | (lr[j] >> mbit)) & 1u) != 0;
       C y0 = a[j], y1 = a[j1];
-      pair2x2<SM>(y0, y1, m[0], m[1], m[2], m[3], m[4], m[5], m[6], m[7]);
-      // rt and lr[j] have disjoint bits: test the thread part once
-      const bool on = ((rt & lctrl) | (lr[j] & lctrl)) == lctrl;
-      a[j] = csel(on, y0, a[j]);
-      a[j1] = csel(on, y1, a[j1]);
-    } else {
-      pair2x2<SM>(a[j], a[j1], m[0], m[1], m[2], m[3], m[4], m[5], m[6],
-                  m[7]);
+      pair2x2(y0, y1, m);
+      const bool keep = pair_on(rt, lr[j], lctrl) && (h ? sel : !sel);
+      a[j] = csel(keep, y0, a[j]);
+      a[j1] = csel(keep, y1, a[j1]);
     }
   }
 }
 
-// The same update with the matrix chosen per pair by tile-local bit mbit:
-// m0 where the bit is 0, m1 where it is 1 (mbit differs from the target),
-// applied only where every bit of lctrl is 1.  Each pair takes both uniform
-// matrices in turn and keeps the one its bits select: twice the FMAs of a
-// plain op, but the matrices stay in scalar registers (selecting one per
-// pair in vector registers set the register peak of the whole kernel, for
-// an op class that circuits rarely produce).
-template <int I, int R, typename C, typename T>
-__device__ __forceinline__ void dense1_mux_regs(C* a, const T* m0,
-                                                const T* m1, uint32_t rt,
-                                                const uint32_t* lr,
-                                                uint32_t lctrl, int mbit) {
-  if constexpr (sizeof(T) == 4) {
-    // complex64: every pair under m0 (kept where selected), then under m1,
-    // with one matrix at a time in vector registers
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const VMat32 v = vmat32<true>(h ? m1 : m0);
-#pragma unroll
-      for (int j = 0; j < R; ++j) {
-        if (j & (1 << I)) continue;
-        const int j1 = j | (1 << I);
-        const bool sel = (((rt >> mbit) | (lr[j] >> mbit)) & 1u) != 0;
-        const bool on = ((rt & lctrl) | (lr[j] & lctrl)) == lctrl;
-        C y0 = a[j], y1 = a[j1];
-        pair2x2v<true>(y0, y1, v);
-        const bool keep = on && (h ? sel : !sel);
-        a[j] = csel(keep, y0, a[j]);
-        a[j1] = csel(keep, y1, a[j1]);
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    if (j & (1 << I)) continue;
-    const int j1 = j | (1 << I);
-    const bool sel = (((rt >> mbit) | (lr[j] >> mbit)) & 1u) != 0;
-    const bool on = ((rt & lctrl) | (lr[j] & lctrl)) == lctrl;
-    C y0 = a[j], y1 = a[j1];
-    pair2x2<true>(y0, y1, m0[0], m0[1], m0[2], m0[3], m0[4], m0[5], m0[6],
-                  m0[7]);
-    a[j] = csel(on && !sel, y0, a[j]);
-    a[j1] = csel(on && !sel, y1, a[j1]);
-    C z0 = a[j], z1 = a[j1];
-    pair2x2<true>(z0, z1, m1[0], m1[1], m1[2], m1[3], m1[4], m1[5], m1[6],
-                  m1[7]);
-    a[j] = csel(on && sel, z0, a[j]);
-    a[j1] = csel(on && sel, z1, a[j1]);
-  }
-}
-
-template <int R, typename C, typename T>
-__device__ __forceinline__ void dense1_mux_dispatch(int reg, C* a, const T* m0,
-                                                    const T* m1, uint32_t rt,
-                                                    const uint32_t* lr,
-                                                    uint32_t lctrl, int mbit) {
-#define QSV_D1M(I)                                                        \
-  case I:                                                                 \
-    if constexpr ((1 << I) < R) {                                         \
-      dense1_mux_regs<I, R>(a, m0, m1, rt, lr, lctrl, mbit);              \
-      break;                                                              \
-    } else {                                                              \
-      __builtin_unreachable();                                            \
-    }
-  switch (reg) {
-    QSV_D1M(0)
-    QSV_D1M(1)
-    QSV_D1M(2)
-    QSV_D1M(3)
-    QSV_D1M(4)
-    default:
-      __builtin_unreachable();  // the planner emits reg < RB only
-  }
-#undef QSV_D1M
-}
-
-template <int R, bool CTRL, bool SM, typename C, typename T>
-__device__ __forceinline__ void dense1_dispatch(int reg, C* a, const T* m,
+// Both by target register.
+template <int R, bool MUX, typename T, typename C>
+__device__ __forceinline__ void dense1_dispatch(int reg, C* a,
+                                                const uint64_t* q0,
+                                                const uint64_t* q1,
                                                 uint32_t rt, const uint32_t* lr,
-                                                uint32_t lctrl) {
+                                                uint32_t lctrl, int mbit) {
 #define QSV_D1(I)                                                          \
   case I:                                                                  \
     if constexpr ((1 << I) < R) {                                          \
-      dense1_regs<I, R, CTRL, SM>(a, m, rt, lr, lctrl);                    \
+      if constexpr (MUX)                                                   \
+        dense1_mux_regs<I, R, T>(a, q0, q1, rt, lr, lctrl, mbit);          \
+      else                                                                 \
+        dense1_ctrl_regs<I, R, T>(a, q0, rt, lr, lctrl);                   \
       break;                                                               \
     } else {                                                               \
       __builtin_unreachable();                                             \
@@ -320,32 +295,20 @@ __device__ __forceinline__ void dense1_dispatch(int reg, C* a, const T* m,
 }
 
 // The mux update when the mux bit is register bit K of the segment: which
-// matrix a pair takes is known at compile time, both matrices are uniform.
-template <int I, int K, int R, typename C, typename T>
-__device__ __forceinline__ void dense1_muxreg_regs(C* a, const T* m0,
-                                                   const T* m1) {
-  if constexpr (sizeof(T) == 4) {
-    // complex64: the pairs of m0, then those of m1, one matrix at a time
-    // in vector registers
+// matrix a pair takes is known at compile time.  The pairs of q0, then those
+// of q1, one matrix at a time.
+template <int I, int K, int R, typename T, typename C>
+__device__ __forceinline__ void dense1_muxreg_regs(C* a, const uint64_t* q0,
+                                                   const uint64_t* q1) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const VMat32 v = vmat32<true>(h ? m1 : m0);
+  for (int h = 0; h < 2; ++h) {
+    const auto m = uniform_mat<T>(h ? q1 : q0);
 #pragma unroll
-      for (int j = 0; j < R; ++j) {
-        if (j & (1 << I)) continue;
-        if ((j >> K & 1) != h) continue;
-        pair2x2v<true>(a[j], a[j | (1 << I)], v);
-      }
+    for (int j = 0; j < R; ++j) {
+      if (j & (1 << I)) continue;
+      if ((j >> K & 1) != h) continue;
+      pair2x2(a[j], a[j | (1 << I)], m);
     }
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    if (j & (1 << I)) continue;
-    const int j1 = j | (1 << I);
-    const T* m = (j >> K & 1) ? m1 : m0;
-    pair2x2<true>(a[j], a[j1], m[0], m[1], m[2], m[3], m[4], m[5], m[6],
-                  m[7]);
   }
 }
 
@@ -588,17 +551,16 @@ __device__ __forceinline__ void phase_block(typename CxT<T>::type* a,
 }
 
 // The fields of one tile op that the kernels read: its 32-byte header and
-// both matrices (FP32 for complex64 states, FP64 for complex128), as raw
-// bit patterns, loaded in one batch of scalar loads.
+// both matrices (FP32 for complex64 states, FP64 for complex128), loaded in
+// one batch of scalar loads.
 template <typename T>
 struct OpFields {
-  using B = std::conditional_t<sizeof(T) == 4, uint32_t, uint64_t>;
   int32_t code, arg;
   uint32_t lctrl;
   int32_t blob;
   uint64_t gctrl;
   int32_t dbit0, dbit1;
-  B m0[8], m1[8];
+  uint64_t m0[kMatWords<T>], m1[kMatWords<T>];
 };
 
 template <typename T>
@@ -613,26 +575,17 @@ __device__ __forceinline__ OpFields<T> load_op(const TileOp* op) {
   f.gctrl = uint64_t(h1.x) | (uint64_t(h1.y) << 32);
   f.dbit0 = int32_t(h1.z);
   f.dbit1 = int32_t(h1.w);
-  if constexpr (sizeof(T) == 4) {
-    const cptr<u32x4> mv = as_const(reinterpret_cast<const u32x4*>(op->mf));
+  constexpr int W = kMatWords<T>;
+  const cptr<u32x4> mv = as_const(reinterpret_cast<const u32x4*>(
+      sizeof(T) == 4 ? static_cast<const void*>(op->mf)
+                     : static_cast<const void*>(op->m)));
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const u32x4 u = mv[i], v = mv[2 + i];
-      f.m0[4 * i] = u.x; f.m0[4 * i + 1] = u.y;
-      f.m0[4 * i + 2] = u.z; f.m0[4 * i + 3] = u.w;
-      f.m1[4 * i] = v.x; f.m1[4 * i + 1] = v.y;
-      f.m1[4 * i + 2] = v.z; f.m1[4 * i + 3] = v.w;
-    }
-  } else {
-    const cptr<u32x4> mv = as_const(reinterpret_cast<const u32x4*>(op->m));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const u32x4 u = mv[i], v = mv[4 + i];
-      f.m0[2 * i] = uint64_t(u.x) | (uint64_t(u.y) << 32);
-      f.m0[2 * i + 1] = uint64_t(u.z) | (uint64_t(u.w) << 32);
-      f.m1[2 * i] = uint64_t(v.x) | (uint64_t(v.y) << 32);
-      f.m1[2 * i + 1] = uint64_t(v.z) | (uint64_t(v.w) << 32);
-    }
+  for (int i = 0; i < W / 2; ++i) {
+    const u32x4 u = mv[i], v = mv[W / 2 + i];
+    f.m0[2 * i] = uint64_t(u.x) | (uint64_t(u.y) << 32);
+    f.m0[2 * i + 1] = uint64_t(u.z) | (uint64_t(u.w) << 32);
+    f.m1[2 * i] = uint64_t(v.x) | (uint64_t(v.y) << 32);
+    f.m1[2 * i + 1] = uint64_t(v.z) | (uint64_t(v.w) << 32);
   }
   return f;
 }
@@ -645,7 +598,8 @@ __device__ __forceinline__ void pin_op_fields(OpFields<T>& f) {
   asm volatile("" : "+s"(f.code), "+s"(f.arg), "+s"(f.lctrl), "+s"(f.blob),
                     "+s"(f.gctrl), "+s"(f.dbit0), "+s"(f.dbit1));
 #pragma unroll
-  for (int e = 0; e < 8; ++e) asm volatile("" : "+s"(f.m0[e]), "+s"(f.m1[e]));
+  for (int e = 0; e < kMatWords<T>; ++e)
+    asm volatile("" : "+s"(f.m0[e]), "+s"(f.m1[e]));
 }
 
 // Read one word of each 64-byte line of a pass's program that its kernel
@@ -746,46 +700,39 @@ __device__ __forceinline__ void load_lds_offsets(const uint32_t* p,
 template <int CLS, int I, int K, int RB, typename T, typename C>
 __device__ __forceinline__ void hot_op(C* a, OpFields<T>& f, uint64_t base,
                                        uint32_t rt, const TileOp* next) {
-  using Bits = typename OpFields<T>::B;
-  constexpr int R = 1 << RB;
-  T m0[8], m1[8];
+  constexpr int R = 1 << RB, W = kMatWords<T>;
+  // the barriers keep the compiler from moving the loads below the update,
+  // and their first use above its end
   if constexpr (CLS == kCodeUniform) {
     // one matrix for the whole tile, chosen by one bit of its base index (an
     // outer mux qubit, or bit 63, which no index has); the choice is made on
-    // the bit patterns, so it stays scalar and the FMAs read the matrix from
-    // scalar registers
+    // the bit patterns, so it stays scalar
     const bool second = ((base >> (f.arg & 63)) & 1) != 0;
+    uint64_t q[W];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      Bits b = second ? f.m1[e] : f.m0[e];
-      asm volatile("" : "+s"(b));
-      m0[e] = __builtin_bit_cast(T, b);
+    for (int e = 0; e < W; ++e) {
+      q[e] = second ? f.m1[e] : f.m0[e];
+      asm volatile("" : "+s"(q[e]));
     }
+    const auto m = uniform_mat<T>(q);
+    f = load_op<T>(next);
+    __builtin_amdgcn_sched_barrier(0);
+    dense1_regs<I, R>(a, m);
+    __builtin_amdgcn_sched_barrier(0);
+  } else if constexpr (CLS == kCodeThreadMux) {
+    // mux bit in the thread index: one matrix per thread
+    const VecMat<T> m =
+        thread_mat<T>(f.m0, f.m1, ((rt >> f.arg) & 1u) != 0);
+    f = load_op<T>(next);
+    __builtin_amdgcn_sched_barrier(0);
+    dense1_regs<I, R>(a, m);
+    __builtin_amdgcn_sched_barrier(0);
   } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      m0[e] = __builtin_bit_cast(T, f.m0[e]);
-      m1[e] = __builtin_bit_cast(T, f.m1[e]);
-    }
-    if constexpr (CLS == kCodeThreadMux) {
-      // mux bit in the thread index: one matrix per thread
-      const bool sel = ((rt >> f.arg) & 1u) != 0;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) m0[e] = sel ? m1[e] : m0[e];
-    }
+    __builtin_amdgcn_sched_barrier(0);
+    dense1_muxreg_regs<I, K, R, T>(a, f.m0, f.m1);
+    __builtin_amdgcn_sched_barrier(0);
+    f = load_op<T>(next);
   }
-  // the barriers keep the compiler from moving the loads below the update,
-  // and their first use above its end
-  if constexpr (CLS != kCodeRegMux) f = load_op<T>(next);
-  __builtin_amdgcn_sched_barrier(0);
-  if constexpr (CLS == kCodeUniform)
-    dense1_regs<I, R, false, true>(a, m0, rt, nullptr, 0u);
-  else if constexpr (CLS == kCodeRegMux)
-    dense1_muxreg_regs<I, K, R>(a, m0, m1);
-  else
-    dense1_regs<I, R, false, false>(a, m0, rt, nullptr, 0u);
-  __builtin_amdgcn_sched_barrier(0);
-  if constexpr (CLS == kCodeRegMux) f = load_op<T>(next);
   pin_op_fields(f);
 }
 
@@ -884,23 +831,21 @@ __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
       const int cls = f.code >> 6;
       if ((base & f.gctrl) == f.gctrl) {  // else an outer control is 0
       const int reg = f.code & 7;
-      T m0[8], m1[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        m0[e] = __builtin_bit_cast(T, f.m0[e]);
-        m1[e] = __builtin_bit_cast(T, f.m1[e]);
-      }
       uint32_t lr[R];
 #pragma unroll
       for (int j = 0; j < R; ++j) lr[j] = reg_offset(lay, j);
       if (cls == kCodeCtrl) {
         const bool second = ((base >> (f.arg & 63)) & 1) != 0;
-        T m[8];
+        uint64_t q[kMatWords<T>];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) m[e] = second ? m1[e] : m0[e];
-        dense1_dispatch<R, true, false>(reg, a, m, rt, lr, f.lctrl);
+        for (int e = 0; e < kMatWords<T>; ++e) {
+          q[e] = second ? f.m1[e] : f.m0[e];
+          asm volatile("" : "+s"(q[e]));
+        }
+        dense1_dispatch<R, false, T>(reg, a, q, nullptr, rt, lr, f.lctrl, 0);
       } else if (cls == kCodeCtrlMux) {
-        dense1_mux_dispatch<R>(reg, a, m0, m1, rt, lr, f.lctrl, f.arg);
+        dense1_dispatch<R, true, T>(reg, a, f.m0, f.m1, rt, lr, f.lctrl,
+                                    f.arg);
       } else if (cls == kCodePhaseBlock) {
         phase_block<T, RB>(
             a,
@@ -909,8 +854,10 @@ __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
             rt, base);
       } else if (cls == kCodePhase) {
         C ph;
-        ph.x = m0[0];
-        ph.y = m0[1];
+        ph.x = mat_entry<T>(f.m0, 0);
+        ph.y = mat_entry<T>(f.m0, 1);
+        if constexpr (sizeof(T) == 4)  // see VecMat
+          asm volatile("" : "+v"(ph.x), "+v"(ph.y));
         // the index's thread and register parts have disjoint bits
         const uint32_t tm = rt & f.lctrl;
 #pragma unroll
@@ -929,8 +876,8 @@ __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
         C t[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          t[e].x = m0[2 * e];
-          t[e].y = m0[2 * e + 1];
+          t[e].x = mat_entry<T>(f.m0, 2 * e);
+          t[e].y = mat_entry<T>(f.m0, 2 * e + 1);
         }
         // thread parts of the two index bits, once per op
         const uint32_t t0 = d0 >= 0 ? (rt >> (d0 & 31)) & 1u : g0;
