@@ -702,7 +702,7 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
     std::string err = emit_tile_pass(p, G, po.reg_log2, &tpasses, &tsegs,
                                      &tops, &est);
     if (!err.empty()) return fail(QSV_ERR_DEVICE, err);
-    set_lds_offsets(tile_lds_map(s->prec, po.reg_log2), po.reg_log2,
+    set_lds_offsets(tile_lds_map(s->prec, po.reg_log2, n, p.L), po.reg_log2,
                     &tpasses.back(), tsegs.data());
     return QSV_OK;
   };

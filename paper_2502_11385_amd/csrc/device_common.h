@@ -104,9 +104,25 @@ hipError_t launch_dense(int prec, void* amp, int n, const HostGate& g,
 // Plain diagonal gate (any k, controls).
 hipError_t launch_diag(int prec, void* amp, int n, const HostGate& g,
                        hipStream_t stream);
-// The LDS map of the tile kernel's re-layouts (prec, register bits).
-inline LdsMap tile_lds_map(int prec, int rb) {
-  return prec == 1 && rb == 4 ? kLds4 : kLds8;
+// Whether a pass's tiles re-lay out through LDS whole (an amplitude at a time)
+// or in halves (real parts, then imaginary parts).  Whole takes half the LDS
+// instructions and barriers, and twice the LDS.  complex64 with 8 or 32
+// registers always goes whole.  The others do while every tile of the state
+// has its LDS at once, 128 KiB on each of 256 CUs, where the chain of
+// latencies of a tile bounds the pass; beyond, the work-groups per CU that
+// the halves leave room for count more (kernel time, halves -> whole:
+// complex64 20 qubits 138 -> 133 us, 22 qubits 233 -> 226, 23 qubits
+// 364 -> 377, 26 qubits 2.64 -> 2.84 ms; complex128 12 qubits 60 -> 56 us,
+// 21 qubits 212 -> 209, 22 qubits 341 -> 362, 24 qubits 1.07 -> 1.24 ms).
+inline bool tile_whole(int prec, int rb, int n, int L) {
+  if (prec == 1 && rb != 4) return true;
+  const uint64_t amp = prec == 1 ? 8 : 16;
+  return (amp << n) <= uint64_t(32) << 20 && (amp << L) <= 65536;
+}
+// The LDS map of the tile kernel's re-layouts.
+inline LdsMap tile_lds_map(int prec, int rb, int n, int L) {
+  if (tile_whole(prec, rb, n, L)) return prec == 1 ? kLds8 : kLds16;
+  return prec == 1 ? kLds4 : kLds8;
 }
 // One tile pass: pass/segs/ops point into the device program buffer,
 // host_pass is the host copy of *pass; rb is the register bits.

@@ -23,11 +23,6 @@
 
 namespace qsv {
 
-// Tile kernels whose re-layouts go in halves (one component per amplitude
-// through LDS): complex64 with 16 registers per thread, and complex128.
-template <typename T, int RB>
-constexpr bool kHalves = (sizeof(T) == 4 && RB == 4) || sizeof(T) == 8;
-
 // Tile index -> global index of the tile's first amplitude: the index's
 // bits spread over the non-tile qubits, run by run (four cover every tile
 // of up to four groups of consecutive qubits, so that the usual tile needs
@@ -116,8 +111,8 @@ __device__ __forceinline__ void tile_outputs(
 // disjoint bit sets: the lane part (thread bits 0..5 spread over their tile
 // qubits) differs per lane, the others are uniform over a wave.  Each access
 // is therefore one wave-uniform 64-bit address plus a per-lane offset,
-// 32-bit where LANE32 says it fits (else 64-bit).
-template <typename T, int RB, bool LANE32>
+// 32-bit where LANE32 says it fits (else 64-bit).  HALVES: see tile_whole.
+template <typename T, int RB, bool LANE32, bool HALVES>
 __device__ __forceinline__ void tile_body(typename CxT<T>::type* __restrict__ amp,
                                           const TilePass* __restrict__ pass,
                                           const TileSeg* __restrict__ segs,
@@ -175,9 +170,7 @@ __device__ __forceinline__ void tile_body(typename CxT<T>::type* __restrict__ am
     }
   }
   if (blockIdx.x < kWarmTiles) warm_program<T>(pass, segs, ops, tid);
-  // complex64 with 16 registers and complex128 re-lay out in halves (half
-  // the LDS)
-  tile_apply<T, RB, kHalves<T, RB>>(a, pass, segs, ops, base, tid, true);
+  tile_apply<T, RB, HALVES>(a, pass, segs, ops, base, tid, true);
   // The store addresses are formed again from the few values they derive
   // from (opaque to the compiler), so that the sixteen register addresses
   // are not held in scalar registers across the op loop.
@@ -210,42 +203,43 @@ __device__ __forceinline__ void tile_body(typename CxT<T>::type* __restrict__ am
   }
 }
 
-// complex64 with 16 registers per thread: capped at 102 VGPRs so that at
+// complex64 with 16 registers per thread, in halves: capped at 102 VGPRs so that at
 // least five waves share each SIMD (the build reaches 80 VGPRs, six waves;
-// the half re-layouts take 16 KiB of LDS per tile, ten tiles per CU).
+// the half re-layouts take 16 KiB of LDS per tile, ten tiles per CU).  Seven
+// and eight waves were no faster (30 qubits: 154 and 198 ms against 153).
 template <bool LANE32>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5)))
     tile_kernel_c64_rb4(float2* __restrict__ amp,
                         const TilePass* __restrict__ pass,
                         const TileSeg* __restrict__ segs,
                         const TileOp* __restrict__ ops) {
-  tile_body<float, 4, LANE32>(amp, pass, segs, ops);
+  tile_body<float, 4, LANE32, true>(amp, pass, segs, ops);
 }
 
-template <typename T, int RB, bool LANE32>
+template <typename T, int RB, bool LANE32, bool HALVES>
 __global__ void __launch_bounds__(512)
     tile_kernel(typename CxT<T>::type* __restrict__ amp,
                 const TilePass* __restrict__ pass,
                 const TileSeg* __restrict__ segs,
                 const TileOp* __restrict__ ops) {
-  tile_body<T, RB, LANE32>(amp, pass, segs, ops);
+  tile_body<T, RB, LANE32, HALVES>(amp, pass, segs, ops);
 }
 
-template <typename T, int RB, bool LANE32>
+template <typename T, int RB, bool LANE32, bool HALVES>
 static hipError_t tile_launch(void* amp, int n, int L, bool outputs,
                               const TilePass* pass, const TileSeg* segs,
                               const TileOp* ops, hipStream_t stream) {
   using C = typename CxT<T>::type;
   void (*fn)(C*, const TilePass*, const TileSeg*, const TileOp*);
-  if constexpr (sizeof(T) == 4 && RB == 4)
+  if constexpr (sizeof(T) == 4 && HALVES)
     fn = tile_kernel_c64_rb4<LANE32>;
   else
-    fn = tile_kernel<T, RB, LANE32>;
+    fn = tile_kernel<T, RB, LANE32, HALVES>;
   // re-layouts in halves need one component per amplitude; the folded
   // outputs stage FP64 values (8 bytes)
-  const size_t lds = !kHalves<T, RB> ? size_t(sizeof(C)) << L
-                     : outputs      ? std::max(size_t(8), sizeof(T)) << L
-                                    : size_t(sizeof(T)) << L;
+  const size_t lds = !HALVES   ? size_t(sizeof(C)) << L
+                     : outputs ? std::max(size_t(8), sizeof(T)) << L
+                               : size_t(sizeof(T)) << L;
   // set once per kernel function; callers on several threads (the server's
   // scheduler and its clients) reach this together, hence call_once
   static std::once_flag once;
@@ -263,16 +257,16 @@ static hipError_t tile_launch(void* amp, int n, int L, bool outputs,
   return hipGetLastError();
 }
 
-template <typename T, int RB>
+template <typename T, int RB, bool HALVES>
 static hipError_t tile_launch_t(void* amp, int n, const TilePass& hp,
                                 const TilePass* pass, const TileSeg* segs,
                                 const TileOp* ops, hipStream_t stream) {
   const bool outputs = (hp.flags & kPassOutputs) != 0;
   if (hp.flags & kPassLane32)
-    return tile_launch<T, RB, true>(amp, n, hp.L, outputs, pass, segs, ops,
-                                    stream);
-  return tile_launch<T, RB, false>(amp, n, hp.L, outputs, pass, segs, ops,
-                                   stream);
+    return tile_launch<T, RB, true, HALVES>(amp, n, hp.L, outputs, pass, segs,
+                                            ops, stream);
+  return tile_launch<T, RB, false, HALVES>(amp, n, hp.L, outputs, pass, segs,
+                                           ops, stream);
 }
 
 hipError_t launch_tile(int prec, int rb, void* amp, int n,
@@ -282,18 +276,23 @@ hipError_t launch_tile(int prec, int rb, void* amp, int n,
   const int L = host_pass.L;
   if (L - rb < 0 || L - rb > 9 || L > kMaxTileBits || n - L > 31)
     return hipErrorInvalidValue;
-#define QSV_T(T, RB) \
-  return tile_launch_t<T, RB>(amp, n, host_pass, pass, segs, ops, stream)
+#define QSV_T(T, RB, HALVES)                                            \
+  return tile_launch_t<T, RB, HALVES>(amp, n, host_pass, pass, segs, ops, \
+                                      stream)
+  const bool whole = tile_whole(prec, rb, n, L);
   if (prec == 1) {
-    if (rb == 3) QSV_T(float, 3);
-    if (rb == 4) QSV_T(float, 4);
-    if (rb == 5) QSV_T(float, 5);
+    if (rb == 3) QSV_T(float, 3, false);
+    if (rb == 4 && whole) QSV_T(float, 4, false);
+    if (rb == 4) QSV_T(float, 4, true);
+    if (rb == 5) QSV_T(float, 5, false);
     return hipErrorInvalidValue;
   }
   // complex128 tiles use 8 or 16 registers per thread (the planner rejects
   // reg_log2 = 5 for them: 32 double2 registers would spill)
-  if (rb == 3) QSV_T(double, 3);
-  if (rb == 4) QSV_T(double, 4);
+  if (rb == 3 && whole) QSV_T(double, 3, false);
+  if (rb == 3) QSV_T(double, 3, true);
+  if (rb == 4 && whole) QSV_T(double, 4, false);
+  if (rb == 4) QSV_T(double, 4, true);
   return hipErrorInvalidValue;
 #undef QSV_T
 }

@@ -61,3 +61,28 @@ def test_scattered_tile(runs, prec, reg):
     got = s.get().astype(np.complex128)
     s.free()
     assert np.max(np.abs(got - want)) <= TOL[prec]
+
+
+# state sizes on both sides of the line between whole and half re-layouts
+# (32 MiB), and a tile too large to go whole in a small state
+@pytest.mark.parametrize("prec,n,tile", [(C64, 22, 12), (C64, 23, 12),
+                                         (C64, 16, 13),
+                                         (C128, 21, 12), (C128, 22, 12),
+                                         (C128, 15, 13)])
+def test_whole_and_half_relayouts(prec, n, tile):
+    rng = np.random.default_rng(n + tile)
+    qs = sorted({int(q) for q in rng.permutation(n)[:9]} | {0, n - 1})
+    circ = qsv.Circuit()
+    want = random_state(n, 3)
+    s = qsv.State(n, prec)
+    s.set(want)
+    for i in range(3):
+        for j, q in enumerate(qs):
+            u = _unitary(rng)
+            c = [qs[j - 1]] if i == 1 and j else []
+            circ.add([q], u, c)
+            want = oracle.apply_gate(want, n, u, [q], c)
+    s.apply_fused(circ, qsv.fuse_opts(strategy=qsv.PLAN_TILED, tile_log2=tile,
+                                      reg_log2=4))
+    assert np.max(np.abs(s.get() - want)) <= TOL[prec]
+    s.free()
