@@ -204,7 +204,7 @@ __device__ __forceinline__ void tile_body(typename CxT<T>::type* __restrict__ am
 }
 
 // complex64 with 16 registers per thread, in halves: capped at 102 VGPRs so that at
-// least five waves share each SIMD (the build reaches 80 VGPRs, six waves;
+// least five waves share each SIMD (the build reaches 75 VGPRs, six waves;
 // the half re-layouts take 16 KiB of LDS per tile, ten tiles per CU).  Seven
 // and eight waves were no faster (30 qubits: 154 and 198 ms against 153).
 template <bool LANE32>
@@ -216,6 +216,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5)))
   tile_body<float, 4, LANE32, true>(amp, pass, segs, ops);
 }
 
+// The others without a cap.  complex128 with 16 registers reaches 128 VGPRs,
+// four waves per SIMD; at 140 and three, 23 qubits took 1.30 ms, not 1.21.
 template <typename T, int RB, bool LANE32, bool HALVES>
 __global__ void __launch_bounds__(512)
     tile_kernel(typename CxT<T>::type* __restrict__ amp,

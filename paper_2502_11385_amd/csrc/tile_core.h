@@ -202,12 +202,25 @@ __device__ __forceinline__ VecMat<T> thread_mat(const uint64_t* q0,
   return v;
 }
 
-// Whether the pair of register index offset lr is under every control.
-__device__ __forceinline__ bool pair_on(uint32_t rt, uint32_t lr,
-                                        uint32_t lctrl) {
-  // rt and lr have disjoint bits: the thread part is tested once
-  return ((rt & lctrl) | (lr & lctrl)) == lctrl;
-}
+// The controls of an op inside the tile: an amplitude is under all of them
+// where its thread's bits and its register's are.  The registers' part is
+// uniform, so that one comparison per op is made in vector registers (one
+// per register kept up to eight of them beside the tile).
+struct Controls {
+  bool thread;         // this thread's bits
+  uint32_t mask, reg;  // the mask, and its register bits
+
+  // rt: the thread's part of the index; all: all the register bits
+  __device__ __forceinline__ Controls(uint32_t lctrl, uint32_t rt,
+                                      uint32_t all)
+      : thread((rt & lctrl) == (lctrl & ~all)),
+        mask(lctrl),
+        reg(lctrl & all) {}
+  // register of index offset lr
+  __device__ __forceinline__ bool on(uint32_t lr) const {
+    return thread && (lr & mask) == reg;
+  }
+};
 
 template <int I, int R, typename C, typename M>
 __device__ __forceinline__ void dense1_regs(C* a, const M& m) {
@@ -219,9 +232,8 @@ __device__ __forceinline__ void dense1_regs(C* a, const M& m) {
 // The same update, applied only where every tile-local bit of lctrl is 1.
 template <int I, int R, typename T, typename C>
 __device__ __forceinline__ void dense1_ctrl_regs(C* a, const uint64_t* q,
-                                                 uint32_t rt,
-                                                 const uint32_t* lr,
-                                                 uint32_t lctrl) {
+                                                 const Controls& ctl,
+                                                 const uint32_t* lr) {
   const auto m = uniform_mat<T>(q);
 #pragma unroll
   for (int j = 0; j < R; ++j) {
@@ -229,7 +241,7 @@ __device__ __forceinline__ void dense1_ctrl_regs(C* a, const uint64_t* q,
     const int j1 = j | (1 << I);
     C y0 = a[j], y1 = a[j1];
     pair2x2(y0, y1, m);
-    const bool on = pair_on(rt, lr[j], lctrl);
+    const bool on = ctl.on(lr[j]);
     a[j] = csel(on, y0, a[j]);
     a[j1] = csel(on, y1, a[j1]);
   }
@@ -244,9 +256,10 @@ __device__ __forceinline__ void dense1_ctrl_regs(C* a, const uint64_t* q,
 template <int I, int R, typename T, typename C>
 __device__ __forceinline__ void dense1_mux_regs(C* a, const uint64_t* q0,
                                                 const uint64_t* q1,
+                                                const Controls& ctl,
                                                 uint32_t rt,
-                                                const uint32_t* lr,
-                                                uint32_t lctrl, int mbit) {
+                                                const uint32_t* lr, int mbit) {
+  const bool tsel = ((rt >> mbit) & 1u) != 0;
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const auto m = uniform_mat<T>(h ? q1 : q0);
@@ -254,10 +267,10 @@ __device__ __forceinline__ void dense1_mux_regs(C* a, const uint64_t* q0,
     for (int j = 0; j < R; ++j) {
       if (j & (1 << I)) continue;
       const int j1 = j | (1 << I);
-      const bool sel = (((rt >> mbit) | (lr[j] >> mbit)) & 1u) != 0;
+      const bool sel = tsel || ((lr[j] >> mbit) & 1u) != 0;
       C y0 = a[j], y1 = a[j1];
       pair2x2(y0, y1, m);
-      const bool keep = pair_on(rt, lr[j], lctrl) && (h ? sel : !sel);
+      const bool keep = ctl.on(lr[j]) && (h ? sel : !sel);
       a[j] = csel(keep, y0, a[j]);
       a[j1] = csel(keep, y1, a[j1]);
     }
@@ -269,15 +282,16 @@ template <int R, bool MUX, typename T, typename C>
 __device__ __forceinline__ void dense1_dispatch(int reg, C* a,
                                                 const uint64_t* q0,
                                                 const uint64_t* q1,
+                                                const Controls& ctl,
                                                 uint32_t rt, const uint32_t* lr,
-                                                uint32_t lctrl, int mbit) {
+                                                int mbit) {
 #define QSV_D1(I)                                                          \
   case I:                                                                  \
     if constexpr ((1 << I) < R) {                                          \
       if constexpr (MUX)                                                   \
-        dense1_mux_regs<I, R, T>(a, q0, q1, rt, lr, lctrl, mbit);          \
+        dense1_mux_regs<I, R, T>(a, q0, q1, ctl, rt, lr, mbit);            \
       else                                                                 \
-        dense1_ctrl_regs<I, R, T>(a, q0, rt, lr, lctrl);                   \
+        dense1_ctrl_regs<I, R, T>(a, q0, ctl, lr);                         \
       break;                                                               \
     } else {                                                               \
       __builtin_unreachable();                                             \
@@ -478,7 +492,6 @@ __device__ __forceinline__ void phase_block(typename CxT<T>::type* a,
   constexpr int R = 1 << RB;
   const cptr<PhaseBlock> pb = as_const(pb_gen);
   cptr<PhaseTerm> t = as_const(reinterpret_cast<const PhaseTerm*>(pb_gen + 1));
-  U acc[RB + 1];
   // A term's first 16 bytes (outer mask, thread mask, 32-bit turns) are
   // read as one vector, so that each term costs one scalar load round trip.
   auto head = [](cptr<PhaseTerm> p, uint64_t* gm, uint32_t* tm, U* w) {
@@ -488,6 +501,8 @@ __device__ __forceinline__ void phase_block(typename CxT<T>::type* a,
     if constexpr (sizeof(T) == 4) *w = U(h.w);
     else *w = U(p->turns);
   };
+  // one accumulator at a time: only its sum and its phase are live beside
+  // the tile
 #pragma unroll
   for (int k = 0; k <= RB; ++k) {
     U au = 0;
@@ -511,42 +526,37 @@ __device__ __forceinline__ void phase_block(typename CxT<T>::type* a,
       const bool on = ((base & gm) == gm) & ((rt & tm) == tm);
       av += on ? w : U(0);
     }
-    acc[k] = au + av;
-  }
-  if (pb->n_uni[0] + pb->n_thr[0] > 0) {
-    C f0;
-    if constexpr (sizeof(T) == 4) f0 = turn_phase32(acc[0]);
-    else f0 = turn_phase64(acc[0]);
-    if (pb->has_table) {
+    const bool any = nu + nv > 0;
+    C f;
+    if (any) {
+      if constexpr (sizeof(T) == 4) f = turn_phase32(au + av);
+      else f = turn_phase64(au + av);
+    }
+    if (k > 0) {
+      if (!any) continue;
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+        if (j >> (k - 1) & 1) a[j] = cmul(a[j], f);
+    } else if (any && pb->has_table) {
 #pragma unroll
       for (int j = 0; j < R; ++j) {
         C u;
         if constexpr (sizeof(T) == 4) u = make_float2(pb->tf[2 * j], pb->tf[2 * j + 1]);
         else u = make_double2(pb->td[2 * j], pb->td[2 * j + 1]);
-        a[j] = cmul(a[j], cmul(f0, u));
+        a[j] = cmul(a[j], cmul(f, u));
       }
-    } else {
+    } else if (any) {
 #pragma unroll
-      for (int j = 0; j < R; ++j) a[j] = cmul(a[j], f0);
+      for (int j = 0; j < R; ++j) a[j] = cmul(a[j], f);
+    } else if (pb->has_table) {
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        C u;
+        if constexpr (sizeof(T) == 4) u = make_float2(pb->tf[2 * j], pb->tf[2 * j + 1]);
+        else u = make_double2(pb->td[2 * j], pb->td[2 * j + 1]);
+        a[j] = cmul(a[j], u);
+      }
     }
-  } else if (pb->has_table) {
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      C u;
-      if constexpr (sizeof(T) == 4) u = make_float2(pb->tf[2 * j], pb->tf[2 * j + 1]);
-      else u = make_double2(pb->td[2 * j], pb->td[2 * j + 1]);
-      a[j] = cmul(a[j], u);
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < RB; ++r) {
-    if (pb->n_uni[1 + r] + pb->n_thr[1 + r] == 0) continue;
-    C kr;
-    if constexpr (sizeof(T) == 4) kr = turn_phase32(acc[1 + r]);
-    else kr = turn_phase64(acc[1 + r]);
-#pragma unroll
-    for (int j = 0; j < R; ++j)
-      if (j >> r & 1) a[j] = cmul(a[j], kr);
   }
 }
 
@@ -799,6 +809,7 @@ __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
   // thread tid's part of a tile index in the current layout (the I/O layout
   // takes the low bits)
   uint32_t rt = tid;
+  uint32_t at = lds_place(kMap, tid);  // its place in LDS
   int o = cp->op_begin;
   OpFields<T> f = load_op<T>(ops + o);
   pin_op_fields(f);
@@ -815,9 +826,11 @@ __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
 #pragma unroll
     for (int i = 0; i < RB; ++i) lay.rb[i] = bits[i];
     const uint32_t to = thread_local_base(lay, tid);
-    if (h1.y)
-      relayout<HALVES, R>(a, sf, st, lds_place(kMap, rt), lds_place(kMap, to),
-                          active);
+    if (h1.y) {
+      const uint32_t at_to = lds_place(kMap, to);
+      relayout<HALVES, R>(a, sf, st, at, at_to, active);
+      at = at_to;
+    }
     rt = to;
     lds_from = sg->lds;
     while (o < o_end) {
@@ -834,6 +847,7 @@ __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
       uint32_t lr[R];
 #pragma unroll
       for (int j = 0; j < R; ++j) lr[j] = reg_offset(lay, j);
+      const Controls ctl(f.lctrl, rt, lr[R - 1]);
       if (cls == kCodeCtrl) {
         const bool second = ((base >> (f.arg & 63)) & 1) != 0;
         uint64_t q[kMatWords<T>];
@@ -842,10 +856,9 @@ __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
           q[e] = second ? f.m1[e] : f.m0[e];
           asm volatile("" : "+s"(q[e]));
         }
-        dense1_dispatch<R, false, T>(reg, a, q, nullptr, rt, lr, f.lctrl, 0);
+        dense1_dispatch<R, false, T>(reg, a, q, nullptr, ctl, rt, lr, 0);
       } else if (cls == kCodeCtrlMux) {
-        dense1_dispatch<R, true, T>(reg, a, f.m0, f.m1, rt, lr, f.lctrl,
-                                    f.arg);
+        dense1_dispatch<R, true, T>(reg, a, f.m0, f.m1, ctl, rt, lr, f.arg);
       } else if (cls == kCodePhaseBlock) {
         phase_block<T, RB>(
             a,
@@ -858,11 +871,9 @@ __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
         ph.y = mat_entry<T>(f.m0, 1);
         if constexpr (sizeof(T) == 4)  // see VecMat
           asm volatile("" : "+v"(ph.x), "+v"(ph.y));
-        // the index's thread and register parts have disjoint bits
-        const uint32_t tm = rt & f.lctrl;
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-          const bool on = (tm | (lr[j] & f.lctrl)) == f.lctrl;
+          const bool on = ctl.on(lr[j]);
           const C y = cmul(a[j], ph);
           a[j] = csel(on, y, a[j]);
         }
@@ -880,19 +891,18 @@ __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
           t[e].y = mat_entry<T>(f.m0, 2 * e + 1);
         }
         // thread parts of the two index bits, once per op
-        const uint32_t t0 = d0 >= 0 ? (rt >> (d0 & 31)) & 1u : g0;
-        const uint32_t t1 =
-            dk > 1 ? (d1 >= 0 ? (rt >> (d1 & 31)) & 1u : g1) : 0u;
-        const uint32_t tm = rt & f.lctrl;
+        const bool t0 = d0 >= 0 ? ((rt >> (d0 & 31)) & 1u) != 0 : g0 != 0;
+        const bool t1 =
+            dk > 1 && (d1 >= 0 ? ((rt >> (d1 & 31)) & 1u) != 0 : g1 != 0);
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-          const uint32_t b0 = d0 >= 0 ? t0 | ((lr[j] >> (d0 & 31)) & 1u) : g0;
-          const uint32_t b1 =
-              dk > 1 ? (d1 >= 0 ? t1 | ((lr[j] >> (d1 & 31)) & 1u) : g1) : 0u;
-          const C f01 = csel(b0 != 0, t[1], t[0]);
-          const C f23 = csel(b0 != 0, t[3], t[2]);
-          const C fv = csel(b1 != 0, f23, f01);
-          const bool on = (tm | (lr[j] & f.lctrl)) == f.lctrl;
+          const bool b0 = t0 || (d0 >= 0 && ((lr[j] >> (d0 & 31)) & 1u) != 0);
+          const bool b1 =
+              t1 || (dk > 1 && d1 >= 0 && ((lr[j] >> (d1 & 31)) & 1u) != 0);
+          const C f01 = csel(b0, t[1], t[0]);
+          const C f23 = csel(b0, t[3], t[2]);
+          const C fv = csel(b1, f23, f01);
+          const bool on = ctl.on(lr[j]);
           const C y = cmul(a[j], fv);
           a[j] = csel(on, y, a[j]);
         }
@@ -907,8 +917,7 @@ __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
     uint32_t sf[R], st[R];
     load_lds_offsets<RB>(lds_from, sf);
     load_lds_offsets<RB>(pass->lds, st);
-    relayout<HALVES, R>(a, sf, st, lds_place(kMap, rt), lds_place(kMap, tid),
-                        active);
+    relayout<HALVES, R>(a, sf, st, at, lds_place(kMap, tid), active);
   }
 }
 
