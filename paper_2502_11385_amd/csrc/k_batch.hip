@@ -55,6 +55,7 @@ __device__ __forceinline__ void batch_phase_body(
   }
   uint32_t e = e0;
   for (uint64_t g = lo; g < hi;) {
+    const uint64_t run_begin = work[e].tile_begin;
     const uint64_t run_end =
         e + 1 < n_work ? work[e + 1].tile_begin : n_tiles;
     const BatchCircuit c = circs[work[e].circ];
@@ -71,26 +72,34 @@ __device__ __forceinline__ void batch_phase_body(
     // active wave read the tile's first element, in bounds, and their
     // registers are never written back), so the loads issue back to back
     const bool wave_on = __ballot(active) != 0;
-    uint64_t roff[R];
-    io_reg_offsets<C, RB>(pass, roff);  // bytes of C
+    // element step of each register bit; the registers' offsets are formed
+    // from these at the loads and at the stores (opaque to the compiler), so
+    // that they are not held, and spilled, across the op loop
+    uint32_t step[RB];
+#pragma unroll
+    for (int i = 0; i < RB; ++i) step[i] = 1u << pass->q[L - RB + i];
+    auto reg_el = [&](int j) -> uint32_t {
+      uint32_t o = 0;
+#pragma unroll
+      for (int i = 0; i < RB; ++i)
+        if (j >> i & 1) o += step[i];
+      return o;
+    };
     const uint64_t end = run_end < hi ? run_end : hi;
     warm_program<T>(pass, segs, ops, tid);
     for (; g < end; ++g) {
-      const uint64_t t = g - work[e].tile_begin;
-      uint64_t base = t;
-      for (int b = 0; b < L; ++b) base = insert_zero64(base, pass->q[b]);
-      const char* sb = reinterpret_cast<const char*>(state + base);
+      const uint64_t base = tile_base(pass, uint32_t(g - run_begin));
       C a[R];
       if (!first && wave_on) {
+        const auto rs = raw_rsrc<C>(state + base);
 #pragma unroll
         for (int j = 0; j < R; ++j)
-          a[j] = load_at(state, raw_rsrc<C>(sb + roff[j]),
-                         thr * uint32_t(sizeof(C)));
+          a[j] = load_at(state, rs, thr * uint32_t(sizeof(C)),
+                         reg_el(j) * uint32_t(sizeof(C)));
       } else {
 #pragma unroll
         for (int j = 0; j < R; ++j) {
-          const bool one = first && active && base == 0 && roff[j] == 0 &&
-                           thr == 0;
+          const bool one = j == 0 && first && active && base == 0 && thr == 0;
           a[j].x = one ? T(1) : T(0);
           a[j].y = T(0);
         }
@@ -98,22 +107,23 @@ __device__ __forceinline__ void batch_phase_body(
       // complex64 with 16 registers re-lays out in halves (half the LDS)
       tile_apply<T, RB, sizeof(T) == 4 && RB == 4>(a, pass, segs, ops, base,
                                                   tid, active);
+#pragma unroll
+      for (int i = 0; i < RB; ++i) asm volatile("" : "+s"(step[i]));
       if (active) {
         if (last) {
-          const char* ob =
-              reinterpret_cast<const char*>(out + c.out_offset + base);
+          const auto rs = raw_rsrc<OUT>(out + c.out_offset + base);
 #pragma unroll
           for (int j = 0; j < R; ++j) {
             const double x = double(a[j].x), y = double(a[j].y);
-            const uint64_t ro = roff[j] / sizeof(C) * sizeof(OUT);
-            store_at(raw_rsrc<OUT>(ob + ro), thr * uint32_t(sizeof(OUT)),
-                     OUT(x * x + y * y));
+            store_at(rs, thr * uint32_t(sizeof(OUT)),
+                     reg_el(j) * uint32_t(sizeof(OUT)), OUT(x * x + y * y));
           }
         } else {
+          const auto rs = raw_rsrc<C>(state + base);
 #pragma unroll
           for (int j = 0; j < R; ++j)
-            store_at(raw_rsrc<C>(sb + roff[j]), thr * uint32_t(sizeof(C)),
-                     a[j]);
+            store_at(rs, thr * uint32_t(sizeof(C)),
+                     reg_el(j) * uint32_t(sizeof(C)), a[j]);
         }
       }
     }

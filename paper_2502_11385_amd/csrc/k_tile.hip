@@ -23,22 +23,6 @@
 
 namespace qsv {
 
-// Tile index -> global index of the tile's first amplitude: the index's
-// bits spread over the non-tile qubits, run by run (four cover every tile
-// of up to four groups of consecutive qubits, so that the usual tile needs
-// one batch of loads).
-__device__ __forceinline__ uint64_t tile_base(const TilePass* pass,
-                                              uint32_t tile) {
-  const cptr<TilePass> cp = as_const(pass);
-  uint64_t base = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)  // unused runs have mask 0
-    base |= uint64_t(tile & cp->out_mask[i]) << cp->out_shift[i];
-  for (int i = 4; i < cp->n_out; ++i)
-    base |= uint64_t(tile & cp->out_mask[i]) << cp->out_shift[i];
-  return base;
-}
-
 // Outputs of the last tile pass (kPassOutputs): p = |a|^2 of the tile's
 // final amplitudes (in the I/O layout, register j of thread tid is tile
 // index tid | j << W), stored if requested, then for each key the FP64 sum

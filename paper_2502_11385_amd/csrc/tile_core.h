@@ -921,46 +921,20 @@ __device__ __forceinline__ void tile_apply(typename CxT<T>::type* a,
   }
 }
 
-// Global offsets of a thread's registers in the I/O layout: register j of
-// thread tid sits at gthr | (sum over set bits i of j of greg[i]).
-template <int RB>
-__device__ __forceinline__ void io_offsets(const TilePass* pass, uint64_t base,
-                                           uint32_t tid, uint64_t* gthr,
-                                           uint64_t* greg) {
-  const int W = pass->L - RB;
-  uint64_t g = base;
-  for (int b = 0; b < W; ++b)
-    if (tid >> b & 1) g |= uint64_t(1) << pass->q[b];
-  *gthr = g;
+// Tile index -> global index of the tile's first amplitude: the index's
+// bits spread over the non-tile qubits, run by run (four cover every tile
+// of up to four groups of consecutive qubits, so that the usual tile needs
+// one batch of loads).
+__device__ __forceinline__ uint64_t tile_base(const TilePass* pass,
+                                              uint32_t tile) {
+  const cptr<TilePass> cp = as_const(pass);
+  uint64_t base = 0;
 #pragma unroll
-  for (int i = 0; i < RB; ++i) greg[i] = uint64_t(1) << pass->q[W + i];
-}
-
-// I/O addressing with a uniform per-register pointer and a per-thread
-// 32-bit byte offset (valid when the thread part of the tile index times
-// the amplitude size fits in 32 bits): register j of thread tid is at
-// byte  (tile + sum over set bits i of j of 2^q[W+i]) + thread_off.
-template <typename C, int RB>
-__device__ __forceinline__ uint32_t io_thread_boff(const TilePass* pass,
-                                                   uint32_t tid) {
-  const int W = pass->L - RB;
-  uint32_t o = 0;
-  for (int b = 0; b < W; ++b)
-    if (tid >> b & 1) o |= 1u << pass->q[b];
-  return o * uint32_t(sizeof(C));
-}
-
-// Byte offset of register j of the I/O layout within a tile (uniform).
-template <typename C, int RB>
-__device__ __forceinline__ void io_reg_offsets(const TilePass* pass,
-                                               uint64_t* roff) {
-  const int W = pass->L - RB;
-  roff[0] = 0;
-#pragma unroll
-  for (int j = 1; j < (1 << RB); ++j) {
-    const int i = __builtin_ctz(j);
-    roff[j] = roff[j & (j - 1)] + (uint64_t(sizeof(C)) << pass->q[W + i]);
-  }
+  for (int i = 0; i < 4; ++i)  // unused runs have mask 0
+    base |= uint64_t(tile & cp->out_mask[i]) << cp->out_shift[i];
+  for (int i = 4; i < cp->n_out; ++i)
+    base |= uint64_t(tile & cp->out_mask[i]) << cp->out_shift[i];
+  return base;
 }
 
 template <typename C>
@@ -983,52 +957,46 @@ __device__ __forceinline__ uint32_t io_thread_index(const TilePass* pass,
   return o;
 }
 
-// Raw buffer loads and stores at a 32-bit byte offset from a uniform buffer
-// resource (no per-access 64-bit vector address arithmetic).
+// Raw buffer loads and stores at a 32-bit byte offset and a uniform one from
+// a uniform buffer resource (no per-access address arithmetic).
 __device__ __forceinline__ float2 load_at(const float2*,
                                           __amdgpu_buffer_rsrc_t r,
-                                          uint32_t boff) {
-  return __builtin_bit_cast(float2,
-                            __builtin_amdgcn_raw_buffer_load_b64(r, boff, 0, 0));
+                                          uint32_t boff, uint32_t soff) {
+  return __builtin_bit_cast(
+      float2, __builtin_amdgcn_raw_buffer_load_b64(r, boff, soff, 0));
 }
 __device__ __forceinline__ double2 load_at(const double2*,
                                            __amdgpu_buffer_rsrc_t r,
-                                           uint32_t boff) {
-  return __builtin_bit_cast(double2,
-                            __builtin_amdgcn_raw_buffer_load_b128(r, boff, 0, 0));
+                                           uint32_t boff, uint32_t soff) {
+  return __builtin_bit_cast(
+      double2, __builtin_amdgcn_raw_buffer_load_b128(r, boff, soff, 0));
 }
 __device__ __forceinline__ void store_at(__amdgpu_buffer_rsrc_t r,
-                                         uint32_t boff, float2 v) {
+                                         uint32_t boff, uint32_t soff,
+                                         float2 v) {
   using V = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0));
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V, v), r, boff, 0, 0);
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V, v), r, boff,
+                                        soff, 0);
 }
 __device__ __forceinline__ void store_at(__amdgpu_buffer_rsrc_t r,
-                                         uint32_t boff, float v) {
+                                         uint32_t boff, uint32_t soff,
+                                         float v) {
   __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r,
-                                        boff, 0, 0);
+                                        boff, soff, 0);
 }
 __device__ __forceinline__ void store_at(__amdgpu_buffer_rsrc_t r,
-                                         uint32_t boff, double v) {
+                                         uint32_t boff, uint32_t soff,
+                                         double v) {
   using V = decltype(__builtin_amdgcn_raw_buffer_load_b64(r, 0, 0, 0));
-  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V, v), r, boff, 0,
-                                        0);
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V, v), r, boff,
+                                        soff, 0);
 }
 __device__ __forceinline__ void store_at(__amdgpu_buffer_rsrc_t r,
-                                         uint32_t boff, double2 v) {
+                                         uint32_t boff, uint32_t soff,
+                                         double2 v) {
   using V = decltype(__builtin_amdgcn_raw_buffer_load_b128(r, 0, 0, 0));
-  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(V, v), r, boff, 0,
-                                         0);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(V, v), r, boff,
+                                         soff, 0);
 }
-
-template <int RB>
-__device__ __forceinline__ uint64_t io_addr(uint64_t gthr, const uint64_t* greg,
-                                            int j) {
-  uint64_t o = gthr;
-#pragma unroll
-  for (int i = 0; i < RB; ++i)
-    if (j >> i & 1) o |= greg[i];
-  return o;
-}
-
 
 }  // namespace qsv
