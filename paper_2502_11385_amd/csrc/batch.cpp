@@ -100,7 +100,7 @@ std::string build_program(const qsv_variant* vars, size_t count, int b,
   std::iota(hp->order.begin(), hp->order.end(), 0);
   std::stable_sort(hp->order.begin(), hp->order.end(),
                    [&](int a, int c) { return cost[a] > cost[c]; });
-  finalize_program(hp);
+  finalize_program(hp, b, RB);
   return "";
 }
 
@@ -148,9 +148,6 @@ std::string append_variant(int w, const std::vector<HostGate>& G, int b,
       hp->tiles += uint64_t(1) << (w - p.L);
       bc.n_passes = 1;
     }
-    for (int p = 0; p < bc.n_passes; ++p)
-      set_lds_offsets(batch_lds_map(b, RB), RB,
-                      &hp->passes[size_t(bc.pass_begin + p)], hp->segs.data());
     if (hp->out_offsets.empty()) hp->out_offsets.push_back(0);
     bc.out_offset = hp->out_offsets[i];
     hp->out_offsets.push_back(hp->out_offsets[i] + (uint64_t(1) << w));
@@ -163,7 +160,7 @@ std::string append_variant(int w, const std::vector<HostGate>& G, int b,
   return "";
 }
 
-void finalize_program(HostProgram* hp) {
+void finalize_program(HostProgram* hp, int b, int RB) {
   const size_t n = hp->circs.size();
   std::vector<int32_t> ord = hp->order;
   if (ord.size() != n) {
@@ -215,6 +212,12 @@ void finalize_program(HostProgram* hp) {
     hp->phase_tiles.push_back(tiles);
     hp->phase_cost.push_back(cost);
   }
+  uint64_t most = 0;
+  for (uint64_t t : hp->phase_tiles) most = std::max(most, t);
+  hp->whole = batch_whole(b, RB, most);
+  const LdsMap map = b == 16 ? kLds16 : hp->whole ? kLds8 : kLds4;
+  for (TilePass& tp : hp->passes)
+    set_lds_offsets(map, RB, &tp, hp->segs.data());
 }
 
 }  // namespace qsv

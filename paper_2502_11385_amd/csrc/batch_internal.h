@@ -30,21 +30,26 @@ struct HostProgram {
   std::vector<uint64_t> phase_tiles;       // tiles per phase
   std::vector<uint64_t> phase_cost;        // summed tile cost per phase
   uint64_t state_amps = 0;
+  bool whole = true;  // re-layouts a whole amplitude at a time
 };
 
-// Lay out the states of multi-pass variants and list each phase's tile
-// runs (variants in hp->order, or in index order when it is empty).
-void finalize_program(HostProgram* hp);
+// Lay out the states of multi-pass variants, list each phase's tile
+// runs (variants in hp->order, or in index order when it is empty), and
+// choose how the tiles re-lay out.
+void finalize_program(HostProgram* hp, int b, int RB);
 
 // Plan one variant (validated gates G on w qubits, started in |0...0>) and
 // append it to hp; *cost (may be null) receives its estimated work.
 std::string append_variant(int w, const std::vector<HostGate>& G, int b,
                            int L, int RB, HostProgram* hp, double* cost);
 
-// The LDS map of the batch kernel's re-layouts (amplitude bytes, register
-// bits).
-inline LdsMap batch_lds_map(int b, int rb) {
-  return b == 16 ? kLds16 : (rb == 4 ? kLds4 : kLds8);
+// Whether tiles re-lay out whole or, complex64 with 16 registers, in halves,
+// by the tiles of the largest phase (amplitude bytes, register bits).  Whole
+// is faster while the tiles are few (150 tiles of 12 qubits 271 -> 231 us, 512
+// tiles 551 -> 504, 1568 tiles 985 -> 953); with many, the smaller LDS is
+// (192 variants, 21000 tiles: 3.56 ms in halves, 3.95 whole).
+inline bool batch_whole(int b, int rb, uint64_t phase_tiles) {
+  return b == 16 || rb != 4 || phase_tiles <= 2048;
 }
 
 // True when every gate can run inside batched tiles.

@@ -19,7 +19,7 @@
 
 namespace qsv {
 
-template <typename T, typename OUT, int RB>
+template <typename T, typename OUT, int RB, bool HALVES>
 __device__ __forceinline__ void batch_phase_body(
     const BatchCircuit* __restrict__ circs, const TilePass* __restrict__ passes,
     const TileSeg* __restrict__ segs, const TileOp* __restrict__ ops,
@@ -104,9 +104,7 @@ __device__ __forceinline__ void batch_phase_body(
           a[j].y = T(0);
         }
       }
-      // complex64 with 16 registers re-lays out in halves (half the LDS)
-      tile_apply<T, RB, sizeof(T) == 4 && RB == 4>(a, pass, segs, ops, base,
-                                                  tid, active);
+      tile_apply<T, RB, HALVES>(a, pass, segs, ops, base, tid, active);
 #pragma unroll
       for (int i = 0; i < RB; ++i) asm volatile("" : "+s"(step[i]));
       if (active) {
@@ -141,12 +139,13 @@ __global__ void __launch_bounds__(256)
                        uint64_t n_tiles, uint64_t n_cost, int phase,
                        OUT* __restrict__ out,
                        typename CxT<T>::type* __restrict__ states) {
-  batch_phase_body<T, OUT, RB>(circs, passes, segs, ops, work, n_work,
+  batch_phase_body<T, OUT, RB, false>(circs, passes, segs, ops, work, n_work,
                                n_tiles, n_cost, phase, out, states);
 }
 
-// complex64 with 16 registers per thread: capped at 128 VGPRs so that four
-// waves share each SIMD.
+// complex64 with 16 registers per thread, re-laid out in halves: capped at 128
+// VGPRs so that at least four waves share each SIMD (the build reaches 89,
+// five).
 template <typename OUT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
     batch_phase_kernel_c64_rb4(const BatchCircuit* __restrict__ circs,
@@ -158,27 +157,26 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
                                uint64_t n_cost, int phase,
                                OUT* __restrict__ out,
                                float2* __restrict__ states) {
-  batch_phase_body<float, OUT, 4>(circs, passes, segs, ops, work, n_work,
-                                  n_tiles, n_cost, phase, out, states);
+  batch_phase_body<float, OUT, 4, true>(circs, passes, segs, ops, work,
+                                        n_work, n_tiles, n_cost, phase, out,
+                                        states);
 }
 
-template <typename T, typename OUT, int RB>
-static const void* batch_fn() {
-  if constexpr (sizeof(T) == 4 && RB == 4)
-    return reinterpret_cast<const void*>(&batch_phase_kernel_c64_rb4<OUT>);
+template <typename T, typename OUT, int RB, bool HALVES>
+static auto batch_fn() {
+  if constexpr (HALVES)
+    return &batch_phase_kernel_c64_rb4<OUT>;
   else
-    return reinterpret_cast<const void*>(&batch_phase_kernel<T, OUT, RB>);
+    return &batch_phase_kernel<T, OUT, RB>;
 }
 
-// LDS of one work-group: the tile, at 4 bytes per amplitude where the
-// re-layouts go in halves (complex64, 16 registers per thread).
-template <typename T, int RB>
+// LDS of one work-group: the tile, or one component per amplitude.
+template <typename T, bool HALVES>
 static size_t batch_lds_bytes(int L) {
-  using C = typename CxT<T>::type;
-  return (sizeof(T) == 4 && RB == 4) ? size_t(4) << L : size_t(sizeof(C)) << L;
+  return (HALVES ? sizeof(T) : 2 * sizeof(T)) << L;
 }
 
-template <typename T, typename OUT, int RB>
+template <typename T, typename OUT, int RB, bool HALVES>
 static hipError_t batch_launch_t(const BatchCircuit* circs,
                                  const TilePass* passes, const TileSeg* segs,
                                  const TileOp* ops, const BatchWork* work,
@@ -191,12 +189,13 @@ static hipError_t batch_launch_t(const BatchCircuit* circs,
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [] {
-    attr_err = hipFuncSetAttribute(batch_fn<T, OUT, RB>(),
+    attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(
+                                       batch_fn<T, OUT, RB, HALVES>()),
                                    hipFuncAttributeMaxDynamicSharedMemorySize,
                                    160 * 1024);
   });
   if (attr_err != hipSuccess) return attr_err;
-  const size_t lds = batch_lds_bytes<T, RB>(L);
+  const size_t lds = batch_lds_bytes<T, HALVES>(L);
   const size_t phases = hp.phase_tiles.size();
   for (size_t p = 0; p < phases; ++p) {
     const uint64_t tiles = hp.phase_tiles[p];
@@ -204,30 +203,25 @@ static hipError_t batch_launch_t(const BatchCircuit* circs,
     const uint64_t wb = hp.phase_work_begin[p];
     const uint32_t nw = uint32_t(hp.phase_work_begin[p + 1] - wb);
     const unsigned g = unsigned(tiles < uint64_t(grid) ? tiles : uint64_t(grid));
-    if constexpr (sizeof(T) == 4 && RB == 4)
-      batch_phase_kernel_c64_rb4<OUT><<<g, 256, lds, stream>>>(
-          circs, passes, segs, ops, work + wb, nw, tiles, hp.phase_cost[p],
-          int(p), static_cast<OUT*>(out), static_cast<C*>(states));
-    else
-      batch_phase_kernel<T, OUT, RB><<<g, 256, lds, stream>>>(
-          circs, passes, segs, ops, work + wb, nw, tiles, hp.phase_cost[p],
-          int(p), static_cast<OUT*>(out), static_cast<C*>(states));
+    batch_fn<T, OUT, RB, HALVES>()<<<g, 256, lds, stream>>>(
+        circs, passes, segs, ops, work + wb, nw, tiles, hp.phase_cost[p],
+        int(p), static_cast<OUT*>(out), static_cast<C*>(states));
   }
   return hipGetLastError();
 }
 
-// Resident work-groups per CU of the batch kernel for (prec, out, rb, L).
-// (Its LDS: batch_lds_bytes.)
+// Resident work-groups per CU of the batch kernel for (prec, out, rb, L), the
+// kernel of a large batch.
 template <typename T, typename OUT, int RB>
 static int batch_occupancy_t(int L) {
-  using C = typename CxT<T>::type;
-  (void)hipFuncSetAttribute(batch_fn<T, OUT, RB>(),
-                            hipFuncAttributeMaxDynamicSharedMemorySize,
+  constexpr bool HALVES = sizeof(T) == 4 && RB == 4;
+  const void* fn =
+      reinterpret_cast<const void*>(batch_fn<T, OUT, RB, HALVES>());
+  (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                             160 * 1024);
   int n = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &n, batch_fn<T, OUT, RB>(), 256, batch_lds_bytes<T, RB>(L)) !=
-      hipSuccess) {
+          &n, fn, 256, batch_lds_bytes<T, HALVES>(L)) != hipSuccess) {
     (void)hipGetLastError();
     return 0;
   }
@@ -253,19 +247,23 @@ hipError_t launch_batch(int prec, int out_fp64, int rb,
                         void* out, void* states, int L, int grid,
                         hipStream_t stream) {
   if (L - rb < 0 || L - rb > 8 || grid < 1) return hipErrorInvalidValue;
-#define QSV_B(T, O, RBV)                                                  \
-  return batch_launch_t<T, O, RBV>(circs, passes, segs, ops, work, hp, out, \
-                                   states, L, grid, stream)
+#define QSV_B(T, O, RBV, HALVES)                                             \
+  return batch_launch_t<T, O, RBV, HALVES>(circs, passes, segs, ops, work, hp, \
+                                           out, states, L, grid, stream)
   if (prec == 1) {
-    if (out_fp64) {
-      if (rb == 4) QSV_B(float, double, 4);
-      QSV_B(float, double, 5);
+    if (rb != 4) {
+      if (out_fp64) QSV_B(float, double, 5, false);
+      QSV_B(float, float, 5, false);
     }
-    if (rb == 4) QSV_B(float, float, 4);
-    QSV_B(float, float, 5);
+    if (hp.whole) {
+      if (out_fp64) QSV_B(float, double, 4, false);
+      QSV_B(float, float, 4, false);
+    }
+    if (out_fp64) QSV_B(float, double, 4, true);
+    QSV_B(float, float, 4, true);
   }
-  if (out_fp64) QSV_B(double, double, 4);
-  QSV_B(double, float, 4);
+  if (out_fp64) QSV_B(double, double, 4, false);
+  QSV_B(double, float, 4, false);
 #undef QSV_B
 }
 

@@ -266,7 +266,7 @@ void launch_batched(qsv_server s, Group* g, int prec) {
       return;
     }
   }
-  finalize_program(&hp);  // variants in submission order
+  finalize_program(&hp, b, RB);  // variants in submission order
   std::vector<char> img;
   const size_t o_c = put_vec(img, hp.circs), o_w = put_vec(img, hp.work),
                o_p = put_vec(img, hp.passes), o_s = put_vec(img, hp.segs),

@@ -382,7 +382,7 @@ __device__ __forceinline__ void lds_load(uint32_t at, C& v) {
 }
 
 // LDS map of a tile's re-layouts (the host filled the register offsets of
-// the same one: tile_lds_map, batch_lds_map).
+// the same one: tile_lds_map, finalize_program).
 template <typename T, bool HALVES>
 constexpr LdsMap lds_map() {
   return sizeof(T) == 4 ? (HALVES ? kLds4 : kLds8) : (HALVES ? kLds8 : kLds16);

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 import oracle
-from circuits import random_state
+from circuits import batch_variants, random_state
 
 torch = pytest.importorskip("torch")
 from paper_2502_11385_amd import qsv  # noqa: E402
@@ -86,3 +86,25 @@ def test_whole_and_half_relayouts(prec, n, tile):
                                       reg_log2=4))
     assert np.max(np.abs(s.get() - want)) <= TOL[prec]
     s.free()
+
+
+def test_batches_on_both_sides_of_the_relayout_line():
+    """The same variants in a batch of few tiles (whole re-layouts) and of
+    more than 2048 (halves, complex64): the oracle's vectors, the same bits."""
+    vs = batch_variants(count=2, seed=5, wmin=18, wmax=18, dmin=3, dmax=4)
+    got = []
+    for copies in (1, 20):
+        b = qsv.Batch(vs * copies, prec=C64)
+        out = b.output()
+        b.launch(out)
+        torch.cuda.synchronize()
+        got.append(out.cpu().numpy())
+        assert (int(b.offsets[-1]) >> 12 > 2048) == (copies == 20)
+        b.free()
+    size = got[0].size
+    for c in range(20):
+        assert np.array_equal(got[1][c * size:(c + 1) * size], got[0]), c
+    for i, v in enumerate(vs):
+        want = oracle.variant_probabilities(v)
+        p = got[0][i << 18:(i + 1) << 18].astype(np.float64)
+        assert np.max(np.abs(p - want)) <= 2e-6
