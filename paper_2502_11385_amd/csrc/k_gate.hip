@@ -271,55 +271,59 @@ struct DiagArgs {
   double d[64];         // diagonal entries (re, im); masked: d[0..1] = phase
 };
 
-// Masked phase: multiply the amplitudes whose bits in fixed_mask and in
-// lowmask are all 1 (SKIP: a lane whose lowmask bits are not leaves its
-// amplitude alone; otherwise it stores it back unchanged).
-template <typename T, bool SKIP>
+// Multiply amplitudes by a diagonal's factor where the controls (fixed_mask
+// and lowmask) are satisfied: by one phase (masked: the targets are in the
+// masks as well), or by d[r(i)], r the target bits (TABLE).  SKIP: a lane whose
+// lowmask bits are not all 1 leaves its amplitude alone; otherwise it stores
+// it back unchanged.  Bound by the amplitudes' bytes: each thread has U
+// loads in flight, and the table is read from LDS (a lane-dependent index
+// into the kernel arguments was one more dependent load per amplitude:
+// 27 qubits complex64, one target, 460 us).
+template <typename T, bool TABLE, bool SKIP, int U>
 __global__ void __launch_bounds__(256)
-    diag_masked_kernel(typename CxT<T>::type* __restrict__ a, DiagArgs args) {
+    diag_kernel(typename CxT<T>::type* __restrict__ a, DiagArgs args) {
   using C = typename CxT<T>::type;
+  __shared__ C tab[TABLE ? 1 << kMaxK : 1];
+  if constexpr (TABLE) {
+    if (threadIdx.x < 1u << args.k) {
+      C f;
+      f.x = T(args.d[2 * threadIdx.x]);
+      f.y = T(args.d[2 * threadIdx.x + 1]);
+      tab[threadIdx.x] = f;
+    }
+    __syncthreads();
+  }
   C ph;
   ph.x = T(args.d[0]);
   ph.y = T(args.d[1]);
-  const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-  for (uint64_t g = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  const uint64_t stride = uint64_t(gridDim.x) * (256 * U);
+  for (uint64_t g = uint64_t(blockIdx.x) * (256 * U) + threadIdx.x;
        g < args.n_items; g += stride) {
-    uint64_t i = g;
-    for (int p = 0; p < args.npos; ++p) i = insert_zero64(i, args.pos[p]);
-    i |= args.fixed_mask;
-    const C v = a[i];
-    const bool on = (i & args.lowmask) == args.lowmask;
-    if constexpr (SKIP) {
-      if (on) a[i] = cmul(v, ph);
-    } else {
-      a[i] = on ? cmul(v, ph) : v;
+    uint64_t i[U];
+    C v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      i[u] = g + 256 * u;
+      for (int p = 0; p < args.npos; ++p)
+        i[u] = insert_zero64(i[u], args.pos[p]);
+      i[u] |= args.fixed_mask;
+      v[u] = a[i[u]];
     }
-  }
-}
-
-// General diagonal: multiply by d[r(i)], r the target bits, where the
-// controls (fixed_mask and lowmask) are satisfied.
-template <typename T, bool SKIP>
-__global__ void __launch_bounds__(256)
-    diag_table_kernel(typename CxT<T>::type* __restrict__ a, DiagArgs args) {
-  using C = typename CxT<T>::type;
-  const uint64_t stride = uint64_t(gridDim.x) * blockDim.x;
-  for (uint64_t g = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-       g < args.n_items; g += stride) {
-    uint64_t i = g;
-    for (int p = 0; p < args.npos; ++p) i = insert_zero64(i, args.pos[p]);
-    i |= args.fixed_mask;
-    int r = 0;
-    for (int j = 0; j < args.k; ++j) r |= int((i >> args.tq[j]) & 1) << j;
-    C f;
-    f.x = T(args.d[2 * r]);
-    f.y = T(args.d[2 * r + 1]);
-    const C v = a[i];
-    const bool on = (i & args.lowmask) == args.lowmask;
-    if constexpr (SKIP) {
-      if (on) a[i] = cmul(v, f);
-    } else {
-      a[i] = on ? cmul(v, f) : v;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      C f = ph;
+      if constexpr (TABLE) {
+        int r = 0;
+        for (int j = 0; j < args.k; ++j)
+          r |= int((i[u] >> args.tq[j]) & 1) << j;
+        f = tab[r];
+      }
+      const bool on = (i[u] & args.lowmask) == args.lowmask;
+      if constexpr (SKIP) {
+        if (on) a[i[u]] = cmul(v[u], f);
+      } else {
+        a[i[u]] = on ? cmul(v[u], f) : v[u];
+      }
     }
   }
 }
@@ -347,29 +351,24 @@ hipError_t launch_diag(int prec, void* amp, int n, const HostGate& g,
   args.fixed_mask &= ~args.lowmask;
   sorted_positions(args.fixed_mask, args.pos, &args.npos);
   args.n_items = uint64_t(1) << (n - args.npos);
-  const unsigned blocks = grid_blocks(args.n_items, 256);
-#define QSV_DIAG(KERNEL, T)                                              \
-  do {                                                                   \
-    using C = typename CxT<T>::type;                                     \
-    if (skip)                                                            \
-      KERNEL<T, true><<<blocks, 256, 0, stream>>>(static_cast<C*>(amp),  \
-                                                  args);                 \
-    else                                                                 \
-      KERNEL<T, false><<<blocks, 256, 0, stream>>>(static_cast<C*>(amp), \
-                                                   args);                \
-  } while (0)
-  if (g.masked_phase) {
-    if (prec == 1)
-      QSV_DIAG(diag_masked_kernel, float);
-    else
-      QSV_DIAG(diag_masked_kernel, double);
-  } else {
-    if (prec == 1)
-      QSV_DIAG(diag_table_kernel, float);
-    else
-      QSV_DIAG(diag_table_kernel, double);
-  }
+  // four amplitudes per thread once that leaves every CU a work-group (n_items
+  // is a power of two, so that the chunks of 1024 are full)
+  const bool wide = args.n_items >= uint64_t(1) << 18;
+  const unsigned blocks = grid_blocks(args.n_items, wide ? 1024 : 256);
+#define QSV_DIAG_U(T, TABLE, SKIP, U)                                       \
+  diag_kernel<T, TABLE, SKIP, U><<<blocks, 256, 0, stream>>>(               \
+      static_cast<CxT<T>::type*>(amp), args)
+#define QSV_DIAG_S(T, TABLE, SKIP)                                          \
+  (wide ? QSV_DIAG_U(T, TABLE, SKIP, 4) : QSV_DIAG_U(T, TABLE, SKIP, 1))
+#define QSV_DIAG(T, TABLE)                                                  \
+  (skip ? QSV_DIAG_S(T, TABLE, true) : QSV_DIAG_S(T, TABLE, false))
+  if (g.masked_phase)
+    prec == 1 ? QSV_DIAG(float, false) : QSV_DIAG(double, false);
+  else
+    prec == 1 ? QSV_DIAG(float, true) : QSV_DIAG(double, true);
 #undef QSV_DIAG
+#undef QSV_DIAG_S
+#undef QSV_DIAG_U
   return hipGetLastError();
 }
 
