@@ -98,7 +98,7 @@ enum LowMode { kLowNone, kLowKeep, kLowSkip };
 
 // PTR: the matrix comes from device memory (FP64, rounded once to T while
 // staged in LDS); otherwise from the kernel arguments (k <= 2).
-template <typename T, int K, bool PTR, int LOW>
+template <typename T, int K, bool PTR, int LOW, bool NT>
 __global__ void __launch_bounds__(256)
     dense_kernel(typename CxT<T>::type* __restrict__ a, DenseArgs args) {
   using C = typename CxT<T>::type;
@@ -132,7 +132,7 @@ __global__ void __launch_bounds__(256)
         LOW == kLowNone || (base & args.lowmask) == args.lowmask;
     C v[D];
 #pragma unroll
-    for (int r = 0; r < D; ++r) v[r] = a[base + off[r]];
+    for (int r = 0; r < D; ++r) v[r] = stream_load<NT>(a + base + off[r]);
     // All inputs are in registers, so each output can be stored at once.
 #pragma unroll
     for (int r = 0; r < D; ++r) {
@@ -154,14 +154,14 @@ __global__ void __launch_bounds__(256)
       w.x = re;
       w.y = im;
       if constexpr (LOW == kLowKeep)
-        a[base + off[r]] = on ? w : v[r];
+        stream_store<NT>(a + base + off[r], on ? w : v[r]);
       else if (on)
-        a[base + off[r]] = w;
+        stream_store<NT>(a + base + off[r], w);
     }
   }
 }
 
-template <typename T, int LOW>
+template <typename T, int LOW, bool NT>
 static void dense_dispatch_t(void* amp, int k, unsigned blocks,
                              const DenseArgs& args, hipStream_t stream) {
   using C = typename CxT<T>::type;
@@ -170,37 +170,46 @@ static void dense_dispatch_t(void* amp, int k, unsigned blocks,
   switch (k) {
     case 1:
       if (ptr)
-        dense_kernel<T, 1, true, LOW><<<blocks, 256, 0, stream>>>(a, args);
+        dense_kernel<T, 1, true, LOW, NT><<<blocks, 256, 0, stream>>>(a, args);
       else
-        dense_kernel<T, 1, false, LOW><<<blocks, 256, 0, stream>>>(a, args);
+        dense_kernel<T, 1, false, LOW, NT><<<blocks, 256, 0, stream>>>(a, args);
       break;
     case 2:
       if (ptr)
-        dense_kernel<T, 2, true, LOW><<<blocks, 256, 0, stream>>>(a, args);
+        dense_kernel<T, 2, true, LOW, NT><<<blocks, 256, 0, stream>>>(a, args);
       else
-        dense_kernel<T, 2, false, LOW><<<blocks, 256, 0, stream>>>(a, args);
+        dense_kernel<T, 2, false, LOW, NT><<<blocks, 256, 0, stream>>>(a, args);
       break;
     case 3:
-      dense_kernel<T, 3, true, LOW><<<blocks, 256, 0, stream>>>(a, args);
+      dense_kernel<T, 3, true, LOW, NT><<<blocks, 256, 0, stream>>>(a, args);
       break;
   }
 }
 
-template <typename T>
-static void dense_dispatch(void* amp, int k, unsigned blocks,
-                           const DenseArgs& args, hipStream_t stream) {
+template <typename T, bool NT>
+static void dense_dispatch_nt(void* amp, int k, unsigned blocks,
+                              const DenseArgs& args, hipStream_t stream) {
   constexpr LowBits lb = sizeof(T) == 4 ? kDenseLowC64 : kDenseLowC128;
   if constexpr (lb.keep | lb.skip) {
     if (args.lowmask & lb.keep) {
-      dense_dispatch_t<T, kLowKeep>(amp, k, blocks, args, stream);
+      dense_dispatch_t<T, kLowKeep, NT>(amp, k, blocks, args, stream);
       return;
     }
     if (args.lowmask) {
-      dense_dispatch_t<T, kLowSkip>(amp, k, blocks, args, stream);
+      dense_dispatch_t<T, kLowSkip, NT>(amp, k, blocks, args, stream);
       return;
     }
   }
-  dense_dispatch_t<T, kLowNone>(amp, k, blocks, args, stream);
+  dense_dispatch_t<T, kLowNone, NT>(amp, k, blocks, args, stream);
+}
+
+template <typename T>
+static void dense_dispatch(void* amp, int n, int k, unsigned blocks,
+                           const DenseArgs& args, hipStream_t stream) {
+  if ((2 * sizeof(T) << n) > kStreamBytes)
+    dense_dispatch_nt<T, true>(amp, k, blocks, args, stream);
+  else
+    dense_dispatch_nt<T, false>(amp, k, blocks, args, stream);
 }
 
 static void sorted_positions(uint64_t mask, int32_t* pos, int32_t* npos) {
@@ -229,9 +238,9 @@ hipError_t launch_dense(int prec, void* amp, int n, const HostGate& g,
   }
   const unsigned blocks = grid_blocks(args.n_groups, 256);
   if (prec == 1)
-    dense_dispatch<float>(amp, g.k, blocks, args, stream);
+    dense_dispatch<float>(amp, n, g.k, blocks, args, stream);
   else
-    dense_dispatch<double>(amp, g.k, blocks, args, stream);
+    dense_dispatch<double>(amp, n, g.k, blocks, args, stream);
   return hipGetLastError();
 }
 
@@ -252,9 +261,9 @@ hipError_t launch_dense_dev(int prec, void* amp, int n, int k,
   args.mptr = dev_matrix;
   const unsigned blocks = grid_blocks(args.n_groups, 256);
   if (prec == 1)
-    dense_dispatch<float>(amp, k, blocks, args, stream);
+    dense_dispatch<float>(amp, n, k, blocks, args, stream);
   else
-    dense_dispatch<double>(amp, k, blocks, args, stream);
+    dense_dispatch<double>(amp, n, k, blocks, args, stream);
   return hipGetLastError();
 }
 
@@ -279,7 +288,7 @@ struct DiagArgs {
 // loads in flight, and the table is read from LDS (a lane-dependent index
 // into the kernel arguments was one more dependent load per amplitude:
 // 27 qubits complex64, one target, 460 us).
-template <typename T, bool TABLE, bool SKIP, int U>
+template <typename T, bool TABLE, bool SKIP, int U, bool NT>
 __global__ void __launch_bounds__(256)
     diag_kernel(typename CxT<T>::type* __restrict__ a, DiagArgs args) {
   using C = typename CxT<T>::type;
@@ -307,7 +316,7 @@ __global__ void __launch_bounds__(256)
       for (int p = 0; p < args.npos; ++p)
         i[u] = insert_zero64(i[u], args.pos[p]);
       i[u] |= args.fixed_mask;
-      v[u] = a[i[u]];
+      v[u] = stream_load<NT>(a + i[u]);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -320,9 +329,9 @@ __global__ void __launch_bounds__(256)
       }
       const bool on = (i[u] & args.lowmask) == args.lowmask;
       if constexpr (SKIP) {
-        if (on) a[i[u]] = cmul(v[u], f);
+        if (on) stream_store<NT>(a + i[u], cmul(v[u], f));
       } else {
-        a[i[u]] = on ? cmul(v[u], f) : v[u];
+        stream_store<NT>(a + i[u], on ? cmul(v[u], f) : v[u]);
       }
     }
   }
@@ -354,12 +363,16 @@ hipError_t launch_diag(int prec, void* amp, int n, const HostGate& g,
   // four amplitudes per thread once that leaves every CU a work-group (n_items
   // is a power of two, so that the chunks of 1024 are full)
   const bool wide = args.n_items >= uint64_t(1) << 18;
+  const bool nt =
+      wide && (uint64_t(prec == 1 ? 8 : 16) << n) > kStreamBytes;
   const unsigned blocks = grid_blocks(args.n_items, wide ? 1024 : 256);
-#define QSV_DIAG_U(T, TABLE, SKIP, U)                                       \
-  diag_kernel<T, TABLE, SKIP, U><<<blocks, 256, 0, stream>>>(               \
+#define QSV_DIAG_U(T, TABLE, SKIP, U, NT)                                   \
+  diag_kernel<T, TABLE, SKIP, U, NT><<<blocks, 256, 0, stream>>>(               \
       static_cast<CxT<T>::type*>(amp), args)
 #define QSV_DIAG_S(T, TABLE, SKIP)                                          \
-  (wide ? QSV_DIAG_U(T, TABLE, SKIP, 4) : QSV_DIAG_U(T, TABLE, SKIP, 1))
+  (nt     ? QSV_DIAG_U(T, TABLE, SKIP, 4, true)                             \
+   : wide ? QSV_DIAG_U(T, TABLE, SKIP, 4, false)                            \
+          : QSV_DIAG_U(T, TABLE, SKIP, 1, false))
 #define QSV_DIAG(T, TABLE)                                                  \
   (skip ? QSV_DIAG_S(T, TABLE, true) : QSV_DIAG_S(T, TABLE, false))
   if (g.masked_phase)

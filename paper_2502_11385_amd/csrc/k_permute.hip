@@ -17,37 +17,6 @@
 
 namespace qsv {
 
-// A state larger than the last-level cache (256 MiB) is streamed past it:
-// non-temporal accesses copy 2 GiB at 5.7 TB/s where plain ones reach 5.3
-// and the runtime's copy 4.5 to 5.5.  Smaller ones stay cached for the pass
-// that follows.
-constexpr uint64_t kStreamBytes = uint64_t(256) << 20;
-
-template <bool NT, typename C>
-__device__ __forceinline__ C stream_load(const C* p) {
-  using E = decltype(p->x);
-  typedef E V __attribute__((ext_vector_type(2)));
-  if constexpr (!NT) return *p;
-  const V v = __builtin_nontemporal_load(reinterpret_cast<const V*>(p));
-  C r;
-  r.x = v.x;
-  r.y = v.y;
-  return r;
-}
-template <bool NT, typename C>
-__device__ __forceinline__ void stream_store(C* p, const C& c) {
-  using E = decltype(p->x);
-  typedef E V __attribute__((ext_vector_type(2)));
-  if constexpr (!NT) {
-    *p = c;
-  } else {
-    V v;
-    v.x = c.x;
-    v.y = c.y;
-    __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
-  }
-}
-
 // Copy of a state (16-byte elements, 8 in flight per thread).
 template <bool NT>
 __global__ void __launch_bounds__(256)
