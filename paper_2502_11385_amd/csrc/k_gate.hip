@@ -203,10 +203,23 @@ static void dense_dispatch_nt(void* amp, int k, unsigned blocks,
   dense_dispatch_t<T, kLowNone, NT>(amp, k, blocks, args, stream);
 }
 
+// Whether a pass over a state of n qubits streams past the cache: the state
+// is larger than it, and a wave's accesses, in runs of 2^low amplitudes
+// (`low`: the lowest bit inserted into its indexes), cover whole 128-byte
+// lines.  Where they cover a line in parts, it has to stay cached between
+// them: 30 qubits complex64, targets 0, 7 and 22, 4.63 ms streamed and 3.2
+// cached.
+// Where they do, one-target gates on 29 qubits complex64 gain 6 to 12 %, on 28
+// qubits complex128 5 to 7 %.
+template <typename T>
+static bool streamed(int n, int low) {
+  return (2 * sizeof(T) << n) > kStreamBytes && (2 * sizeof(T) << low) >= 128;
+}
+
 template <typename T>
 static void dense_dispatch(void* amp, int n, int k, unsigned blocks,
                            const DenseArgs& args, hipStream_t stream) {
-  if ((2 * sizeof(T) << n) > kStreamBytes)
+  if (streamed<T>(n, args.npos ? args.pos[0] : n))
     dense_dispatch_nt<T, true>(amp, k, blocks, args, stream);
   else
     dense_dispatch_nt<T, false>(amp, k, blocks, args, stream);
@@ -360,27 +373,31 @@ hipError_t launch_diag(int prec, void* amp, int n, const HostGate& g,
   args.fixed_mask &= ~args.lowmask;
   sorted_positions(args.fixed_mask, args.pos, &args.npos);
   args.n_items = uint64_t(1) << (n - args.npos);
-  // four amplitudes per thread once that leaves every CU a work-group (n_items
-  // is a power of two, so that the chunks of 1024 are full)
-  const bool wide = args.n_items >= uint64_t(1) << 18;
-  const bool nt =
-      wide && (uint64_t(prec == 1 ? 8 : 16) << n) > kStreamBytes;
+  // complex64: four amplitudes per thread once that leaves every CU a
+  // work-group (n_items is a power of two, so that the chunks of 1024 are
+  // full), and streamed where `streamed` says so.  complex128 gained nothing
+  // from either (28 qubits, one-target table 1.44 and 1.43 ms) and lost under
+  // low bits (CZ(3, 27) 0.37 -> 0.54), complex64 lost where lanes skip
+  // (CZ(3, 4) on 29 qubits 0.67 -> 0.76): those take one.
+  const bool wide = prec == 1 && !skip && args.n_items >= uint64_t(1) << 18;
+  const bool nt = wide && streamed<float>(n, args.npos ? args.pos[0] : n);
   const unsigned blocks = grid_blocks(args.n_items, wide ? 1024 : 256);
 #define QSV_DIAG_U(T, TABLE, SKIP, U, NT)                                   \
-  diag_kernel<T, TABLE, SKIP, U, NT><<<blocks, 256, 0, stream>>>(               \
+  diag_kernel<T, TABLE, SKIP, U, NT><<<blocks, 256, 0, stream>>>(           \
       static_cast<CxT<T>::type*>(amp), args)
-#define QSV_DIAG_S(T, TABLE, SKIP)                                          \
-  (nt     ? QSV_DIAG_U(T, TABLE, SKIP, 4, true)                             \
-   : wide ? QSV_DIAG_U(T, TABLE, SKIP, 4, false)                            \
-          : QSV_DIAG_U(T, TABLE, SKIP, 1, false))
 #define QSV_DIAG(T, TABLE)                                                  \
-  (skip ? QSV_DIAG_S(T, TABLE, true) : QSV_DIAG_S(T, TABLE, false))
+  (skip ? QSV_DIAG_U(T, TABLE, true, 1, false)                              \
+        : QSV_DIAG_U(T, TABLE, false, 1, false))
+#define QSV_DIAG_WIDE(TABLE)                                                \
+  (nt     ? QSV_DIAG_U(float, TABLE, false, 4, true)                        \
+   : wide ? QSV_DIAG_U(float, TABLE, false, 4, false)                       \
+          : QSV_DIAG(float, TABLE))
   if (g.masked_phase)
-    prec == 1 ? QSV_DIAG(float, false) : QSV_DIAG(double, false);
+    prec == 1 ? QSV_DIAG_WIDE(false) : QSV_DIAG(double, false);
   else
-    prec == 1 ? QSV_DIAG(float, true) : QSV_DIAG(double, true);
+    prec == 1 ? QSV_DIAG_WIDE(true) : QSV_DIAG(double, true);
+#undef QSV_DIAG_WIDE
 #undef QSV_DIAG
-#undef QSV_DIAG_S
 #undef QSV_DIAG_U
   return hipGetLastError();
 }
