@@ -378,9 +378,13 @@ hipError_t launch_diag(int prec, void* amp, int n, const HostGate& g,
   // full), and streamed where `streamed` says so.  complex128 gained nothing
   // from either (28 qubits, one-target table 1.44 and 1.43 ms) and lost under
   // low bits (CZ(3, 27) 0.37 -> 0.54), complex64 lost where lanes skip
-  // (CZ(3, 4) on 29 qubits 0.67 -> 0.76): those take one.
-  const bool wide = prec == 1 && !skip && args.n_items >= uint64_t(1) << 18;
-  const bool nt = wide && streamed<float>(n, args.npos ? args.pos[0] : n);
+  // (CZ(3, 4) on 29 qubits 0.67 -> 0.76) and where the runs between the fixed
+  // bits do not cover whole lines (CZ(2, 3) 1.22 -> 1.50; with lane-tested bits
+  // below, runs of one line neither gained nor lost): those take one.
+  const int low = args.npos ? args.pos[0] : n;
+  const bool wide = prec == 1 && !skip && low >= (args.lowmask ? 5 : 4) &&
+                    args.n_items >= uint64_t(1) << 18;
+  const bool nt = wide && streamed<float>(n, low);
   const unsigned blocks = grid_blocks(args.n_items, wide ? 1024 : 256);
 #define QSV_DIAG_U(T, TABLE, SKIP, U, NT)                                   \
   diag_kernel<T, TABLE, SKIP, U, NT><<<blocks, 256, 0, stream>>>(           \
