@@ -1822,13 +1822,12 @@ qsv_status qsv_top_k(qsv_state s, uint32_t k, uint64_t* idx_out,
   auto* toff = reinterpret_cast<unsigned long long*>(sc + o_to);
   std::vector<uint64_t> keys, idx;
   unsigned long long found[4];
-  QSV_HIP(s, launch_topk_select(s->prec, s->amp, count, k,
-                                reinterpret_cast<unsigned int*>(sc), counter,
-                                cap, dkey, didx, s->stream));
+  QSV_HIP(s, launch_topk_select(s->prec, s->amp, count, k, hist, counter, cap,
+                                dkey, didx, s->stream));
   QSV_HIP(s, hipMemcpyAsync(found, counter, sizeof found,
                             hipMemcpyDeviceToHost, s->stream));
   QSV_HIP(s, hipStreamSynchronize(s->stream));
-  if (found[1] + found[2] <= cap) {
+  if (found[1] + found[2] >= k && found[1] + found[2] <= cap) {
     const size_t m = size_t(found[1] + found[2]);
     keys.resize(m);
     idx.resize(m);

@@ -193,11 +193,12 @@ hipError_t launch_marginal(int prec, const void* amp, int n,
 size_t sample_scratch_bytes(int n, uint64_t shots);
 // top-k and Pauli expectations (k_outputs.hip)
 // Two passes over the state: found[0..2] = the k-th largest key's bin (the
-// key's top 16 bits), the keys above that bin and those in it; if these are
-// at most cap together, out_key/out_idx receive all of them in no order.
+// key's top 16 bits), the keys above that bin and those in it (zeros before
+// the search); if these are at most cap together, out_key/out_idx receive all
+// of them in no order.
 size_t topk_hist_bytes();
 hipError_t launch_topk_select(int prec, const void* amp, uint64_t count,
-                              uint64_t k, unsigned int* hist,
+                              uint64_t k, unsigned long long* hist,
                               unsigned long long* found, uint64_t cap,
                               uint64_t* out_key, uint64_t* out_idx,
                               hipStream_t stream);

@@ -38,7 +38,9 @@ __device__ __forceinline__ uint64_t topk_key(C v) {
 // among themselves the first pass does not need.  Bound by HBM with one
 // work-group of 1024 threads and eight loads in flight per thread on a CU;
 // finer bins than the 12 top bits save the pass that refines them, and
-// spread the LDS additions.
+// spread the LDS additions.  A work-group's counts fit 32 bits (at most 2^26
+// keys each), the state's do not: 2^32 equal amplitudes share a bin on 32
+// qubits.
 constexpr int kTopkWide = (1 << 15) + 1;
 
 __device__ __forceinline__ uint32_t topk_wide_bin(uint64_t key) {
@@ -49,7 +51,7 @@ __device__ __forceinline__ uint32_t topk_wide_bin(uint64_t key) {
 template <typename C>
 __global__ void __launch_bounds__(1024)
     topk_wide_kernel(const C* __restrict__ a, uint64_t count,
-                     unsigned int* __restrict__ hist) {
+                     unsigned long long* __restrict__ hist) {
   extern __shared__ unsigned int wide[];
   for (int b = threadIdx.x; b < kTopkWide; b += 1024) wide[b] = 0;
   __syncthreads();
@@ -67,13 +69,13 @@ __global__ void __launch_bounds__(1024)
     atomicAdd(&wide[topk_wide_bin(topk_key(a[i]))], 1u);
   __syncthreads();
   for (int b = threadIdx.x; b < kTopkWide; b += 1024)
-    if (wide[b]) atomicAdd(&hist[b], wide[b]);
+    if (wide[b]) atomicAdd(&hist[b], (unsigned long long)wide[b]);
 }
 
 // The bin of the k-th largest key: found[0] = bin, found[1] = keys above it,
 // found[2] = keys in it, found[3] = 0 (the gather's counter).
 __global__ void __launch_bounds__(1024)
-    topk_find_kernel(const unsigned int* __restrict__ hist, uint64_t k,
+    topk_find_kernel(const unsigned long long* __restrict__ hist, uint64_t k,
                      unsigned long long* __restrict__ found) {
   __shared__ unsigned long long sum[1024];
   // thread t owns bins from the top: kTopkWide - 1 - t * 33 downwards
@@ -248,18 +250,23 @@ unsigned topk_grid(uint64_t count) {
 }
 
 __global__ void __launch_bounds__(256)
-    topk_clear_kernel(unsigned int* __restrict__ hist) {
+    topk_clear_kernel(unsigned long long* __restrict__ hist,
+                      unsigned long long* __restrict__ found) {
   const int b = blockIdx.x * 256 + threadIdx.x;
   if (b < kTopkWide) hist[b] = 0;
+  if (b < 4) found[b] = 0;
 }
 
-size_t topk_hist_bytes() { return size_t(kTopkWide) * sizeof(unsigned int); }
+size_t topk_hist_bytes() {
+  return size_t(kTopkWide) * sizeof(unsigned long long);
+}
 
 template <typename C>
 static hipError_t topk_select(const C* a, uint64_t count, uint64_t k,
-                              unsigned int* hist, unsigned long long* found,
-                              uint64_t cap, uint64_t* out_key,
-                              uint64_t* out_idx, hipStream_t stream) {
+                              unsigned long long* hist,
+                              unsigned long long* found, uint64_t cap,
+                              uint64_t* out_key, uint64_t* out_idx,
+                              hipStream_t stream) {
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
   std::call_once(once, [] {
@@ -270,9 +277,10 @@ static hipError_t topk_select(const C* a, uint64_t count, uint64_t k,
   if (attr_err != hipSuccess) return attr_err;
   // one work-group per CU; a state of fewer amplitudes takes one per 8192
   const uint64_t g = (count + 8191) / 8192;
-  topk_clear_kernel<<<(kTopkWide + 255) / 256, 256, 0, stream>>>(hist);
-  topk_wide_kernel<C><<<unsigned(g < 256 ? g : 256), 1024, topk_hist_bytes(),
-                        stream>>>(a, count, hist);
+  topk_clear_kernel<<<(kTopkWide + 255) / 256, 256, 0, stream>>>(hist, found);
+  topk_wide_kernel<C><<<unsigned(g < 256 ? g : 256), 1024,
+                        kTopkWide * sizeof(unsigned int), stream>>>(a, count,
+                                                                    hist);
   topk_find_kernel<<<1, 1024, 0, stream>>>(hist, k, found);
   topk_gather_kernel<C><<<unsigned(g < 2048 ? g : 2048), 256, 0, stream>>>(
       a, count, found, cap, out_key, out_idx);
@@ -280,7 +288,7 @@ static hipError_t topk_select(const C* a, uint64_t count, uint64_t k,
 }
 
 hipError_t launch_topk_select(int prec, const void* amp, uint64_t count,
-                              uint64_t k, unsigned int* hist,
+                              uint64_t k, unsigned long long* hist,
                               unsigned long long* found, uint64_t cap,
                               uint64_t* out_key, uint64_t* out_idx,
                               hipStream_t stream) {
