@@ -911,8 +911,9 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
     hp->out_spec = int32_t(o_os - o_lp);
     tpasses[size_t(op.last_tile)].flags |= kPassOutputs;
   }
-  // the tile kernels read one op past the one they apply
-  buf.resize(buf.size() + sizeof(TileOp));
+  // the tile kernels read one op past the one they apply (a plan without
+  // tile passes, matrices or blocks uploads nothing)
+  if (!tops.empty()) buf.resize(buf.size() + sizeof(TileOp));
   const auto t1 = std::chrono::steady_clock::now();
 
   if ((st = select_device(s)) != QSV_OK) return st;
