@@ -93,6 +93,18 @@ hipError_t dev_malloc(void** p, size_t bytes) {
   return hipMalloc(p, bytes);
 }
 
+// Allocate *cap bytes, or, where these are not to be had, the `bytes` that the
+// call needs (then *cap = bytes): room for later calls refuses none.
+hipError_t dev_malloc_room(void** p, size_t bytes, size_t* cap) {
+  if (take_injected(g_inject_alloc)) return hipErrorOutOfMemory;
+  if (*cap > bytes) {
+    if (hipMalloc(p, *cap) == hipSuccess) return hipSuccess;
+    (void)hipGetLastError();
+  }
+  *cap = bytes;
+  return hipMalloc(p, bytes);
+}
+
 #define QSV_HIP(s, call)                                             \
   do {                                                               \
     if (take_injected(g_inject_call))                                \
@@ -117,14 +129,16 @@ qsv_status select_device(qsv_state s) {
 
 int bytes_of(int prec) { return prec == QSV_C64 ? 8 : 16; }
 
-qsv_status ensure_scratch(qsv_state s, size_t bytes) {
+// A scratch buffer that has to grow grows to at_least.
+qsv_status ensure_scratch(qsv_state s, size_t bytes, size_t at_least = 0) {
   if (bytes <= s->scratch_cap) return QSV_OK;
   QSV_HIP(s, hipStreamSynchronize(s->stream));
   if (s->scratch) QSV_HIP(s, hipFree(s->scratch));
   s->scratch = nullptr;
   s->scratch_cap = 0;
-  size_t cap = std::max(bytes, size_t(1) << 16);
-  hipError_t e = dev_malloc(reinterpret_cast<void**>(&s->scratch), cap);
+  size_t cap = std::max({bytes, at_least, size_t(1) << 16});
+  hipError_t e =
+      dev_malloc_room(reinterpret_cast<void**>(&s->scratch), bytes, &cap);
   if (e != hipSuccess) {
     s->scratch = nullptr;
     (void)hipGetLastError();
@@ -161,7 +175,8 @@ qsv_status upload(qsv_state s, const void* data, size_t bytes,
     s->prog_dev = nullptr;
     s->prog_cap = 0;
     size_t cap = std::max({room, at_least, size_t(1) << 16, 2 * old});
-    hipError_t e = dev_malloc(reinterpret_cast<void**>(&s->prog_dev), cap);
+    hipError_t e =
+        dev_malloc_room(reinterpret_cast<void**>(&s->prog_dev), room, &cap);
     if (e != hipSuccess) {
       s->prog_dev = nullptr;
       (void)hipGetLastError();
@@ -188,8 +203,9 @@ qsv_status upload(qsv_state s, const void* data, size_t bytes,
     g.own = false;
     g.host = nullptr;
     g.cap = 0;
-    const size_t cap = std::max(room, at_least);
-    if (!pinned(&g.host, cap))
+    size_t cap = std::max(room, at_least);
+    if (cap > room && !pinned(&g.host, cap)) cap = room;
+    if (!g.host && !pinned(&g.host, cap))
       return fail(QSV_ERR_OUT_OF_MEMORY, "pinned staging allocation failed");
     g.own = true;
     g.cap = cap;
@@ -599,12 +615,14 @@ constexpr size_t kEarlyProgram = size_t(2) << 20;
 constexpr size_t kEarlyGates = 64;
 constexpr size_t kEarlyScratch = size_t(16) << 20;
 
-// Scratch that any plan of the options needs for these outputs.
+// Scratch that any tiled plan of the options needs for these outputs (its
+// last pass writes the probabilities, which take none).
 static size_t outputs_bound(qsv_state s, const PlanOptions& po,
                             const qsv_outputs* o) {
   const int n = s->n, L = std::min(po.tile_log2, n);
   const int kb = std::max(0, L - po.reg_log2);
   const size_t tiles = size_t(1) << (n - L);
+  if (!o->marg_m && !o->n_shots) return 0;
   size_t b = 8 * 256;
   if (o->marg_m)
     b += (tiles << std::min(o->marg_m, kb)) * sizeof(double) +
@@ -612,7 +630,6 @@ static size_t outputs_bound(qsv_state s, const PlanOptions& po,
   if (o->n_shots)
     b += sample_scratch_bytes(n, 0) + o->n_shots * sizeof(uint64_t) +
          (tiles << kb) * sizeof(double);
-  if (o->probs_dev) b += norm_scratch_bytes(n);
   return b;
 }
 
@@ -852,10 +869,11 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
       other = std::max(other, marginal_scratch_bytes(n, outs->marg_m));
     op.total = off + al(other);
     if ((st = select_device(s)) != QSV_OK) return st;
-    // (room for any plan's outputs where that is little: may_launch_early)
+    // (where it grows, room for any plan's outputs if that is little: see
+    // may_launch_early)
     const size_t any = outputs_bound(s, po, outs);
-    if ((st = ensure_scratch(s, any <= kEarlyScratch ? std::max(any, op.total)
-                                                     : op.total)) != QSV_OK)
+    if ((st = ensure_scratch(s, op.total,
+                             any <= kEarlyScratch ? any : 0)) != QSV_OK)
       return st;
   }
 
