@@ -37,6 +37,10 @@
  *   return; calls that return host data (norm, marginal, sample, get) wait
  *   for the state's stream.  One state must not be used from two threads at
  *   once; different states are independent.
+ * - Stream capture: calls that only launch kernels can be captured once the
+ *   buffers they need are there.  Calls that wait, grow a buffer or upload a
+ *   program (circuits with tile or fused passes, gates on 3 to 5 targets)
+ *   cannot: they return QSV_ERR_DEVICE and the state turns failed.
  */
 #ifndef QSV_H
 #define QSV_H

@@ -159,12 +159,22 @@ bool pinned(char** p, size_t bytes) {
   return false;
 }
 
-// Copy `bytes` of host data into the state's device program buffer, in
-// stream order; the caller holds an UploadEnd (kernels already enqueued keep reading the previous
-// program until the copy runs).
+bool capturing(qsv_state s) {
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s->stream, &cs) != hipSuccess)
+    (void)hipGetLastError();
+  return cs != hipStreamCaptureStatusNone;
+}
+
+// Copy `bytes` of host data into the state's device program buffer, in stream
+// order: kernels already enqueued read the previous program.  The caller holds
+// an UploadEnd.  Refused while the stream is captured: a replay would read the
+// staging and program buffers, which later calls overwrite, grow and free.
 qsv_status upload(qsv_state s, const void* data, size_t bytes,
                   size_t at_least = 0) {
   if (bytes == 0) return QSV_OK;
+  if (capturing(s))
+    return device_fail(s, hipErrorStreamCaptureUnsupported, "program upload");
   // copied in 16-byte words; a buffer that has to grow, or is new, grows to
   // at_least
   const size_t room = (bytes + 15) & ~size_t(15);
@@ -645,13 +655,7 @@ static bool may_launch_early(qsv_state s, const std::vector<HostGate>& G,
       s->prog_cap < need || s->stage[0].cap < need || s->stage[1].cap < need)
     return false;
   if (o && s->scratch_cap < outputs_bound(s, po, o)) return false;
-  if (!all_tileable(G)) return false;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s->stream, &cs) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return cs == hipStreamCaptureStatusNone;
+  return all_tileable(G) && !capturing(s);
 }
 
 static bool stream_idle(qsv_state s) {
