@@ -401,7 +401,8 @@ qsv_status qsv_permute_qubits(qsv_state s, const int32_t* perm);
  * separately (for c64 the amplitudes are widened to FP64 first), so the
  * selection equals that of any plain FP64 evaluation.  This is the literal
  * top-k alternative to the marginal over specified qubits (Section IV.A).
- * Reads the state about seven times (radix select on 12-bit digits), waits. */
+ * Reads the state twice, or, where many amplitudes share the k-th one's
+ * magnitude, up to seven times (radix select); waits. */
 qsv_status qsv_top_k(qsv_state s, uint32_t k, uint64_t* idx_out,
                      double* p_out);
 

@@ -1795,22 +1795,21 @@ qsv_status qsv_permute_qubits(qsv_state s, const int32_t* perm) {
 
 // ------------------------------------------------------------- top-k
 
-// The first k of the gathered (key, index) pairs, largest key first, equal
-// keys by index.
-static qsv_status write_top_k(uint32_t k, const std::vector<uint64_t>& keys,
-                              const std::vector<uint64_t>& idx,
-                              uint64_t* idx_out, double* p_out) {
-  std::vector<uint32_t> ord(keys.size());
-  for (size_t i = 0; i < ord.size(); ++i) ord[i] = uint32_t(i);
-  std::partial_sort(ord.begin(), ord.begin() + k, ord.end(),
-                    [&](uint32_t x, uint32_t y) {
-                      if (keys[x] != keys[y]) return keys[x] > keys[y];
-                      return idx[x] < idx[y];
-                    });
+// The first k of the pairs, largest key first, equal keys by index.  The k are
+// set apart before they are sorted where there are more; those from `sorted`
+// on are in place.
+static qsv_status write_top_k(uint32_t k, uint64_t sorted,
+                              std::vector<KeyIndex>* pairs, uint64_t* idx_out,
+                              double* p_out) {
+  auto before = [](const KeyIndex& x, const KeyIndex& y) {
+    return x.key != y.key ? x.key > y.key : x.idx < y.idx;
+  };
+  if (pairs->size() > k)
+    std::nth_element(pairs->begin(), pairs->begin() + k, pairs->end(), before);
+  std::sort(pairs->begin(), pairs->begin() + std::ptrdiff_t(sorted), before);
   for (uint32_t i = 0; i < k; ++i) {
-    idx_out[i] = idx[ord[i]];
-    const uint64_t kb = keys[ord[i]];
-    std::memcpy(&p_out[i], &kb, 8);
+    idx_out[i] = (*pairs)[i].idx;
+    std::memcpy(&p_out[i], &(*pairs)[i].key, 8);
   }
   return QSV_OK;
 }
@@ -1824,46 +1823,66 @@ qsv_status qsv_top_k(qsv_state s, uint32_t k, uint64_t* idx_out,
   if (k < 1 || k > 65536 || uint64_t(k) > count)
     return fail(QSV_ERR_INVALID_ARG, "k must be 1..min(65536, 2^n)");
   if ((st = select_device(s)) != QSV_OK) return st;
-  // scratch: histogram (of either kind), counters, gathered keys and
-  // indices, tie counts/offsets.  The gather has room for the k keys and for
-  // as many again as usually share the k-th one's bin.
+  // scratch: histogram (of either kind), counters, gathered pairs, tie
+  // counts/offsets.  The gather has room for the k keys and for as many again
+  // as usually share the k-th one's bin.
   const unsigned tie_blocks = 1024;
   const uint64_t chunk = (count + tie_blocks - 1) / tie_blocks;
   const uint64_t cap = std::min<uint64_t>(count, 2 * uint64_t(k) + 16384);
   const size_t o_cnt = (std::max<size_t>(4096 * 8, topk_hist_bytes()) + 255) &
                        ~size_t(255);
-  const size_t o_key = o_cnt + 256, o_idx = o_key + 8 * size_t(cap);
-  const size_t o_tc = (o_idx + 8 * size_t(cap) + 255) & ~size_t(255);
+  const size_t o_pair = o_cnt + sizeof(TopkFound);
+  const size_t o_tc = (o_pair + sizeof(KeyIndex) * size_t(cap) + 255) &
+                      ~size_t(255);
   const size_t o_to = o_tc + 8 * tie_blocks;
   if ((st = ensure_scratch(s, o_to + 8 * tie_blocks)) != QSV_OK) return st;
   char* sc = s->scratch;
   auto* hist = reinterpret_cast<unsigned long long*>(sc);
-  auto* counter = reinterpret_cast<unsigned long long*>(sc + o_cnt);
-  auto* dkey = reinterpret_cast<uint64_t*>(sc + o_key);
-  auto* didx = reinterpret_cast<uint64_t*>(sc + o_idx);
+  auto* found_dev = reinterpret_cast<TopkFound*>(sc + o_cnt);
+  auto* dpair = reinterpret_cast<KeyIndex*>(sc + o_pair);
   auto* tcount = reinterpret_cast<unsigned long long*>(sc + o_tc);
   auto* toff = reinterpret_cast<unsigned long long*>(sc + o_to);
-  std::vector<uint64_t> keys, idx;
-  unsigned long long found[4];
-  QSV_HIP(s, launch_topk_select(s->prec, s->amp, count, k, hist, counter, cap,
-                                dkey, didx, s->stream));
-  QSV_HIP(s, hipMemcpyAsync(found, counter, sizeof found,
+  QSV_HIP(s, launch_topk_select(s->prec, s->amp, count, k, hist, found_dev, cap,
+                                dpair, s->stream));
+  // the result record and the first pairs come in one copy, with one wait
+  // (8 qubits, k = 1: 84 -> 64 us)
+  struct Head {
+    TopkFound found;
+    KeyIndex first[1024];
+  };
+  std::vector<Head> head(1);
+  const uint64_t n_first = std::min<uint64_t>(cap, 1024);
+  QSV_HIP(s, hipMemcpyAsync(head.data(), found_dev,
+                            sizeof(TopkFound) + sizeof(KeyIndex) * n_first,
                             hipMemcpyDeviceToHost, s->stream));
   QSV_HIP(s, hipStreamSynchronize(s->stream));
-  if (found[1] + found[2] >= k && found[1] + found[2] <= cap) {
-    const size_t m = size_t(found[1] + found[2]);
-    keys.resize(m);
-    idx.resize(m);
-    QSV_HIP(s, hipMemcpyAsync(keys.data(), dkey, 8 * m, hipMemcpyDeviceToHost,
-                              s->stream));
-    QSV_HIP(s, hipMemcpyAsync(idx.data(), didx, 8 * m, hipMemcpyDeviceToHost,
-                              s->stream));
-    QSV_HIP(s, hipStreamSynchronize(s->stream));
-    return write_top_k(k, keys, idx, idx_out, p_out);
+  const TopkFound& found = head[0].found;
+  const uint64_t m = found.above + found.in_bin;
+  std::vector<KeyIndex> pairs;
+  if (m >= k && m <= cap) {
+    pairs.resize(m);
+    std::copy(head[0].first, head[0].first + std::min(m, n_first),
+              pairs.begin());
+    if (m > n_first) {
+      QSV_HIP(s, hipMemcpyAsync(pairs.data() + n_first, dpair + n_first,
+                                sizeof(KeyIndex) * (m - n_first),
+                                hipMemcpyDeviceToHost, s->stream));
+      QSV_HIP(s, hipStreamSynchronize(s->stream));
+    }
+    return write_top_k(k, k, &pairs, idx_out, p_out);
   }
-  // radix select of the k-th largest key, 12 bits per pass from the top
+  // radix select of the k-th largest key, 12 bits per pass, from the 16 bits
+  // that the bin gives (but for the one of keys with the sign bit, which is
+  // no one value of them) or from the top
   uint64_t prefix = 0, mask = 0, need = k, above = 0;
   int fixed = 0;
+  if (m >= k && found.bin < (1u << 15)) {
+    fixed = 16;
+    prefix = found.bin << 48;
+    mask = ~uint64_t(0) << 48;
+    above = found.above;
+    need = k - above;
+  }
   bool whole_bin = false;
   std::vector<unsigned long long> h(4096);
   while (fixed < 64) {
@@ -1892,31 +1911,22 @@ qsv_status qsv_top_k(qsv_state s, uint32_t k, uint64_t* idx_out,
       break;
     }
   }
+  pairs.resize(k);
   if (whole_bin) {
-    QSV_HIP(s, hipMemsetAsync(counter, 0, 8, s->stream));
+    QSV_HIP(s, hipMemsetAsync(&found_dev->gathered, 0, 8, s->stream));
     QSV_HIP(s, launch_topk_collect(s->prec, s->amp, count, mask, prefix, 1,
-                                   counter, k, dkey, didx, s->stream));
-    keys.resize(k);
-    idx.resize(k);
-    QSV_HIP(s, hipMemcpyAsync(keys.data(), dkey, 8 * size_t(k),
-                              hipMemcpyDeviceToHost, s->stream));
-    QSV_HIP(s, hipMemcpyAsync(idx.data(), didx, 8 * size_t(k),
+                                   &found_dev->gathered, k, dpair, s->stream));
+    QSV_HIP(s, hipMemcpyAsync(pairs.data(), dpair, sizeof(KeyIndex) * size_t(k),
                               hipMemcpyDeviceToHost, s->stream));
     QSV_HIP(s, hipStreamSynchronize(s->stream));
   } else {
     // prefix is the exact k-th key: `above` keys exceed it, `need` of the
     // keys equal to it complete the k, in index order
-    keys.resize(k);
-    idx.resize(k);
     if (above) {
-      QSV_HIP(s, hipMemsetAsync(counter, 0, 8, s->stream));
+      QSV_HIP(s, hipMemsetAsync(&found_dev->gathered, 0, 8, s->stream));
       QSV_HIP(s, launch_topk_collect(s->prec, s->amp, count, ~uint64_t(0),
-                                     prefix, 0, counter, above, dkey, didx,
-                                     s->stream));
-      QSV_HIP(s, hipMemcpyAsync(keys.data(), dkey, 8 * above,
-                                hipMemcpyDeviceToHost, s->stream));
-      QSV_HIP(s, hipMemcpyAsync(idx.data(), didx, 8 * above,
-                                hipMemcpyDeviceToHost, s->stream));
+                                     prefix, 0, &found_dev->gathered, above,
+                                     dpair, s->stream));
     }
     QSV_HIP(s, launch_topk_ties(s->prec, s->amp, count, prefix, tie_blocks,
                                 chunk, tcount, nullptr, 0, nullptr,
@@ -1933,14 +1943,13 @@ qsv_status qsv_top_k(qsv_state s, uint32_t k, uint64_t* idx_out,
     QSV_HIP(s, hipMemcpyAsync(toff, to.data(), 8 * tie_blocks,
                               hipMemcpyHostToDevice, s->stream));
     QSV_HIP(s, launch_topk_ties(s->prec, s->amp, count, prefix, tie_blocks,
-                                chunk, tcount, toff, need, didx + above,
+                                chunk, tcount, toff, need, dpair + above,
                                 s->stream));
-    QSV_HIP(s, hipMemcpyAsync(idx.data() + above, didx + above, 8 * need,
+    QSV_HIP(s, hipMemcpyAsync(pairs.data(), dpair, sizeof(KeyIndex) * size_t(k),
                               hipMemcpyDeviceToHost, s->stream));
     QSV_HIP(s, hipStreamSynchronize(s->stream));
-    for (uint64_t i = above; i < k; ++i) keys[i] = prefix;
   }
-  return write_top_k(k, keys, idx, idx_out, p_out);
+  return write_top_k(k, whole_bin ? k : above, &pairs, idx_out, p_out);
 }
 
 // ------------------------------------------------- Pauli expectations

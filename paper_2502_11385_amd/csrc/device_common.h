@@ -192,15 +192,25 @@ hipError_t launch_marginal(int prec, const void* amp, int n,
                            double* out_dev, hipStream_t stream);
 size_t sample_scratch_bytes(int n, uint64_t shots);
 // top-k and Pauli expectations (k_outputs.hip)
-// Two passes over the state: found[0..2] = the k-th largest key's bin (the
-// key's top 16 bits), the keys above that bin and those in it (zeros before
-// the search); if these are at most cap together, out_key/out_idx receive all
-// of them in no order.
+// A basis state's key (the bits of its probability) and index.
+struct KeyIndex {
+  uint64_t key;
+  uint64_t idx;
+};
+// The k-th largest key's bin (by the key's top 16 bits), the keys above that
+// bin and those in it (zeros before the search), and the gather's counter.
+struct TopkFound {
+  uint64_t bin;
+  uint64_t above;
+  uint64_t in_bin;
+  unsigned long long gathered;
+};
+// Two passes over the state: *found, then, if the keys above the bin and in
+// it are at most cap, all of them in no order into out.
 size_t topk_hist_bytes();
 hipError_t launch_topk_select(int prec, const void* amp, uint64_t count,
                               uint64_t k, unsigned long long* hist,
-                              unsigned long long* found, uint64_t cap,
-                              uint64_t* out_key, uint64_t* out_idx,
+                              TopkFound* found, uint64_t cap, KeyIndex* out,
                               hipStream_t stream);
 hipError_t launch_topk_hist(int prec, const void* amp, uint64_t count,
                             uint64_t mask, uint64_t prefix, int shift,
@@ -209,13 +219,12 @@ hipError_t launch_topk_hist(int prec, const void* amp, uint64_t count,
 hipError_t launch_topk_collect(int prec, const void* amp, uint64_t count,
                                uint64_t mask, uint64_t prefix, int ge,
                                unsigned long long* counter, uint64_t cap,
-                               uint64_t* out_key, uint64_t* out_idx,
-                               hipStream_t stream);
+                               KeyIndex* out, hipStream_t stream);
 hipError_t launch_topk_ties(int prec, const void* amp, uint64_t count,
                             uint64_t key, unsigned blocks, uint64_t chunk,
                             unsigned long long* counts,
                             const unsigned long long* offsets, uint64_t need,
-                            uint64_t* out_idx, hipStream_t stream);
+                            KeyIndex* out, hipStream_t stream);
 // qubit relabelling (k_permute.hip): tile source bits s_bits (ascending,
 // s of them), their destinations d_bits (ascending), and the outer source
 // bits with their destinations

@@ -11,9 +11,9 @@
 // the state at HBM's rate where 12-bit digits took three or more (27 qubits,
 // k = 64: 0.70 -> 0.48 ms complex64, 1.17 -> 0.84 ms complex128).  Where those
 // are too many (states of many equal magnitudes), a radix select on 12-bit
-// digits (one histogram pass per digit, integer counts) fixes the threshold
-// key; the elements above it are gathered, and the remaining places go to
-// the elements equal to it in index order.
+// digits below the bin's (one histogram pass per digit, integer counts) fixes
+// the threshold key; the elements above it are gathered, and the remaining
+// places go to the elements equal to it in index order.
 #include <algorithm>
 #include <mutex>
 
@@ -48,6 +48,19 @@ __device__ __forceinline__ uint32_t topk_wide_bin(uint64_t key) {
   return d < (1u << 15) ? d : (1u << 15);
 }
 
+// A wave whose keys share a bin (states of few amplitudes that are not 0)
+// adds their number once: additions to one address go one after the other.
+__device__ __forceinline__ void topk_wide_add(unsigned int* wide,
+                                              uint64_t key) {
+  const uint32_t bin = topk_wide_bin(key);
+  const uint32_t first = __builtin_amdgcn_readfirstlane(bin);
+  const uint64_t lanes = __ballot(1);
+  if (__ballot(bin == first) != lanes)
+    atomicAdd(&wide[bin], 1u);
+  else if ((threadIdx.x & 63u) == uint32_t(__builtin_ctzll(lanes)))
+    atomicAdd(&wide[first], uint32_t(__popcll(lanes)));
+}
+
 template <typename C>
 __global__ void __launch_bounds__(1024)
     topk_wide_kernel(const C* __restrict__ a, uint64_t count,
@@ -62,21 +75,18 @@ __global__ void __launch_bounds__(1024)
 #pragma unroll
     for (int j = 0; j < 8; ++j) v[j] = a[i + j * stride];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      atomicAdd(&wide[topk_wide_bin(topk_key(v[j]))], 1u);
+    for (int j = 0; j < 8; ++j) topk_wide_add(wide, topk_key(v[j]));
   }
-  for (; i < count; i += stride)
-    atomicAdd(&wide[topk_wide_bin(topk_key(a[i]))], 1u);
+  for (; i < count; i += stride) topk_wide_add(wide, topk_key(a[i]));
   __syncthreads();
   for (int b = threadIdx.x; b < kTopkWide; b += 1024)
     if (wide[b]) atomicAdd(&hist[b], (unsigned long long)wide[b]);
 }
 
-// The bin of the k-th largest key: found[0] = bin, found[1] = keys above it,
-// found[2] = keys in it, found[3] = 0 (the gather's counter).
+// The bin of the k-th largest key into *found.
 __global__ void __launch_bounds__(1024)
     topk_find_kernel(const unsigned long long* __restrict__ hist, uint64_t k,
-                     unsigned long long* __restrict__ found) {
+                     TopkFound* __restrict__ found) {
   __shared__ unsigned long long sum[1024];
   // thread t owns bins from the top: kTopkWide - 1 - t * 33 downwards
   constexpr int kPer = (kTopkWide + 1023) / 1024;
@@ -98,10 +108,9 @@ __global__ void __launch_bounds__(1024)
     for (int j = 0; j < kPer; ++j) {
       const unsigned long long h = hist[top - j];
       if (cum + h >= k) {
-        found[0] = top - j;
-        found[1] = cum;
-        found[2] = h;
-        found[3] = 0;
+        found->bin = uint64_t(top - j);
+        found->above = cum;
+        found->in_bin = h;
         break;
       }
       cum += h;
@@ -114,19 +123,15 @@ __global__ void __launch_bounds__(1024)
 template <typename C>
 __global__ void __launch_bounds__(256)
     topk_gather_kernel(const C* __restrict__ a, uint64_t count,
-                       unsigned long long* __restrict__ found, uint64_t cap,
-                       uint64_t* __restrict__ out_key,
-                       uint64_t* __restrict__ out_idx) {
-  if (found[1] + found[2] > cap) return;
-  const uint32_t bin = uint32_t(found[0]);
+                       TopkFound* __restrict__ found, uint64_t cap,
+                       KeyIndex* __restrict__ out) {
+  if (found->above + found->in_bin > cap) return;
+  const uint32_t bin = uint32_t(found->bin);
   const uint64_t stride = uint64_t(gridDim.x) * 256;
   auto put = [&](uint64_t key, uint64_t i) {
     if (topk_wide_bin(key) < bin) return;
-    const unsigned long long slot = atomicAdd(&found[3], 1ull);
-    if (slot < cap) {
-      out_key[slot] = key;
-      out_idx[slot] = i;
-    }
+    const unsigned long long slot = atomicAdd(&found->gathered, 1ull);
+    if (slot < cap) out[slot] = KeyIndex{key, i};
   };
   uint64_t i = uint64_t(blockIdx.x) * 256 + threadIdx.x;
   for (; i + 7 * stride < count; i += 8 * stride) {
@@ -169,8 +174,7 @@ __global__ void __launch_bounds__(256)
     topk_collect_kernel(const C* __restrict__ a, uint64_t count,
                         uint64_t mask, uint64_t prefix, int ge,
                         unsigned long long* __restrict__ counter, uint64_t cap,
-                        uint64_t* __restrict__ out_key,
-                        uint64_t* __restrict__ out_idx) {
+                        KeyIndex* __restrict__ out) {
   const uint64_t stride = uint64_t(gridDim.x) * 256;
   for (uint64_t i = uint64_t(blockIdx.x) * 256 + threadIdx.x; i < count;
        i += stride) {
@@ -178,10 +182,7 @@ __global__ void __launch_bounds__(256)
     const uint64_t m = k & mask;
     if (ge ? m >= prefix : m > prefix) {
       const unsigned long long slot = atomicAdd(counter, 1ull);
-      if (slot < cap) {
-        out_key[slot] = k;
-        out_idx[slot] = i;
-      }
+      if (slot < cap) out[slot] = KeyIndex{k, i};
     }
   }
 }
@@ -213,7 +214,7 @@ __global__ void __launch_bounds__(256)
     topk_tie_collect_kernel(const C* __restrict__ a, uint64_t count,
                             uint64_t chunk, uint64_t key,
                             const unsigned long long* __restrict__ offsets,
-                            uint64_t need, uint64_t* __restrict__ out_idx) {
+                            uint64_t need, KeyIndex* __restrict__ out) {
   __shared__ unsigned int wave_cnt[4];
   const uint64_t base = offsets[blockIdx.x];
   if (base >= need) return;  // uniform over the block
@@ -231,7 +232,7 @@ __global__ void __launch_bounds__(256)
     for (int w = 0; w < wv; ++w) before += wave_cnt[w];
     const uint64_t mine = __popcll(bal & ((uint64_t(1) << lane) - 1));
     const uint64_t rank = run + before + mine;
-    if (eq && rank < need) out_idx[rank] = i;
+    if (eq && rank < need) out[rank] = KeyIndex{key, i};
     uint64_t total = 0;
     for (int w = 0; w < 4; ++w) total += wave_cnt[w];
     __syncthreads();
@@ -251,10 +252,10 @@ unsigned topk_grid(uint64_t count) {
 
 __global__ void __launch_bounds__(256)
     topk_clear_kernel(unsigned long long* __restrict__ hist,
-                      unsigned long long* __restrict__ found) {
+                      TopkFound* __restrict__ found) {
   const int b = blockIdx.x * 256 + threadIdx.x;
   if (b < kTopkWide) hist[b] = 0;
-  if (b < 4) found[b] = 0;
+  if (b == 0) *found = TopkFound{};
 }
 
 size_t topk_hist_bytes() {
@@ -263,9 +264,8 @@ size_t topk_hist_bytes() {
 
 template <typename C>
 static hipError_t topk_select(const C* a, uint64_t count, uint64_t k,
-                              unsigned long long* hist,
-                              unsigned long long* found, uint64_t cap,
-                              uint64_t* out_key, uint64_t* out_idx,
+                              unsigned long long* hist, TopkFound* found,
+                              uint64_t cap, KeyIndex* out,
                               hipStream_t stream) {
   static std::once_flag once;
   static hipError_t attr_err = hipSuccess;
@@ -275,28 +275,27 @@ static hipError_t topk_select(const C* a, uint64_t count, uint64_t k,
         hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
   });
   if (attr_err != hipSuccess) return attr_err;
-  // one work-group per CU; a state of fewer amplitudes takes one per 8192
-  const uint64_t g = (count + 8191) / 8192;
+  // one work-group per CU, a state of fewer amplitudes one per 2048; the
+  // gather, whose pairs the host sorts, in fewer pieces
+  const uint64_t g = (count + 2047) / 2048, gg = (count + 8191) / 8192;
   topk_clear_kernel<<<(kTopkWide + 255) / 256, 256, 0, stream>>>(hist, found);
   topk_wide_kernel<C><<<unsigned(g < 256 ? g : 256), 1024,
                         kTopkWide * sizeof(unsigned int), stream>>>(a, count,
                                                                     hist);
   topk_find_kernel<<<1, 1024, 0, stream>>>(hist, k, found);
-  topk_gather_kernel<C><<<unsigned(g < 2048 ? g : 2048), 256, 0, stream>>>(
-      a, count, found, cap, out_key, out_idx);
+  topk_gather_kernel<C><<<unsigned(gg < 2048 ? gg : 2048), 256, 0, stream>>>(
+      a, count, found, cap, out);
   return hipGetLastError();
 }
 
 hipError_t launch_topk_select(int prec, const void* amp, uint64_t count,
                               uint64_t k, unsigned long long* hist,
-                              unsigned long long* found, uint64_t cap,
-                              uint64_t* out_key, uint64_t* out_idx,
+                              TopkFound* found, uint64_t cap, KeyIndex* out,
                               hipStream_t stream) {
   if (prec == 1)
-    return topk_select(as<float2>(amp), count, k, hist, found, cap, out_key,
-                       out_idx, stream);
-  return topk_select(as<double2>(amp), count, k, hist, found, cap, out_key,
-                     out_idx, stream);
+    return topk_select(as<float2>(amp), count, k, hist, found, cap, out,
+                       stream);
+  return topk_select(as<double2>(amp), count, k, hist, found, cap, out, stream);
 }
 
 hipError_t launch_topk_hist(int prec, const void* amp, uint64_t count,
@@ -316,17 +315,14 @@ hipError_t launch_topk_hist(int prec, const void* amp, uint64_t count,
 hipError_t launch_topk_collect(int prec, const void* amp, uint64_t count,
                                uint64_t mask, uint64_t prefix, int ge,
                                unsigned long long* counter, uint64_t cap,
-                               uint64_t* out_key, uint64_t* out_idx,
-                               hipStream_t stream) {
+                               KeyIndex* out, hipStream_t stream) {
   const unsigned g = topk_grid(count);
   if (prec == 1)
     topk_collect_kernel<float2><<<g, 256, 0, stream>>>(
-        as<float2>(amp), count, mask, prefix, ge, counter, cap, out_key,
-        out_idx);
+        as<float2>(amp), count, mask, prefix, ge, counter, cap, out);
   else
     topk_collect_kernel<double2><<<g, 256, 0, stream>>>(
-        as<double2>(amp), count, mask, prefix, ge, counter, cap, out_key,
-        out_idx);
+        as<double2>(amp), count, mask, prefix, ge, counter, cap, out);
   return hipGetLastError();
 }
 
@@ -334,7 +330,7 @@ hipError_t launch_topk_ties(int prec, const void* amp, uint64_t count,
                             uint64_t key, unsigned blocks, uint64_t chunk,
                             unsigned long long* counts,
                             const unsigned long long* offsets, uint64_t need,
-                            uint64_t* out_idx, hipStream_t stream) {
+                            KeyIndex* out, hipStream_t stream) {
   if (!offsets) {
     if (prec == 1)
       topk_tie_count_kernel<float2><<<blocks, 256, 0, stream>>>(
@@ -345,10 +341,10 @@ hipError_t launch_topk_ties(int prec, const void* amp, uint64_t count,
   } else {
     if (prec == 1)
       topk_tie_collect_kernel<float2><<<blocks, 256, 0, stream>>>(
-          as<float2>(amp), count, chunk, key, offsets, need, out_idx);
+          as<float2>(amp), count, chunk, key, offsets, need, out);
     else
       topk_tie_collect_kernel<double2><<<blocks, 256, 0, stream>>>(
-          as<double2>(amp), count, chunk, key, offsets, need, out_idx);
+          as<double2>(amp), count, chunk, key, offsets, need, out);
   }
   return hipGetLastError();
 }
