@@ -181,12 +181,18 @@ __global__ void __launch_bounds__(256)
 // Bound by the HBM write of the outcomes (8 bytes each, n_c multiply-adds):
 // V stays in registers over all rows and W is formed once per row, where a
 // wave per 64 outcomes formed both again for each block and waited for their
-// loads.  2^28 outcomes, 2 cuts, n_c = 4: 0.96 -> 0.39 ms, 5.5 TB/s.
+// loads.  2^28 outcomes, 2 cuts, n_c = 4: 0.88 -> 0.39 ms a call, 5.5 TB/s.
+// Where there are fewer W than threads, the terms of their sums over u are
+// formed by all the threads, a round at a time, and added in increasing u as
+// one thread would: a thread per W alone made few outcomes with many cuts wait
+// for a chain of 4^cuts loads (12 qubits, 4 cuts, n_u = 64: 95 -> 40 us a call).
 template <int NC>
 __global__ void __launch_bounds__(256)
     cut_kron_tile_kernel(CutArgs a, const double* __restrict__ T,
                          double* __restrict__ out, int rows_log) {
   __shared__ double W[(1 << kCutRowsLog) * NC];
+  __shared__ double P[2 * 256];  // a round's terms, two rounds in turn
+  __shared__ uint32_t Y[kCutMaxSub << kCutRowsLog];
   const uint32_t tid = threadIdx.x;
   const int chunk_log = a.n_free - rows_log;
   const uint64_t chunk = blockIdx.x & ((uint64_t(1) << chunk_log) - 1);
@@ -199,20 +205,43 @@ __global__ void __launch_bounds__(256)
     x0 |= ((chunk >> i) & 1) << a.free_pos[rows_log + i];
   const int rows = 1 << rows_log;
   const uint64_t n_u = a.n_u;
-  for (int i = tid; i < rows * NC; i += 256) {
-    const int f = i / NC, c = i % NC;
+  // output index of each uniform subcircuit in each row
+  for (int i = tid; i < rows * a.n_uni; i += 256) {
     uint64_t x = x0;
     for (int b = 0; b < rows_log; ++b)
-      x |= uint64_t((f >> b) & 1) << a.free_pos[b];
-    double sum = 0.0;
-    for (uint64_t u = 0; u < n_u; ++u) {
-      const uint64_t* row = a.ttu + (uint64_t(c) * n_u + u) * uint64_t(a.n_uni);
-      double prod = 1.0;
-      for (int k = 0; k < a.n_uni; ++k)
-        prod *= T[row[k] + cut_gather(a.subs[a.uni_sub[k]], x)];
-      sum += prod;
+      x |= uint64_t((i >> b) & 1) << a.free_pos[b];
+    Y[i] = uint32_t(cut_gather(a.subs[a.uni_sub[i >> rows_log]], x));
+  }
+  __syncthreads();
+  auto term = [&](int i, uint64_t u) {
+    const int f = i / NC, c = i % NC;
+    const uint64_t* row = a.ttu + (uint64_t(c) * n_u + u) * uint64_t(a.n_uni);
+    double prod = 1.0;
+    for (int k = 0; k < a.n_uni; ++k)
+      prod *= T[row[k] + Y[(k << rows_log) + f]];
+    return prod;
+  };
+  const int n_w = rows * NC;
+  const uint64_t per = n_w < 256 ? 256 / n_w : 1;  // threads per W
+  if (per == 1 || n_u == 1) {
+    for (int i = tid; i < n_w; i += 256) {
+      double sum = 0.0;
+      for (uint64_t u = 0; u < n_u; ++u) sum += term(i, u);
+      W[i] = sum;
     }
-    W[i] = sum;
+  } else {
+    const uint64_t step = per < n_u ? per : n_u;  // powers of two
+    const int i = int(tid) & (n_w - 1);
+    const uint64_t g = tid / n_w;
+    double sum = 0.0;
+    int buf = 0;
+    for (uint64_t u = 0; u < n_u; u += step, buf ^= 256) {
+      if (g < step) P[buf + g * n_w + i] = term(i, u + g);
+      __syncthreads();
+      if (g == 0)
+        for (uint64_t j = 0; j < step; ++j) sum += P[buf + j * n_w + i];
+    }
+    if (g == 0) W[i] = sum;
   }
   const uint64_t xt = xv | tid;
   double V[NC];
