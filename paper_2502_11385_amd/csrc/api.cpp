@@ -1715,8 +1715,15 @@ qsv_status qsv_permute_qubits(qsv_state s, const int32_t* perm) {
   if (identity) return QSV_OK;
   if ((st = select_device(s)) != QSV_OK) return st;
   // Tile source bits: the m lowest and those that land on the m lowest, m as
-  // large as a tile of 32 KiB allows, then the lowest others.
-  const int cap = std::min(n, s->b == 8 ? 12 : 11);
+  // large as a tile allows, then the lowest others.  A tile has 8 KiB where
+  // 32 KiB would leave the CUs two or fewer each: states of up to 16 MiB
+  // (kernel time, tiles of 32 KiB -> 8 KiB, random permutation: complex64 16
+  // qubits 6.2 -> 4.8 us, 18 qubits 6.4 -> 5.6, 21 qubits 12.8 -> 10.2, 22
+  // qubits 14.6 -> 15.6; complex128 16 qubits 5.3 -> 4.7, 20 qubits 11.9 -> 9.1;
+  // beyond, the tiles' runs count: complex64 23 qubits, qubits 0 and 1
+  // exchanged, 21.2 -> 23.2).
+  const int tile_log2 = (size_t(s->b) << n) > (size_t(16) << 20) ? 15 : 13;
+  const int cap = std::min(n, tile_log2 - (s->b == 8 ? 3 : 4));
   auto span = [&](int m) {
     uint64_t v = 0;
     for (int q = 0; q < m; ++q)

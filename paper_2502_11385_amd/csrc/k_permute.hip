@@ -4,15 +4,19 @@
 // one pass moves busy high qubits to low positions, where later tiles and
 // coalesced runs cover them.  A work-group takes tiles of source indices
 // spanned by the lowest source qubits and the qubits that land on the lowest
-// destination qubits, as many of both as a 32 KiB tile holds: its reads and
-// its writes are contiguous runs (512 bytes or more where the two sets are
-// disjoint), with the tile transposed through LDS in between.
+// destination qubits, as many of both as a tile of 32 KiB holds (8 KiB for
+// small states, see qsv_permute_qubits): its reads and its writes are
+// contiguous runs (512 bytes or more where the two sets are disjoint, 256 in
+// small tiles), with the tile transposed through LDS in between.
 //
 // Bound by HBM (2^n amplitudes read and written), given enough bytes in
 // flight: each thread loads 8 (complex128) or 16 (complex64) amplitudes
-// before it stores any, and five such tiles share a CU.  Random permutation
+// of a 32 KiB tile before it stores any, and five such tiles share a CU.  Random permutation
 // of 27 qubits, complex128: 1.60 -> 0.82 ms (5.25 TB/s); the tiles of at most
 // 4 KiB before had one load in flight per thread and a work-group each.
+//
+// The file also holds the other kernels that only move data: the state's copy
+// and the upload of programs.
 #include "device_common.h"
 
 namespace qsv {
