@@ -203,23 +203,25 @@ static void dense_dispatch_nt(void* amp, int k, unsigned blocks,
   dense_dispatch_t<T, kLowNone, NT>(amp, k, blocks, args, stream);
 }
 
-// Whether a pass over a state of n qubits streams past the cache: the state
-// is larger than it, and a wave's accesses, in runs of 2^low amplitudes
+// Whether a pass over `bytes` of a state streams past the cache: the bytes are
+// more than it holds, and a wave's accesses, in runs of 2^low amplitudes
 // (`low`: the lowest bit inserted into its indexes), cover whole 128-byte
 // lines.  Where they cover a line in parts, it has to stay cached between
 // them: 30 qubits complex64, targets 0, 7 and 22, 4.63 ms streamed and 3.2
 // cached.
 // Where they do, one-target gates on 29 qubits complex64 gain 6 to 12 %, on 28
-// qubits complex128 5 to 7 %.
+// qubits complex128 5 to 7 %.  `bytes` are those between the pass's fixed bits:
+// half of a 512 MiB state stays cached from one gate to the next (26 qubits
+// complex64, control on qubit 25: 66 us cached, 81 streamed).
 template <typename T>
-static bool streamed(int n, int low) {
-  return (2 * sizeof(T) << n) > kStreamBytes && (2 * sizeof(T) << low) >= 128;
+static bool streamed(uint64_t bytes, int low) {
+  return bytes > kStreamBytes && (2 * sizeof(T) << low) >= 128;
 }
 
 template <typename T>
-static void dense_dispatch(void* amp, int n, int k, unsigned blocks,
+static void dense_dispatch(void* amp, int k, unsigned blocks,
                            const DenseArgs& args, hipStream_t stream) {
-  if (streamed<T>(n, args.npos ? args.pos[0] : n))
+  if (streamed<T>((2 * sizeof(T) * args.n_groups) << k, args.pos[0]))
     dense_dispatch_nt<T, true>(amp, k, blocks, args, stream);
   else
     dense_dispatch_nt<T, false>(amp, k, blocks, args, stream);
@@ -251,9 +253,9 @@ hipError_t launch_dense(int prec, void* amp, int n, const HostGate& g,
   }
   const unsigned blocks = grid_blocks(args.n_groups, 256);
   if (prec == 1)
-    dense_dispatch<float>(amp, n, g.k, blocks, args, stream);
+    dense_dispatch<float>(amp, g.k, blocks, args, stream);
   else
-    dense_dispatch<double>(amp, n, g.k, blocks, args, stream);
+    dense_dispatch<double>(amp, g.k, blocks, args, stream);
   return hipGetLastError();
 }
 
@@ -274,9 +276,9 @@ hipError_t launch_dense_dev(int prec, void* amp, int n, int k,
   args.mptr = dev_matrix;
   const unsigned blocks = grid_blocks(args.n_groups, 256);
   if (prec == 1)
-    dense_dispatch<float>(amp, n, k, blocks, args, stream);
+    dense_dispatch<float>(amp, k, blocks, args, stream);
   else
-    dense_dispatch<double>(amp, n, k, blocks, args, stream);
+    dense_dispatch<double>(amp, k, blocks, args, stream);
   return hipGetLastError();
 }
 
@@ -384,7 +386,7 @@ hipError_t launch_diag(int prec, void* amp, int n, const HostGate& g,
   const int low = args.npos ? args.pos[0] : n;
   const bool wide = prec == 1 && !skip && low >= (args.lowmask ? 5 : 4) &&
                     args.n_items >= uint64_t(1) << 18;
-  const bool nt = wide && streamed<float>(n, low);
+  const bool nt = wide && streamed<float>(sizeof(float2) * args.n_items, low);
   const unsigned blocks = grid_blocks(args.n_items, wide ? 1024 : 256);
 #define QSV_DIAG_U(T, TABLE, SKIP, U, NT)                                   \
   diag_kernel<T, TABLE, SKIP, U, NT><<<blocks, 256, 0, stream>>>(           \
