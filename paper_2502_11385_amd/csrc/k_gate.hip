@@ -296,57 +296,86 @@ struct DiagArgs {
 };
 
 // Multiply amplitudes by a diagonal's factor where the controls (fixed_mask
-// and lowmask) are satisfied: by one phase (masked: the targets are in the
-// masks as well), or by d[r(i)], r the target bits (TABLE).  SKIP: a lane whose
-// lowmask bits are not all 1 leaves its amplitude alone; otherwise it stores
-// it back unchanged.  Bound by the amplitudes' bytes: each thread has U
-// loads in flight, and the table is read from LDS (a lane-dependent index
-// into the kernel arguments was one more dependent load per amplitude:
-// 27 qubits complex64, one target, 460 us).
-template <typename T, bool TABLE, bool SKIP, int U, bool NT>
+// and lowmask) are satisfied: by one phase (kPhase: the targets are in the
+// masks as well), or by d[r(i)], r the target bits: read from LDS (kTable), or
+// chosen in registers where there are one or two targets (kTable1, kTable2).
+// Lanes whose lowmask bits are not all 1 store their amplitude back unchanged
+// (kKeep) or leave it alone (kSkip; kSkipLine: do not load it either).
+// Bound by the amplitudes' bytes: each thread has U loads in flight.
+//
+// A lane-dependent index into the kernel arguments was one more dependent load
+// per amplitude (27 qubits complex64, one target, four loads in flight: 440 ->
+// 330 us).  With one load in flight the wait for the LDS table counts: choosing
+// in registers (complex64), and under a control on qubit 3, half of whose
+// lines need not be read, not loading those and filling the table under the
+// first loads (27 qubits, one target, control 3: index 401, LDS 432, registers
+// 339 us complex64; 454, 540, 375 complex128; five targets 432, 440, 429 and
+// 484, 543, 493).  The other complex128 tables stay with LDS: 695 us where
+// registers take 725.
+enum DiagFactor { kPhase, kTable1, kTable2, kTable };
+enum DiagLow { kKeep, kSkip, kSkipLine };
+
+template <typename T, DiagFactor F, DiagLow LOW, int U, bool NT>
 __global__ void __launch_bounds__(256)
     diag_kernel(typename CxT<T>::type* __restrict__ a, DiagArgs args) {
   using C = typename CxT<T>::type;
-  __shared__ C tab[TABLE ? 1 << kMaxK : 1];
-  if constexpr (TABLE) {
-    if (threadIdx.x < 1u << args.k) {
-      C f;
-      f.x = T(args.d[2 * threadIdx.x]);
-      f.y = T(args.d[2 * threadIdx.x + 1]);
-      tab[threadIdx.x] = f;
-    }
+  __shared__ C tab[F == kTable ? 1 << kMaxK : 1];
+  auto entry = [&](int r) {
+    C f;
+    f.x = T(args.d[2 * r]);
+    f.y = T(args.d[2 * r + 1]);
+    return f;
+  };
+  auto fill = [&] {
+    if (threadIdx.x < 1u << args.k) tab[threadIdx.x] = entry(threadIdx.x);
     __syncthreads();
+  };
+  constexpr int n_e = F == kTable2 ? 4 : F == kTable1 ? 2 : 1;
+  C e[n_e];
+#pragma unroll
+  for (int r = 0; r < n_e; ++r) e[r] = entry(r);
+  bool filled = F != kTable;
+  if constexpr (LOW != kSkipLine) {
+    if (!filled) fill();
+    filled = true;
   }
-  C ph;
-  ph.x = T(args.d[0]);
-  ph.y = T(args.d[1]);
   const uint64_t stride = uint64_t(gridDim.x) * (256 * U);
   for (uint64_t g = uint64_t(blockIdx.x) * (256 * U) + threadIdx.x;
        g < args.n_items; g += stride) {
     uint64_t i[U];
     C v[U];
+    bool on[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       i[u] = g + 256 * u;
       for (int p = 0; p < args.npos; ++p)
         i[u] = insert_zero64(i[u], args.pos[p]);
       i[u] |= args.fixed_mask;
-      v[u] = stream_load<NT>(a + i[u]);
+      on[u] = (i[u] & args.lowmask) == args.lowmask;
+      if (LOW != kSkipLine || on[u]) v[u] = stream_load<NT>(a + i[u]);
+    }
+    if (!filled) {  // the work-group's threads take the same rounds
+      fill();
+      filled = true;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      C f = ph;
-      if constexpr (TABLE) {
+      C f = e[0];
+      if constexpr (F == kTable) {
         int r = 0;
         for (int j = 0; j < args.k; ++j)
           r |= int((i[u] >> args.tq[j]) & 1) << j;
         f = tab[r];
+      } else if constexpr (F != kPhase) {
+        f = csel((i[u] >> args.tq[0]) & 1, e[1], f);
+        if constexpr (F == kTable2)
+          f = csel((i[u] >> args.tq[1]) & 1,
+                   csel((i[u] >> args.tq[0]) & 1, e[3], e[2]), f);
       }
-      const bool on = (i[u] & args.lowmask) == args.lowmask;
-      if constexpr (SKIP) {
-        if (on) stream_store<NT>(a + i[u], cmul(v[u], f));
+      if constexpr (LOW != kKeep) {
+        if (on[u]) stream_store<NT>(a + i[u], cmul(v[u], f));
       } else {
-        stream_store<NT>(a + i[u], on ? cmul(v[u], f) : v[u]);
+        stream_store<NT>(a + i[u], on[u] ? cmul(v[u], f) : v[u]);
       }
     }
   }
@@ -388,23 +417,37 @@ hipError_t launch_diag(int prec, void* amp, int n, const HostGate& g,
                     args.n_items >= uint64_t(1) << 18;
   const bool nt = wide && streamed<float>(sizeof(float2) * args.n_items, low);
   const unsigned blocks = grid_blocks(args.n_items, wide ? 1024 : 256);
-#define QSV_DIAG_U(T, TABLE, SKIP, U, NT)                                   \
-  diag_kernel<T, TABLE, SKIP, U, NT><<<blocks, 256, 0, stream>>>(           \
+  // (n_items a multiple of 256: whole work-groups at the table's barrier)
+  const bool skip_line =
+      skip && (args.lowmask >> 3 & 1) && args.n_items >= 256 && !g.masked_phase;
+#define QSV_DIAG(T, F, LOW, U, NT)                                \
+  diag_kernel<T, F, LOW, U, NT><<<blocks, 256, 0, stream>>>(      \
       static_cast<CxT<T>::type*>(amp), args)
-#define QSV_DIAG(T, TABLE)                                                  \
-  (skip ? QSV_DIAG_U(T, TABLE, true, 1, false)                              \
-        : QSV_DIAG_U(T, TABLE, false, 1, false))
-#define QSV_DIAG_WIDE(TABLE)                                                \
-  (nt     ? QSV_DIAG_U(float, TABLE, false, 4, true)                        \
-   : wide ? QSV_DIAG_U(float, TABLE, false, 4, false)                       \
-          : QSV_DIAG(float, TABLE))
-  if (g.masked_phase)
-    prec == 1 ? QSV_DIAG_WIDE(false) : QSV_DIAG(double, false);
-  else
-    prec == 1 ? QSV_DIAG_WIDE(true) : QSV_DIAG(double, true);
+#define QSV_DIAG_LINE(T)                                          \
+  (g.k == 1   ? QSV_DIAG(T, kTable1, kSkipLine, 1, false)         \
+   : g.k == 2 ? QSV_DIAG(T, kTable2, kSkipLine, 1, false)         \
+              : QSV_DIAG(T, kTable, kSkipLine, 1, false))
+#define QSV_DIAG_LOW(T, F)                                        \
+  (skip ? QSV_DIAG(T, F, kSkip, 1, false) : QSV_DIAG(T, F, kKeep, 1, false))
+#define QSV_DIAG_WIDE(F)                                          \
+  (nt ? QSV_DIAG(float, F, kKeep, 4, true) : QSV_DIAG(float, F, kKeep, 4, false))
+  if (prec == 1) {
+    if (skip_line) QSV_DIAG_LINE(float);
+    else if (g.masked_phase)
+      wide ? QSV_DIAG_WIDE(kPhase) : QSV_DIAG_LOW(float, kPhase);
+    else if (wide) QSV_DIAG_WIDE(kTable);
+    else if (g.k == 1) QSV_DIAG_LOW(float, kTable1);
+    else if (g.k == 2) QSV_DIAG_LOW(float, kTable2);
+    else QSV_DIAG_LOW(float, kTable);
+  } else {
+    if (skip_line) QSV_DIAG_LINE(double);
+    else if (g.masked_phase) QSV_DIAG_LOW(double, kPhase);
+    else QSV_DIAG_LOW(double, kTable);
+  }
 #undef QSV_DIAG_WIDE
+#undef QSV_DIAG_LOW
+#undef QSV_DIAG_LINE
 #undef QSV_DIAG
-#undef QSV_DIAG_U
   return hipGetLastError();
 }
 
