@@ -221,7 +221,11 @@ static bool streamed(uint64_t bytes, int low) {
 template <typename T>
 static void dense_dispatch(void* amp, int k, unsigned blocks,
                            const DenseArgs& args, hipStream_t stream) {
-  if (streamed<T>((2 * sizeof(T) * args.n_groups) << k, args.pos[0]))
+  // (a control 2 KiB up, above the lowest target: 28 qubits complex64, control 8,
+  // target 4, 451 us cached and 468 streamed)
+  constexpr int kBit2K = sizeof(T) == 4 ? 8 : 7;
+  if (streamed<T>((2 * sizeof(T) * args.n_groups) << k, args.pos[0]) &&
+      !((args.cmask >> kBit2K & 1) && args.pos[0] < kBit2K))
     dense_dispatch_nt<T, true>(amp, k, blocks, args, stream);
   else
     dense_dispatch_nt<T, false>(amp, k, blocks, args, stream);
@@ -309,8 +313,8 @@ struct DiagArgs {
 // in registers (complex64), and under a control on qubit 3, half of whose
 // lines need not be read, not loading those and filling the table under the
 // first loads (27 qubits, one target, control 3: index 401, LDS 432, registers
-// 339 us complex64; 454, 540, 375 complex128; five targets 432, 440, 429 and
-// 484, 543, 493).  The other complex128 tables stay with LDS: 695 us where
+// 325 us complex64; 454, 540, 362 complex128; five targets 432, 440, 422 and
+// 484, 543, 479).  The other complex128 tables stay with LDS: 695 us where
 // registers take 725.
 enum DiagFactor { kPhase, kTable1, kTable2, kTable };
 enum DiagLow { kKeep, kSkip, kSkipLine };
@@ -409,13 +413,19 @@ hipError_t launch_diag(int prec, void* amp, int n, const HostGate& g,
   // full), and streamed where `streamed` says so.  complex128 gained nothing
   // from either (28 qubits, one-target table 1.44 and 1.43 ms) and lost under
   // low bits (CZ(3, 27) 0.37 -> 0.54), complex64 lost where lanes skip
-  // (CZ(3, 4) on 29 qubits 0.67 -> 0.76) and where the runs between the fixed
+  // (CZ(3, 4) on 29 qubits 0.67 -> 0.76), where the runs between the fixed
   // bits do not cover whole lines (CZ(2, 3) 1.22 -> 1.50; with lane-tested bits
-  // below, runs of one line neither gained nor lost): those take one.
+  // below, runs of one line neither gained nor lost) and, beyond half of the
+  // cache, where bit 8 is fixed, so that a thread's loads are 4 KiB apart and a
+  // work-group's miss every other 2 KiB (phase on qubit 8 of 27, 186 us with one
+  // load and 260 with four, of 24 19.8 and 18.3; qubits 7 and 9 of 27, 178 and
+  // 180 with one, 166 with four): those take one.
   const int low = args.npos ? args.pos[0] : n;
+  const uint64_t bytes = sizeof(float2) * args.n_items;
   const bool wide = prec == 1 && !skip && low >= (args.lowmask ? 5 : 4) &&
+                    !((args.fixed_mask >> 8 & 1) && bytes > kStreamBytes / 2) &&
                     args.n_items >= uint64_t(1) << 18;
-  const bool nt = wide && streamed<float>(sizeof(float2) * args.n_items, low);
+  const bool nt = wide && streamed<float>(bytes, low);
   const unsigned blocks = grid_blocks(args.n_items, wide ? 1024 : 256);
   // (n_items a multiple of 256: whole work-groups at the table's barrier)
   const bool skip_line =
