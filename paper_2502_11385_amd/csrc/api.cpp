@@ -33,14 +33,18 @@ struct qsv_state_s {
   // program buffer (device) and its pinned host staging copies
   char* prog_dev = nullptr;
   size_t prog_cap = 0;
-  // taken in turn, four for programs of up to kStageSmall bytes (parts of one
+  // Taken in turn, four for programs of up to kStageSmall bytes (parts of one
   // allocation) and the first two for larger ones: a call fills one while the
-  // device may still read the others; `done` follows the call's last kernel.
-  // With two, a queue of calls of about 30 us waited for the host's waking up
-  // from each event (9 qubits, 6 layers: 33.5 us a call, and 51.7 alone).
+  // device may still read the others.  Programs follow each other in a buffer
+  // while they fit, and `done` is recorded when it is left, behind the kernels
+  // that read it: an event per gate matrix of a few KiB cost 1.3 us of the
+  // stream's time (gates of 3 targets, 23 qubits complex64: 30.6 and 26.0 us).
+  // With two buffers a queue of calls of about 30 us waited for the host's
+  // waking up from each event (9 qubits, 6 layers: 33.5 us a call, 31 with four).
   struct Staging {
     char* host = nullptr;
     size_t cap = 0;
+    size_t used = 0;  // by programs since it was last free
     hipEvent_t done = nullptr;
     bool pending = false;
     bool own = false;  // an allocation of its own
@@ -159,6 +163,16 @@ bool pinned(char** p, size_t bytes) {
   return false;
 }
 
+// Leave the staging buffer under way: its event after the kernels so far.
+hipError_t leave_stage(qsv_state s) {
+  qsv_state_s::Staging& g = s->stage[s->stage_i];
+  const hipError_t e = hipEventRecord(g.done, s->stream);
+  if (e != hipSuccess) return e;
+  g.pending = true;
+  s->stage_i = (s->stage_i + 1) & 3;
+  return hipSuccess;
+}
+
 bool capturing(qsv_state s) {
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s->stream, &cs) != hipSuccess)
@@ -202,13 +216,21 @@ qsv_status upload(qsv_state s, const void* data, size_t bytes,
       s->stage[i].cap = kStageSmall;
     }
   }
-  s->stage_i &= room <= kStageSmall ? 3 : 1;
+  const bool large = room > kStageSmall;
+  {
+    const qsv_state_s::Staging& g = s->stage[s->stage_i];
+    if (!g.pending && g.used &&
+        (room > g.cap - g.used || (large && s->stage_i > 1)))
+      QSV_HIP(s, leave_stage(s));
+  }
+  if (large) s->stage_i &= 1;
   qsv_state_s::Staging& g = s->stage[s->stage_i];
   if (g.pending) {
     QSV_HIP(s, hipEventSynchronize(g.done));
     g.pending = false;
+    g.used = 0;
   }
-  if (room > g.cap) {
+  if (room > g.cap - g.used) {  // of an empty buffer: a full one was left
     if (g.own) QSV_HIP(s, hipHostFree(g.host));
     g.own = false;
     g.host = nullptr;
@@ -220,26 +242,25 @@ qsv_status upload(qsv_state s, const void* data, size_t bytes,
     g.own = true;
     g.cap = cap;
   }
-  std::memcpy(g.host, data, bytes);
+  char* at = g.host + g.used;
+  std::memcpy(at, data, bytes);
+  g.used = std::min(g.cap, g.used + ((room + 255) & ~size_t(255)));
   s->stage_open = true;
-  QSV_HIP(s, launch_upload(g.host, s->prog_dev, bytes, s->stream));
+  QSV_HIP(s, launch_upload(at, s->prog_dev, bytes, s->stream));
   return QSV_OK;
 }
 
-// Ends a call that may have uploaded: records the staging buffer's event
-// after the call's kernels (not between the upload and the kernels that read
-// it) and turns to the other buffer.
+// Ends a call that may have uploaded: leaves the staging buffer, behind the
+// call's kernels, unless programs like this one still fit into it.
 class UploadEnd {
  public:
   explicit UploadEnd(qsv_state s) : s_(s) {}
   ~UploadEnd() {
     if (!s_->stage_open) return;
     s_->stage_open = false;
-    qsv_state_s::Staging& g = s_->stage[s_->stage_i];
-    if (hipEventRecord(g.done, s_->stream) == hipSuccess) {
-      g.pending = true;
-      s_->stage_i = (s_->stage_i + 1) & 3;
-    } else {
+    const qsv_state_s::Staging& g = s_->stage[s_->stage_i];
+    if (g.used <= g.cap / 2) return;
+    if (leave_stage(s_) != hipSuccess) {
       (void)hipGetLastError();
       s_->failed = true;
     }
