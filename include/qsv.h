@@ -304,6 +304,11 @@ qsv_status qsv_plan_program_stats(const qsv_circuit* circ, int32_t n_qubits,
  * a negative count. */
 qsv_status qsv_debug_inject(int32_t kind, int32_t count);
 
+/* Testing aid: the passes of the last qsv_apply_fused (Section III.B's
+ * cache-blocked plan) that were launched while later ones were still being
+ * planned.  Errors: QSV_ERR_INVALID_ARG for a NULL state or out. */
+qsv_status qsv_debug_early_passes(qsv_state s, uint64_t* out);
+
 /* Testing aid (host only, no device work): plan the circuit with the
  * tiled strategy (Section III.B's cache blocking) for n_qubits <= 16,
  * build the exact device program the

@@ -59,6 +59,7 @@ struct qsv_state_s {
   char* scratch = nullptr;
   size_t scratch_cap = 0;
   uint64_t stats[13] = {0};
+  uint64_t early_passes = 0;  // of the last call
   // per-pass timing
   bool profiling = false;
   std::vector<hipEvent_t> evs;
@@ -251,15 +252,21 @@ qsv_status upload(qsv_state s, const void* data, size_t bytes,
 }
 
 // Ends a call that may have uploaded: leaves the staging buffer, behind the
-// call's kernels, unless programs like this one still fit into it.
+// call's kernels, unless programs like this one still fit.  Circuits leave it
+// always once there is a large buffer: the large ones take turns, so that both
+// get their size (may_launch_early), and asking whether the stream is idle
+// costs a marker of its own where no event ends the call before (17 qubits,
+// tiles of 9: 77 and 95 us a call).
 class UploadEnd {
  public:
-  explicit UploadEnd(qsv_state s) : s_(s) {}
+  explicit UploadEnd(qsv_state s, bool circuit = true)
+      : s_(s), circuit_(circuit) {}
   ~UploadEnd() {
     if (!s_->stage_open) return;
     s_->stage_open = false;
     const qsv_state_s::Staging& g = s_->stage[s_->stage_i];
-    if (g.used <= g.cap / 2) return;
+    const bool leave = circuit_ && (s_->stage[0].own || s_->stage[1].own);
+    if (!leave && g.used <= g.cap / 2) return;
     if (leave_stage(s_) != hipSuccess) {
       (void)hipGetLastError();
       s_->failed = true;
@@ -268,6 +275,7 @@ class UploadEnd {
 
  private:
   qsv_state s_;
+  bool circuit_;
 };
 
 qsv_status parse_circuit(const qsv_circuit* circ, int n,
@@ -521,7 +529,7 @@ qsv_status qsv_apply_gate(qsv_state s, const int32_t* targets, int32_t k,
   std::string err = make_gate(s->n, k, c, qs.data(), matrix, &g);
   if (!err.empty()) return fail(QSV_ERR_INVALID_ARG, err);
   if ((st = select_device(s)) != QSV_OK) return st;
-  UploadEnd end(s);
+  UploadEnd end(s, false);
   if (g.diagonal) {
     QSV_HIP(s, launch_diag(s->prec, s->amp, s->n, g, s->stream));
   } else if (block_gate(g)) {
@@ -665,7 +673,10 @@ static size_t outputs_bound(qsv_state s, const PlanOptions& po,
 }
 
 // Only where no buffer can need to grow once a pass has been launched, so
-// that a failed allocation still leaves the state as it was.
+// that a failed allocation still leaves the state as it was.  The large staging
+// buffers grow to program_bound one at a time, with the first two programs of
+// more than kStageSmall bytes: those two are launched whole, and so is every
+// circuit whose program stays below (on 20 qubits up to about 450 gates).
 static bool may_launch_early(qsv_state s, const std::vector<HostGate>& G,
                              const PlanOptions& po, const qsv_outputs* o) {
   // (below the width where the planner searches, planning is quick)
@@ -1030,6 +1041,7 @@ static qsv_status apply_fused_impl(qsv_state s, const qsv_circuit* circ,
       QSV_HIP(s, hipEventRecord(s->evs[2 * pi + 1], s->stream));
   }
   early.whole = true;
+  s->early_passes = done;
   s->stats[0] = plan.passes.size();
   s->stats[1] = G.size();
   s->stats[2] = plan.alg_bytes;
@@ -1344,6 +1356,13 @@ qsv_status qsv_last_plan_stats(qsv_state s, uint64_t* out, int32_t n_out) {
   if (!out || n_out < 0 || n_out > 13)
     return fail(QSV_ERR_INVALID_ARG, "bad stats buffer");
   for (int i = 0; i < n_out; ++i) out[i] = s->stats[i];
+  return QSV_OK;
+}
+
+qsv_status qsv_debug_early_passes(qsv_state s, uint64_t* out) {
+  if (!s) return fail(QSV_ERR_INVALID_ARG, "null state");
+  if (!out) return fail(QSV_ERR_INVALID_ARG, "null output");
+  *out = s->early_passes;
   return QSV_OK;
 }
 

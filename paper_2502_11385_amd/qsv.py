@@ -55,6 +55,7 @@ EXPORTED = [
     "qsv_server_create", "qsv_server_submit", "qsv_server_wait",
     "qsv_server_release", "qsv_server_stats", "qsv_server_destroy",
     "qsv_server_wait_timeout", "qsv_server_cancel", "qsv_debug_inject",
+    "qsv_debug_early_passes",
     "qsv_clock", "qsv_debug_emulate_tiled", "qsv_plan_program_stats",
     "qsv_cut_workspace_bytes", "qsv_cut_reconstruct",
     "qsv_top_k", "qsv_expectation_pauli", "qsv_permute_qubits",
@@ -186,6 +187,7 @@ _SIGS = {
     "qsv_server_wait_timeout": [_p, _u64, C.c_double, C.POINTER(qsv_result)],
     "qsv_server_cancel": [_p, _u64],
     "qsv_debug_inject": [_i32, _i32],
+    "qsv_debug_early_passes": [_p, _pu64],
     "qsv_server_release": [_p, _u64],
     "qsv_server_stats": [_p, _pu64, _i32],
     "qsv_server_destroy": [_p],
@@ -505,6 +507,13 @@ class State:
                 "fused_passes", "segments", "plan_ns", "tile_ops",
                 "phase_blocks", "block_gates", "folded_outputs", "tile_flops")
         return {k: int(v) for k, v in zip(keys, out)}
+
+    def early_passes(self) -> int:
+        """Passes of the last apply_fused launched while later ones were
+        being planned (for tests)."""
+        v = C.c_uint64(0)
+        _check(_lib.qsv_debug_early_passes(self._h, C.byref(v)))
+        return v.value
 
     def set_profiling(self, enable: bool):
         _check(_lib.qsv_set_profiling(self._h, 1 if enable else 0))
