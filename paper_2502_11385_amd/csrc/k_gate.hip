@@ -419,17 +419,31 @@ hipError_t launch_diag(int prec, void* amp, int n, const HostGate& g,
   // cache, where bit 8 is fixed, so that a thread's loads are 4 KiB apart and a
   // work-group's miss every other 2 KiB (phase on qubit 8 of 27, 186 us with one
   // load and 260 with four, of 24 19.8 and 18.3; qubits 7 and 9 of 27, 178 and
-  // 180 with one, 166 with four): those take one.
+  // 180 with one, 166 with four): those take one.  So do phases on 2^29
+  // amplitudes and more (31 qubits, CZ(4, 15) 1.40 and 1.58 ms, a phase on
+  // qubit 30 2.72 and 2.85), where a thread's rounds are 2 GiB apart.
   const int low = args.npos ? args.pos[0] : n;
   const uint64_t bytes = sizeof(float2) * args.n_items;
   const bool wide = prec == 1 && !skip && low >= (args.lowmask ? 5 : 4) &&
                     !((args.fixed_mask >> 8 & 1) && bytes > kStreamBytes / 2) &&
+                    !(g.masked_phase && args.n_items >= uint64_t(1) << 29) &&
                     args.n_items >= uint64_t(1) << 18;
   const bool nt = wide && streamed<float>(bytes, low);
-  const unsigned blocks = grid_blocks(args.n_items, wide ? 1024 : 256);
-  // (n_items a multiple of 256: whole work-groups at the table's barrier)
+  // (n_items a multiple of 256: whole work-groups at the table's barrier; beyond
+  // 2^29 complex64 gains less from the lines left out than from full rows: one
+  // target on 30 qubits 2.71 and 2.35 ms, 2.50 with the index)
   const bool skip_line =
-      skip && (args.lowmask >> 3 & 1) && args.n_items >= 256 && !g.masked_phase;
+      skip && (args.lowmask >> 3 & 1) && args.n_items >= 256 && !g.masked_phase &&
+      (prec == 2 || args.n_items < uint64_t(1) << 29);
+  // Several rounds, a grid of 2^20 work-groups, are worth more than one up to
+  // 2^31 amplitudes where complex64 has one load in flight (phase on qubit 3 of
+  // 30: 2.36 and 2.48 ms) and where a table is filled under the loads (complex128
+  // with three targets, control 3, 30 qubits: 3.31 and 3.59; 3.04 with the
+  // index).  The others: complex64 one-target table on 31 qubits 6.11 and 5.58,
+  // complex128 phase on qubit 0 of 30 6.5 and 5.8.
+  const bool rounds = (prec == 1 && !wide) || (skip_line && g.k > 2);
+  const unsigned blocks = grid_blocks(args.n_items, wide ? 1024 : 256,
+                                      rounds ? 1u << 20 : 1u << 23);
 #define QSV_DIAG(T, F, LOW, U, NT)                                \
   diag_kernel<T, F, LOW, U, NT><<<blocks, 256, 0, stream>>>(      \
       static_cast<CxT<T>::type*>(amp), args)

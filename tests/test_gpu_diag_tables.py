@@ -48,3 +48,35 @@ def test_tables_under_controls(n, prec):
                 err = np.max(np.abs(s.get() - want))
                 assert err <= 4 * EPS[prec], (k, controls, t, err)
     s.free()
+
+
+# From 2^29 amplitudes up other forms are chosen, and a grid may take several
+# rounds over them.
+@pytest.mark.parametrize("prec", [qsv.QSV_C64, qsv.QSV_C128])
+@pytest.mark.parametrize("targets,control", [([7], 3), ([7, 15], 3),
+                                             ([0, 7, 15], 3), ([7], None),
+                                             ([4], 15)])
+def test_tables_and_phases_of_large_states(targets, control, prec):
+    n = 30
+    dtype = torch.complex64 if prec == qsv.QSV_C64 else torch.complex128
+    rng = np.random.default_rng(n)
+    row = rng.uniform(-.7, .7, 1 << 16) + 1j * rng.uniform(-.7, .7, 1 << 16)
+    row = torch.tensor(row, dtype=dtype, device="cuda")
+    psi = row.repeat(1 << (n - 16))
+    d = np.exp(1j * rng.uniform(0, 6.28, 1 << len(targets)))
+    if targets == [4]:
+        d[0] = 1                 # a phase where the target is 1
+    want = oracle.apply_gate(row.cpu().numpy().astype(np.complex128), 16,
+                             np.diag(d), targets,
+                             [] if control is None else [control])
+    want = torch.tensor(want, device="cuda")
+    torch.cuda.synchronize()
+    s = qsv.State(n, prec, tensor=psi)
+    s.apply_gate(targets, np.diag(d), [] if control is None else [control])
+    s.sync()
+    err = max(float((p - want).abs().max())
+              for p in psi.view(-1, 1 << 8, 1 << 16))
+    assert err <= 4 * EPS[prec], err
+    s.free()
+    del psi
+    torch.cuda.empty_cache()
