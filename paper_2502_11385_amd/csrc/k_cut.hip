@@ -182,17 +182,15 @@ __global__ void __launch_bounds__(256)
 // V stays in registers over all rows and W is formed once per row, where a
 // wave per 64 outcomes formed both again for each block and waited for their
 // loads.  2^28 outcomes, 2 cuts, n_c = 4: 0.88 -> 0.39 ms a call, 5.5 TB/s.
-// Where there are fewer W than threads, the terms of their sums over u are
-// formed by all the threads, a round at a time, and added in increasing u as
-// one thread would: a thread per W alone made few outcomes with many cuts wait
-// for a chain of 4^cuts loads (12 qubits, 4 cuts, n_u = 64: 95 -> 40 us a call).
-template <int NC>
+// ALL: the terms of the sums over u are formed by all the threads, a round at a
+// time, and added in increasing u as one thread would: a thread per W alone made
+// few outcomes with many cuts wait for a chain of 4^cuts loads (12 qubits, 4
+// cuts, n_u = 64: 95 -> 40 us a call).
+template <int NC, bool ALL>
 __global__ void __launch_bounds__(256)
     cut_kron_tile_kernel(CutArgs a, const double* __restrict__ T,
                          double* __restrict__ out, int rows_log) {
   __shared__ double W[(1 << kCutRowsLog) * NC];
-  __shared__ double P[2 * 256];  // a round's terms, two rounds in turn
-  __shared__ uint32_t Y[kCutMaxSub << kCutRowsLog];
   const uint32_t tid = threadIdx.x;
   const int chunk_log = a.n_free - rows_log;
   const uint64_t chunk = blockIdx.x & ((uint64_t(1) << chunk_log) - 1);
@@ -205,41 +203,53 @@ __global__ void __launch_bounds__(256)
     x0 |= ((chunk >> i) & 1) << a.free_pos[rows_log + i];
   const int rows = 1 << rows_log;
   const uint64_t n_u = a.n_u;
-  // output index of each uniform subcircuit in each row
-  for (int i = tid; i < rows * a.n_uni; i += 256) {
+  const int n_w = rows * NC;
+  auto row_x = [&](int f) {
     uint64_t x = x0;
     for (int b = 0; b < rows_log; ++b)
-      x |= uint64_t((i >> b) & 1) << a.free_pos[b];
-    Y[i] = uint32_t(cut_gather(a.subs[a.uni_sub[i >> rows_log]], x));
-  }
-  __syncthreads();
-  auto term = [&](int i, uint64_t u) {
-    const int f = i / NC, c = i % NC;
-    const uint64_t* row = a.ttu + (uint64_t(c) * n_u + u) * uint64_t(a.n_uni);
-    double prod = 1.0;
-    for (int k = 0; k < a.n_uni; ++k)
-      prod *= T[row[k] + Y[(k << rows_log) + f]];
-    return prod;
+      x |= uint64_t((f >> b) & 1) << a.free_pos[b];
+    return x;
   };
-  const int n_w = rows * NC;
-  const uint64_t per = n_w < 256 ? 256 / n_w : 1;  // threads per W
-  if (per == 1 || n_u == 1) {
+  if constexpr (!ALL) {
     for (int i = tid; i < n_w; i += 256) {
+      const int f = i / NC, c = i % NC;
+      const uint64_t x = row_x(f);
       double sum = 0.0;
-      for (uint64_t u = 0; u < n_u; ++u) sum += term(i, u);
+      for (uint64_t u = 0; u < n_u; ++u) {
+        const uint64_t* row = a.ttu + (uint64_t(c) * n_u + u) * uint64_t(a.n_uni);
+        double prod = 1.0;
+        for (int k = 0; k < a.n_uni; ++k)
+          prod *= T[row[k] + cut_gather(a.subs[a.uni_sub[k]], x)];
+        sum += prod;
+      }
       W[i] = sum;
     }
   } else {
-    const uint64_t step = per < n_u ? per : n_u;  // powers of two
-    const int i = int(tid) & (n_w - 1);
-    const uint64_t g = tid / n_w;
+    __shared__ double P[2 * 256];  // a round's terms, two rounds in turn
+    __shared__ uint32_t Y[kCutMaxSub << kCutRowsLog];
+    // output index of each uniform subcircuit in each row
+    for (int i = tid; i < rows * a.n_uni; i += 256)
+      Y[i] = uint32_t(cut_gather(a.subs[a.uni_sub[i >> rows_log]],
+                                 row_x(i & (rows - 1))));
+    __syncthreads();
+    const uint32_t per = 256 / n_w;  // threads per W: a power of two, as n_u is
+    const uint32_t step = per < n_u ? per : uint32_t(n_u);
+    const uint32_t i = tid & (n_w - 1), g = tid / n_w;
+    const int f = i / NC, c = i % NC;
     double sum = 0.0;
     int buf = 0;
     for (uint64_t u = 0; u < n_u; u += step, buf ^= 256) {
-      if (g < step) P[buf + g * n_w + i] = term(i, u + g);
+      if (g < step) {
+        const uint64_t* row =
+            a.ttu + (uint64_t(c) * n_u + u + g) * uint64_t(a.n_uni);
+        double prod = 1.0;
+        for (int k = 0; k < a.n_uni; ++k)
+          prod *= T[row[k] + Y[(k << rows_log) + f]];
+        P[buf + g * n_w + i] = prod;
+      }
       __syncthreads();
       if (g == 0)
-        for (uint64_t j = 0; j < step; ++j) sum += P[buf + j * n_w + i];
+        for (uint32_t j = 0; j < step; ++j) sum += P[buf + j * n_w + i];
     }
     if (g == 0) W[i] = sum;
   }
@@ -291,7 +301,15 @@ static void launch_cut_tile(const CutArgs& a, double* out,
   int rows_log = a.n_free < kCutRowsLog ? a.n_free : kCutRowsLog;
   while (rows_log > 2 && a.n_vary_hi + a.n_free - rows_log < 10) --rows_log;
   const unsigned blocks = 1u << (a.n_vary_hi + a.n_free - rows_log);
-  cut_kron_tile_kernel<NC><<<blocks, 256, 0, stream>>>(a, a.T, out, rows_log);
+  // All the threads form the terms where they outnumber W and its sums are long:
+  // 20 qubits with NC = 16 and n_u = 1 take 20.4 us without and 23.6 with, n_u =
+  // 4 23.8 and 26.8, n_u = 16 52 and 49; NC = 4 with n_u = 16 34 and 21.
+  if ((NC << rows_log) <= 128 && a.n_u >= (NC > 4 ? NC : 4))
+    cut_kron_tile_kernel<NC, true><<<blocks, 256, 0, stream>>>(a, a.T, out,
+                                                               rows_log);
+  else
+    cut_kron_tile_kernel<NC, false><<<blocks, 256, 0, stream>>>(a, a.T, out,
+                                                                rows_log);
 }
 
 hipError_t launch_cut(const CutArgs& a, double* out, hipStream_t stream) {
