@@ -150,7 +150,8 @@ typedef enum {
  *   low_qubits : qubits 0..low_qubits-1 belong to every tile so that HBM
  *                accesses are contiguous runs (default 4)
  *   reg_log2   : amplitudes per thread inside a tile, as log2: 3, 4 or 5
- *                (5 for c64 only; default 4)
+ *                (5 for c64 only; default 4, or 3 where a tile of at most
+ *                2^12 holds the whole state)
  * This is the single-GPU form of the chunking and cache blocking of
  * Section III.B: a tile of 2^L amplitudes plays the role of a 2^nc chunk
  * (blocking_qubits), and the planner reorders commuting gates so that runs
@@ -676,8 +677,9 @@ qsv_status qsv_cut_workspace_bytes(const qsv_cut_spec* spec, uint64_t* bytes);
  *   out_dev    : device, 2^n_qubits FP64, written (bit q of the index =
  *                uncut qubit q)
  * All arithmetic is FP64.  The call validates everything on the host first
- * (nothing is launched on an error), copies its tables into the workspace on
- * the stream, waits for that copy, then enqueues two kernels and returns. */
+ * (nothing is launched on an error), enqueues kernels on the stream and
+ * returns.  Its tables travel to the workspace as kernel arguments up to 14080
+ * bytes; larger ones are copied there, and the call waits for that copy. */
 qsv_status qsv_cut_reconstruct(const qsv_cut_spec* spec, const void* probs_dev,
                                int32_t probs_fp64, uint64_t probs_elems,
                                const uint64_t* offsets, void* workspace,

@@ -73,7 +73,7 @@ enum : int32_t {
 //  gctrl: controls outside the tile as a mask of global qubits.
 struct alignas(16) TileOp {
   // kernel header (32 bytes)
-  int32_t code;   // class << 3 | reg (see kCode*)
+  int32_t code;   // class << 6 | mux register << 3 | reg (see kCode*)
   int32_t arg;    // mux bit or outer mux qubit; target count for kCodeDiag
   uint32_t lctrl;
   int32_t blob;   // kOpPhaseBlock only
